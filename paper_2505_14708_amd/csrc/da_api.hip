@@ -92,7 +92,7 @@ Workspace plan_workspace(const Geo& q, long long lists_cap = 0) {
   // the bf16 attention kernel reads Q and writes O in the original token order: no reordered copies of them
   const bool direct = q.dtype == DA_BF16;
   size_t off = 0;
-  w.qp = off; off += direct ? 0 : big;
+  w.qp = off; off += direct ? 0 : big;   // (float32: qp, kp, vt and op are not used; the size callers were told stays)
   w.kp = off; off += big;
   w.vt = off; off += big;
   w.op = off; off += direct ? 0 : big;
@@ -104,6 +104,38 @@ Workspace plan_workspace(const Geo& q, long long lists_cap = 0) {
   w.select = off; off += lists_cap > 0 ? align_up(select_global_workspace(q)) : 0;
   w.total = off;
   return w;
+}
+
+// in / out: where the caller's Q, K, V and O live (NULL: contiguous); reordered: their rows are the slots of
+// Algorithm 1's order instead of tokens
+int set_layout(Geo& q, const da_layout* in, const da_layout* out, int reordered) {
+  if (reordered != 0 && reordered != 1) return DA_ERR_DIM;
+  q.reordered = reordered;
+  const long long rows = reordered ? q.n_pad : q.n;
+  const long long per = q.dtype == DA_BF16 ? 8 : 4;   // elements per 16 bytes
+  Rows dflt;
+  dflt.sn = q.d; dflt.sh = rows * q.d; dflt.sb = (long long)q.H * rows * q.d;
+  q.in = q.out = dflt;
+  const da_layout* given[2] = {in, out};
+  Rows* into[2] = {&q.in, &q.out};
+  for (int t = 0; t < 2; ++t) {
+    if (!given[t]) continue;
+    const da_layout& l = *given[t];
+    if (l.stride_n < q.d || l.stride_h < 1 || l.stride_b < 1) return DA_ERR_DIM;
+    if (l.stride_n % per || l.stride_h % per || l.stride_b % per) return DA_ERR_ALIGN;
+    // the last element must be addressable with 63-bit offsets, with room to spare
+    if ((double)q.B * (double)l.stride_b + (double)q.H * (double)l.stride_h + (double)rows * (double)l.stride_n > 4.0e15)
+      return DA_ERR_DIM;
+    into[t]->sb = l.stride_b; into[t]->sh = l.stride_h; into[t]->sn = l.stride_n;
+  }
+  return DA_OK;
+}
+
+// float32 attention on the tensors of da_permute: rows in slot order, V block-transposed
+hipError_t attn_f32_reordered(Geo q, const void* Qp, const void* Kp, const void* Vt, const int32_t* idx,
+                              const int32_t* row_ptr, long long cap, void* Op, float* lse, hipStream_t s) {
+  set_layout(q, nullptr, nullptr, 1);
+  return launch_attn_f32(q, (const float*)Qp, (const float*)Kp, (const float*)Vt, true, idx, row_ptr, cap, (float*)Op, lse, s);
 }
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? DA_OK : DA_ERR_HIP; }
@@ -196,8 +228,7 @@ int da_sparse_attn(const da_problem* p, const void* Qp, const void* Kp, const vo
   hipStream_t s = (hipStream_t)stream;
   if (q.dtype == DA_BF16)
     return hip_status(launch_attn_bf16_ring(q, Qp, Kp, Vt, idx, nullptr, 0, Op, lse, false, nullptr, s));
-  return hip_status(
-      launch_attn_f32(q, (const float*)Qp, (const float*)Kp, (const float*)Vt, idx, nullptr, 0, (float*)Op, lse, s));
+  return hip_status(attn_f32_reordered(q, Qp, Kp, Vt, idx, nullptr, 0, Op, lse, s));
 }
 
 int da_sparse_attn_ex(const da_problem* p, const void* Q, const void* Kp, const void* Vt, const int32_t* idx, void* O,
@@ -213,8 +244,7 @@ int da_sparse_attn_ex(const da_problem* p, const void* Q, const void* Kp, const 
   if (!attn_supported(q)) return DA_ERR_UNSUPPORTED;
   if (q.dtype != DA_BF16) {
     if (original_order || tile_counts) return DA_ERR_UNSUPPORTED;
-    return hip_status(launch_attn_f32(q, (const float*)Q, (const float*)Kp, (const float*)Vt, idx, nullptr, 0, (float*)O,
-                                      lse, (hipStream_t)stream));
+    return hip_status(attn_f32_reordered(q, Q, Kp, Vt, idx, nullptr, 0, O, lse, (hipStream_t)stream));
   }
   return hip_status(launch_attn_bf16_ring(q, Q, Kp, Vt, idx, nullptr, 0, O, lse, original_order != 0,
                                           (unsigned long long*)tile_counts, (hipStream_t)stream));
@@ -229,31 +259,6 @@ int da_wait_failures(uint64_t* count) {
 }
 
 // da_forward and da_forward_global: the same launches but for the selection
-// in / out: where the caller's Q, K, V and O live (NULL: contiguous); reordered: their rows are the slots of
-// Algorithm 1's order instead of tokens
-static int set_layout(Geo& q, const da_layout* in, const da_layout* out, int reordered) {
-  if (reordered != 0 && reordered != 1) return DA_ERR_DIM;
-  q.reordered = reordered;
-  const long long rows = reordered ? q.n_pad : q.n;
-  const long long per = q.dtype == DA_BF16 ? 8 : 4;   // elements per 16 bytes
-  Rows dflt;
-  dflt.sn = q.d; dflt.sh = rows * q.d; dflt.sb = (long long)q.H * rows * q.d;
-  q.in = q.out = dflt;
-  const da_layout* given[2] = {in, out};
-  Rows* into[2] = {&q.in, &q.out};
-  for (int t = 0; t < 2; ++t) {
-    if (!given[t]) continue;
-    const da_layout& l = *given[t];
-    if (l.stride_n < q.d || l.stride_h < 1 || l.stride_b < 1) return DA_ERR_DIM;
-    if (l.stride_n % per || l.stride_h % per || l.stride_b % per) return DA_ERR_ALIGN;
-    // the last element must be addressable with 63-bit offsets, with room to spare
-    if ((double)q.B * (double)l.stride_b + (double)q.H * (double)l.stride_h + (double)rows * (double)l.stride_n > 4.0e15)
-      return DA_ERR_DIM;
-    into[t]->sb = l.stride_b; into[t]->sh = l.stride_h; into[t]->sn = l.stride_n;
-  }
-  return DA_OK;
-}
-
 static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in, const da_layout* out, int reordered,
                         const void* Q, const void* K, const void* V, void* O, int32_t* idx_out, int32_t* row_ptr_out,
                         void* ws, size_t ws_bytes, void* stream) {
@@ -272,10 +277,8 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   Workspace w = plan_workspace(q, cap);
   if (ws_bytes < w.total) return DA_ERR_WORKSPACE;
   char* base = (char*)ws;
-  void* qp = base + w.qp;
   void* kp = base + w.kp;
   void* vt = base + w.vt;
-  void* op = base + w.op;
   float* q_pool = (float*)(base + w.q_pool);
   float* k_pool = (float*)(base + w.k_pool);
   float* logits = (float*)(base + w.logits);
@@ -286,10 +289,10 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   const bool bf16 = q.dtype == DA_BF16;
   // Definition 3.2: pooled Q~, K~ and the draft logits (the ranking of a row of the draft
   // map is the ranking of its logits, so the softmax itself is not needed here).
-  // The pooling pass also writes the reordered K of Algorithm 1 (one read of K for both).  With bf16, Q is
-  // not copied at all: the attention kernel reads its query rows from their original places and
-  // writes O's rows back to theirs, which is Algorithm 1 for Q and Algorithm 2 for O done by
-  // addressing (a row of 256 bytes is contiguous in either order).
+  // With bf16 the pooling pass also writes the reordered K of Algorithm 1 (one read of K for both); Q is not copied at
+  // all: the attention kernel reads its query rows from their original places and writes O's rows back to theirs,
+  // which is Algorithm 1 for Q and Algorithm 2 for O done by addressing (a row of 256 bytes is contiguous in either
+  // order).  The float32 attention brings every tile in by way of registers and takes K and V by addressing as well.
   // (K that already is a contiguous reordered tensor is used where it is.)
   const bool k_in_place = bf16 && q.reordered && q.in.sn == q.d && q.in.sh == q.n_pad * q.d &&
                           q.in.sb == (long long)q.H * q.n_pad * q.d;
@@ -298,11 +301,10 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   // 0 .. g-1 whatever the draft map says, so pooling, logits and selection are left out and only Algorithm 1 runs.
   const bool all_kept = whole_map ? budget == (long long)q.g * q.g : q.k == q.g;
   if (all_kept) {
-    if (!k_in_place && (e = launch_permute(q, K, kp, DA_REORDER_ROWS, s)) != hipSuccess) return DA_ERR_HIP;
-    if (!bf16 && (e = launch_permute(q, Q, qp, DA_REORDER_ROWS, s)) != hipSuccess) return DA_ERR_HIP;
+    if (bf16 && !k_in_place && (e = launch_permute(q, K, kp, DA_REORDER_ROWS, s)) != hipSuccess) return DA_ERR_HIP;
     e = launch_all_lists(q, idx, row_ptr, whole_map ? cap : (long long)q.g * q.g, s);
   } else {
-    if ((e = launch_pool_reorder(q, Q, K, q_pool, k_pool, bf16 ? nullptr : qp, k_in_place ? nullptr : kp, s)) !=
+    if ((e = launch_pool_reorder(q, Q, K, q_pool, k_pool, nullptr, bf16 && !k_in_place ? kp : nullptr, s)) !=
         hipSuccess)
       return DA_ERR_HIP;
     if ((e = launch_draft_logits(q, q_pool, k_pool, logits, s)) != hipSuccess) return DA_ERR_HIP;
@@ -313,14 +315,13 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
       e = launch_select(q, logits, idx, nullptr, true, s);
   }
   if (e != hipSuccess) return DA_ERR_HIP;
-  // Algorithm 1: reorder V (block-transposed; for bf16 as matrix operands)
-  if ((e = launch_permute(q, V, vt, bf16 ? DA_REORDER_VOP : DA_REORDER_VT, s)) != hipSuccess) return DA_ERR_HIP;
+  if (!bf16)
+    return hip_status(launch_attn_f32(q, (const float*)Q, (const float*)K, (const float*)V, false, idx, row_ptr, cap,
+                                      (float*)O, nullptr, s));
+  // Algorithm 1: reorder V (block-transposed, as matrix operands)
+  if ((e = launch_permute(q, V, vt, DA_REORDER_VOP, s)) != hipSuccess) return DA_ERR_HIP;
   // SparseAttn
-  if (bf16) return hip_status(launch_attn_bf16_ring(q, Q, kp, vt, idx, row_ptr, cap, O, nullptr, true, nullptr, s));
-  e = launch_attn_f32(q, (const float*)qp, (const float*)kp, (const float*)vt, idx, row_ptr, cap, (float*)op, nullptr, s);
-  if (e != hipSuccess) return DA_ERR_HIP;
-  // Algorithm 2: restore
-  return hip_status(launch_permute(q, op, O, DA_RESTORE, s));
+  return hip_status(launch_attn_bf16_ring(q, Q, kp, vt, idx, row_ptr, cap, O, nullptr, true, nullptr, s));
 }
 
 int da_forward(const da_problem* p, const void* Q, const void* K, const void* V, void* O, int32_t* idx_out,
@@ -389,8 +390,7 @@ int da_sparse_attn_lists(const da_problem* p, const void* Qp, const void* Kp, co
   if (!attn_supported(q, true)) return DA_ERR_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   if (q.dtype == DA_BF16) return hip_status(launch_attn_bf16_ring(q, Qp, Kp, Vt, cols, row_ptr, cap, Op, lse, false, nullptr, s));
-  return hip_status(launch_attn_f32(q, (const float*)Qp, (const float*)Kp, (const float*)Vt, cols, row_ptr, cap,
-                                    (float*)Op, lse, s));
+  return hip_status(attn_f32_reordered(q, Qp, Kp, Vt, cols, row_ptr, cap, Op, lse, s));
 }
 
 int da_forward_global(const da_problem* p, const void* Q, const void* K, const void* V, void* O, int32_t* row_ptr_out,

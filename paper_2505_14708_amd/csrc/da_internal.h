@@ -93,8 +93,9 @@ hipError_t launch_select(const Geo& q, const float* scores, int32_t* idx, uint8_
 hipError_t launch_all_lists(const Geo& q, int32_t* idx, int32_t* row_ptr, long long head_stride, hipStream_t s);
 // idx: k columns per row; or, with row_ptr [B,H,g+1], lists of any length, the lists of head bh one after the
 // other from idx + bh * cap on
-hipError_t launch_attn_f32(const Geo& q, const float* Qp, const float* Kp, const float* Vt, const int32_t* idx,
-                           const int32_t* row_ptr, long long cap, float* Op, float* lse, hipStream_t s);
+// The rows of Q, K, V and O are where q.in, q.out and q.reordered say (v_transposed: V is in the DA_REORDER_VT layout)
+hipError_t launch_attn_f32(const Geo& q, const float* Q, const float* K, const float* V, bool v_transposed,
+                           const int32_t* idx, const int32_t* row_ptr, long long cap, float* O, float* lse, hipStream_t s);
 // whole-map threshold selection (k_select_global.hip)
 size_t select_global_workspace(const Geo& q);
 // device address, on the current device, of the library's built-in scratch (DA_STATIC_SCRATCH_BYTES bytes)
