@@ -2,10 +2,24 @@
 //
 // The kept-block decision is taken from these logits, so they are evaluated in float32 with
 // one fixed order that a CPU can repeat bit for bit: acc = fma(q[c], k[c], acc) for c ascending
-// (the IEEE fused multiply-add: one instruction and one rounding per term; no matrix cores, no
-// split sums), then one multiply by float(1/sqrt(d)).  The work is a register-tiled product
-// on the vector ALUs: a workgroup owns a 128x128 tile of L, a thread an 8x8 piece; Q~ and K~
-// pieces go through LDS transposed so a thread reads its 8 rows / 8 columns as 16-byte loads.
+// (the IEEE fused multiply-add: one rounding per term; no split sums), then one multiply by
+// float(1/sqrt(d)).  v_mfma_f32_32x32x2_f32 computes exactly that chain: an output is
+// fma(a1, b1, fma(a0, b0, c)) with each step rounded once, to nearest even, subnormals kept (its
+// results equal fmaf's bit for bit on random, widely scaled, subnormal and overflowing operands,
+// and the parity tests hold every logit against the chain).  So the product runs on the matrix
+// cores at twice the rate of one fused multiply-add per lane and cycle.
+//
+// A workgroup of four waves owns a 64x64 tile of L, a wave a 32x32 quarter of it.  Channels come through LDS 32 at a
+// time, the next 32 on their way to registers meanwhile; a row is stored with its even channels first and its odd ones
+// behind, because lanes 0..31 of an instruction hold channel 2t and lanes 32..63 channel 2t + 1: one 16-byte read then
+// serves four instructions.
+//
+// Measured against an 8x8 piece per thread of a 128x128 tile on the vector ALUs (at its issue rate on large maps, four
+// workgroups on small ones): 24 x 1980 x 1980 x 128 channels 295 -> 280 us, 24 x 588 x 588 53 -> 38 us,
+// 5 x 1260 x 1260 40 -> 33 us, 48 x 28 x 28 25 -> 5.5 us, 2 x 8 x 8 (64 channels) 13.4 -> 3.7 us.  On the largest the
+// products alone take 220 us (110 TFLOP/s; the instruction reaches 130 in a bare loop) and the writing of the map, whose
+// rows start anywhere in a cache line, adds the rest.  128x128 tiles measure the same there (282 us), 12 us where 64x64
+// take 5; a stretch of consecutive tiles per XCD changes nothing (278 us).
 #include <math.h>
 #include "da_internal.h"
 
@@ -15,89 +29,105 @@
 
 namespace da {
 
-constexpr int TM = 128;   // tile rows (query blocks) and columns (key blocks)
-constexpr int TC = 16;    // channels per LDS stage
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int TM = 64;         // tile rows (query blocks) and columns (key blocks) of a workgroup
+constexpr int TC = 32;         // channels per LDS stage
+constexpr int LDR = TC + 4;    // padded row: the 16-byte reads of 32 rows meet no bank conflict
 
 __global__ __launch_bounds__(256) void draft_logits_kernel(Geo q, const float* __restrict__ q_pool,
                                                            const float* __restrict__ k_pool, float* __restrict__ logits,
                                                            float scale) {
-  __shared__ __attribute__((aligned(16))) float qs[TC][TM];
-  __shared__ __attribute__((aligned(16))) float ks[TC][TM];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
+  constexpr int NV = TM * (TC / 4) / 256;              // 16-byte loads of a stage per thread and matrix
+  __shared__ __attribute__((aligned(16))) float smem[2 * TM * LDR];
+  float* const qs = smem;
+  float* const ks = smem + TM * LDR;
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const long long bh = blockIdx.z;
   const int row0 = blockIdx.y * TM, col0 = blockIdx.x * TM;
+  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;   // the wave's corner of the tile
   const float* qb = q_pool + bh * (long long)q.g * q.d;
   const float* kb = k_pool + bh * (long long)q.g * q.d;
-  float acc[8][8];
+  f32x16 acc;
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) acc[a][b] = 0.f;
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 
-  // loader: thread -> (row r = tid/2, half of the TC channels), as 16-byte loads (d is a multiple of 4).  The next
-  // stage's loads are asked for before the current stage is multiplied.
-  const int lr = tid >> 1, lc = (tid & 1) * (TC / 2);
-  const int gr = row0 + lr, gc = col0 + lr;
-  const float* qrow = qb + (long long)min(gr, q.g - 1) * q.d;
-  const float* krow = kb + (long long)min(gc, q.g - 1) * q.d;
-  float4 nq[2], nk[2];
+  // loader: load v of thread tid is channels 4 (tid % 8) .. +3 of row tid / 8 + 32 v.  No load sits behind a branch:
+  // what lies past the last row or channel reads the last one and is not used (d is a multiple of 4).
+  const int lr = tid >> 3, lc = 4 * (tid & 7);
+  f32x4 nq[NV], nk[NV];
   auto fetch = [&](int c0) {
+    const int c = min(c0 + lc, q.d - 4);
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int c = c0 + lc + 4 * v;
-      const bool in = c < q.d;                          // (a group of four is inside the row or outside it as a whole)
-      nq[v] = in && gr < q.g ? *(const float4*)(qrow + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-      nk[v] = in && gc < q.g ? *(const float4*)(krow + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int v = 0; v < NV; ++v) {
+      nq[v] = *(const f32x4*)(qb + (long long)min(row0 + lr + 32 * v, q.g - 1) * q.d + c);
+      nk[v] = *(const f32x4*)(kb + (long long)min(col0 + lr + 32 * v, q.g - 1) * q.d + c);
     }
   };
+  // eight channels (or, `half`, the first four of them) of the stage
+  auto eight = [&](int u, bool half) {
+    const float4 a = *(const float4*)&qs[(wr + r32) * LDR + hh * (TC / 2) + 4 * u];
+    const float4 b = *(const float4*)&ks[(wc + r32) * LDR + hh * (TC / 2) + 4 * u];
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
+    if (half) return;
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+  };
+  const bool works = row0 + wr < q.g && col0 + wc < q.g;   // else all of the wave's tile lies outside
+  auto stage = [&]() {
+    __syncthreads();                                     // everyone has left the previous stage
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      // (the loads are waited for here and not, for the sake of the shuffle below, where they are asked for)
+      asm volatile("" : "+v"(nq[v]), "+v"(nk[v]));
+      float* const qd = qs + (lr + 32 * v) * LDR + lc / 2;
+      float* const kd = ks + (lr + 32 * v) * LDR + lc / 2;
+      *(float2*)qd = make_float2(nq[v].x, nq[v].z);
+      *(float2*)(qd + TC / 2) = make_float2(nq[v].y, nq[v].w);
+      *(float2*)kd = make_float2(nk[v].x, nk[v].z);
+      *(float2*)(kd + TC / 2) = make_float2(nk[v].y, nk[v].w);
+    }
+    __syncthreads();
+  };
   fetch(0);
-  for (int c0 = 0; c0 < q.d; c0 += TC) {
+  int c0 = 0;
+  for (; c0 + TC <= q.d; c0 += TC) {
+    stage();
+    fetch(c0 + TC);                                      // (past the end: the last channels again, not used)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      qs[lc + 4 * v + 0][lr] = nq[v].x; qs[lc + 4 * v + 1][lr] = nq[v].y;
-      qs[lc + 4 * v + 2][lr] = nq[v].z; qs[lc + 4 * v + 3][lr] = nq[v].w;
-      ks[lc + 4 * v + 0][lr] = nk[v].x; ks[lc + 4 * v + 1][lr] = nk[v].y;
-      ks[lc + 4 * v + 2][lr] = nk[v].z; ks[lc + 4 * v + 3][lr] = nk[v].w;
-    }
-    __syncthreads();
-    if (c0 + TC < q.d) fetch(c0 + TC);
-    const int cend = min(TC, q.d - c0);
-    for (int c = 0; c < cend; ++c) {
-      float a[8], b[8];
-      // rows ty*4..+3 and 64+ty*4..+3; columns tx*4..+3 and 64+tx*4..+3
-      *(float4*)&a[0] = *(const float4*)&qs[c][ty * 4];
-      *(float4*)&a[4] = *(const float4*)&qs[c][64 + ty * 4];
-      *(float4*)&b[0] = *(const float4*)&ks[c][tx * 4];
-      *(float4*)&b[4] = *(const float4*)&ks[c][64 + tx * 4];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+    for (int u = 0; u < TC / 8; ++u) eight(u, false);
   }
+  if (c0 < q.d) {
+    stage();
+    for (int c = c0; c < q.d; c += 8) eight((c - c0) >> 3, c + 4 >= q.d);
+  }
+  // Accumulator register r of lane l: row 8(r/4) + 4(l/32) + r%4, column l%32 of the wave's 32x32 piece.  It goes out by
+  // way of LDS (each wave through a stretch of its own), 16 bytes per lane and 128 bytes of a row in one piece.
+  __syncthreads();                                       // the last stage has been read
+  if (!works) return;
   float* out = logits + bh * (long long)q.g * q.g;
-  // a thread's columns come in two runs of four: with g a multiple of 4 a run is inside the row or outside it as a
-  // whole, and 16-byte aligned, so it goes out as one store
-  const bool vec = (q.g & 3) == 0;
+  float* const mine = smem + wave * 32 * LDR;            // (4 * 32 rows of LDR floats: exactly smem)
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    int r = row0 + (i < 4 ? ty * 4 + i : 64 + ty * 4 + (i - 4));
-    if (r >= q.g) continue;
+  for (int r = 0; r < 16; ++r) mine[(8 * (r >> 2) + 4 * hh + (r & 3)) * LDR + r32] = acc[r] * scale;
+  __builtin_amdgcn_wave_barrier();
+  const int rw = row0 + wr, cw = col0 + wc;
+  if ((q.g & 3) == 0) {
+    // g a multiple of 4: four columns are inside the row or outside it as a whole, and 16-byte aligned
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int c = col0 + 64 * h + tx * 4;
-      float* dst = out + (long long)r * q.g + c;
-      if (vec) {
-        if (c < q.g)
-          *(float4*)dst = make_float4(acc[i][4 * h] * scale, acc[i][4 * h + 1] * scale, acc[i][4 * h + 2] * scale,
-                                      acc[i][4 * h + 3] * scale);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (c + j < q.g) dst[j] = acc[i][4 * h + j] * scale;
-      }
+    for (int e0 = 0; e0 < 32 * 8; e0 += 64) {
+      const int e = e0 + lane, r = e >> 3, c = 4 * (e & 7);
+      const float4 v = *(const float4*)&mine[r * LDR + c];
+      if (rw + r < q.g && cw + c < q.g) *(float4*)(out + (long long)(rw + r) * q.g + cw + c) = v;
+    }
+  } else {
+    for (int e = lane; e < 32 * 32; e += 64) {
+      const int r = e >> 5, c = e & 31;
+      const float v = mine[r * LDR + c];
+      if (rw + r < q.g && cw + c < q.g) out[(long long)(rw + r) * q.g + cw + c] = v;
     }
   }
 }
@@ -132,10 +162,10 @@ __global__ __launch_bounds__(256) void row_softmax_kernel(const float* logits, f
 }
 
 hipError_t launch_draft_logits(const Geo& q, const float* q_pool, const float* k_pool, float* logits, hipStream_t s) {
-  unsigned t = (unsigned)((q.g + TM - 1) / TM);
-  float scale = (float)(1.0 / sqrt((double)q.d));
-  dim3 grid(t, t, (unsigned)(q.B * q.H));
-  hipLaunchKernelGGL(draft_logits_kernel, grid, dim3(256), 0, s, q, q_pool, k_pool, logits, scale);
+  const float scale = (float)(1.0 / sqrt((double)q.d));
+  const long long bh = (long long)q.B * q.H;
+  const unsigned t = (unsigned)((q.g + TM - 1) / TM);
+  hipLaunchKernelGGL(draft_logits_kernel, dim3(t, t, (unsigned)bh), dim3(256), 0, s, q, q_pool, k_pool, logits, scale);
   return hipGetLastError();
 }
 
