@@ -150,8 +150,8 @@ int da_permute(const da_problem* p, const void* X, void* Y, int mode, void* stre
  * Supported: DA_BF16 with d = 128 and block = 64 or 128 (8x8 or 8x16 patches, say); DA_F32 with
  * d = 64 or 128 and block = 64; anything else returns DA_ERR_UNSUPPORTED.  bf16 uses bf16 MFMA with float32 accumulation and
  * softmax (and bf16 probabilities); f32 uses float32 arithmetic throughout.
- * The bf16 kernel leaves out, tile by tile (32 queries x 64 keys), keys whose probability is
- * negligible: a tile is dropped when each of its scores is so far below the best score its query
+ * The bf16 kernel leaves out, 64 queries x 32 keys at a time, keys whose probability is
+ * negligible: such a group is dropped when each of its scores is so far below the best score its query
  * has met so far that everything dropped from a row adds up to less than 2^-14 of the row's largest
  * term (the cut is log2(block * k) + 14 powers of two).  The result differs from the full sum by less
  * than a bf16 rounding of the output; how much work is saved depends on how peaked the attention is
@@ -172,9 +172,10 @@ int da_sparse_attn(const da_problem* p, const void* Qp, const void* Kp, const vo
  *   kernel reads each query row from, and writes each output row to, its original place, which is what da_forward
  *   does (Kp and Vt are still the reordered tensors; lse, if given, stays in slot order).  0: as da_sparse_attn.
  * tile_counts (DEVICE, two uint64, may be NULL; DA_BF16 only): the kernel ADDS to [0] the number of tiles
- *   (32 queries x 64 keys) its waves went through and to [1] the number of those whose exponentials and second
- *   product were carried out (the others fell to the drop rule described above).  The caller clears it.  Each tile
- *   is 16 matrix instructions for the first product and, if carried out, 16 for the second.
+ *   (32 queries x 64 keys) its waves went through and to [1] the number of those of which any 32 keys' exponentials
+ *   and second product were carried out (the others fell to the drop rule described above).  The caller clears it.
+ *   Each tile is 16 matrix instructions for the first product and, if carried out, up to 16 for the second (half of
+ *   either for a key block of at most 32 valid slots).
  */
 int da_sparse_attn_ex(const da_problem* p, const void* Q, const void* Kp, const void* Vt, const int32_t* idx, void* O,
                       float* lse, int original_order, uint64_t* tile_counts, void* stream);

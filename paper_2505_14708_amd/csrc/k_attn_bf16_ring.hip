@@ -9,20 +9,24 @@
 // such blocks and walks the UNION of their lists once: every K tile of the union is brought
 // into LDS once for all four, and the V tiles they fetch meet in L2.
 //
-// Workgroup = 8 wavefronts, two per SIMD.  A wavefront owns 32 queries (half a block): with
-// half the accumulators a wave fits in 256 registers, two waves share a SIMD, and while one is
-// in its softmax (vector ALU) the other keeps the matrix pipe busy; the same pairing hides LDS
-// latency and the waits of the ring protocol.  The two waves of a SIMD belong to different
-// query blocks so that they are rarely in the same phase.
+// Workgroup = 8 wavefronts, two per SIMD: while one is in its softmax (vector ALU) the other keeps the matrix pipe
+// busy, and the pairing hides LDS latency, the wait for V and the waits of the ring protocol.  A wavefront owns 64
+// queries (a block) and every other entry of that block's list; the two waves of a block put their sums together at the
+// end.  (With 32 queries and every entry per wave, a key tile is read from LDS and its V from L2 twice: V alone was 128
+// KB per tile step over a path of 64 bytes per cycle and CU.  Measured on 24 heads x 1980 blocks, 198 kept: 21.6 -> 19.8
+// ms where nothing is dropped, 12.0 -> 11.8 ms on peaked inputs.)  64 queries are 128 registers of output, 64 of Q and
+// 32 of scores, which leaves 32 for everything else at two waves per SIMD: tiles are taken 32 keys at a time, operands
+// arrive just ahead of their use, and what can be made anew in the loop is not kept (opaque_lane).  The two waves of a
+// SIMD belong to different query blocks so that they are rarely in the same phase.
 //
-// Per key tile a wave computes
-//     S^T = K Q^T      (64 keys x 32 queries: 2 MFMA tiles of 32x32, 8 k-steps over d)
-//     online softmax over the 64 keys
-//     O^T += V^T P^T   (128 channels x 32 queries: 4 MFMA tiles, 4 k-steps over the keys)
+// Per 32 keys a wave computes
+//     S^T = K Q^T      (32 keys x 64 queries: 2 MFMA tiles of 32x32, 8 k-steps over d)
+//     online softmax over the 32 keys
+//     O^T += V^T P^T   (128 channels x 64 queries: 8 MFMA tiles, 2 k-steps over the keys)
 // The transposed forms put the query on the lane axis (lane l holds query l%32), so row max and
 // row sum run down a lane's own registers plus one exchange between lanes l and l^32.  Lane l
 // feeds K row sigma(l%32) (sigma swaps bits 2 and 3): then the scores a lane holds in
-// accumulator registers 8t..8t+7 belong to keys 16t + 8*(l/32) + 0..7, exactly the eight
+// accumulator registers 8t..8t+7 belong to keys 16t + 8*(l/32) + 0..7 of the 32, exactly the eight
 // contraction elements the P^T operand of the second product needs, so P goes from accumulator
 // to operand without leaving the lane.  V arrives from the reorder step transposed and cut into
 // these operands (one product step's 64 operands are one contiguous KB), so K rows are read from
@@ -33,8 +37,8 @@
 // p ^ swizzle(r), which makes the operand reads conflict-free.  There are no workgroup barriers
 // in the tile loop:
 //   ready[s]   union entry whose K tile slot s holds (set once the tile has landed)
-//   left[s]    how many waves have yet to read the tile in slot s (set when the tile is asked for: the
-//              live waves of the query blocks that hold the entry; every reader takes one off when it
+//   left[s]    how many waves have yet to read the tile in slot s (set when the tile is asked for: one
+//              wave of each query block that holds the entry; every reader takes one off when it
 //              is through): at zero the slot may be overwritten
 //   next_load  entries are requested strictly in order, entry L once its slot L % 8 is free, by the waves
 //              that are waiting for a tile: the one that notices first claims it with a compare-and-
@@ -71,6 +75,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
+typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+typedef __attribute__((address_space(3))) int lds_int;
 
 constexpr int D = 128;
 constexpr int BS = 64;
@@ -88,6 +94,7 @@ constexpr float kC2 = 0.08838834764831845f * 1.4426950408889634f;   // log2(e)/s
 constexpr float kLazy = 8.0f;                     // move the running max only past this many powers of two
 constexpr float kDropLog2 = 14.0f;                // all keys dropped from a row together weigh less than 2^-14 of its largest term
 constexpr int kSpinLimit = 1 << 20;
+constexpr int kPeekTiles = 16;                      // lists of at least so many tiles: both waves of a group look at the first one
 
 // Waves whose bounded wait for a tile ran out since the library was loaded (their rows were written as NaN).
 // No valid input makes that happen; the host can ask (da_wait_failures).
@@ -127,6 +134,20 @@ __device__ __forceinline__ void dma_tile(const unsigned char* src, unsigned lds_
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// the lane number, in a way that the compiler neither moves nor keeps
+__device__ __forceinline__ int opaque_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
+// minus infinity, not kept in a register
+__device__ __forceinline__ float opaque_minus_inf() {
+  float x;
+  asm volatile("v_mov_b32 %0, 0xff800000" : "=v"(x));
+  return x;
+}
+
 __device__ inline int sigma(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -152,33 +173,29 @@ __device__ __forceinline__ float sum_across_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// exp / sum / pack of 16 scores (one accumulator tile) into two P operands
-__device__ __forceinline__ void exp_pack(const f32x16& s, float mc, float& lsum, bf16x8& p_lo, bf16x8& p_hi) {
+// exp / sum / pack of 8 scores (registers o .. o+7 of an accumulator tile) into one P operand
+__device__ __forceinline__ bf16x8 exp_pack(const f32x16& s, int o, float mc, float& lsum) {
   const bf16x2 kOnes = {(__bf16)1.0f, (__bf16)1.0f};
+  bf16x8 p;
 #pragma unroll
-  for (int i = 0; i < 16; i += 2) {
-    float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], kC2, -mc));
-    float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i + 1], kC2, -mc));
+  for (int i = 0; i < 8; i += 2) {
+    float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[o + i], kC2, -mc));
+    float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[o + i + 1], kC2, -mc));
     f32x2 pp = {p0, p1};
     bf16x2 pb = __builtin_convertvector(pp, bf16x2);
     lsum = __builtin_amdgcn_fdot2_f32_bf16(pb, kOnes, lsum, false);   // the sum of what the second product sees
-    if (i < 8) {
-      p_lo[i] = pb[0];
-      p_lo[i + 1] = pb[1];
-    } else {
-      p_hi[i - 8] = pb[0];
-      p_hi[i - 7] = pb[1];
-    }
+    p[i] = pb[0];
+    p[i + 1] = pb[1];
   }
+  return p;
 }
 
-// pad keys out of the softmax: accumulator register i of half mt is key 32mt + 16(i>>3) + 8hh + (i&7)
-__device__ __forceinline__ void mask_pad_half(f32x16& s, int mt, int nv, int hh) {
+// pad keys out of the softmax: accumulator register i is key 16(i>>3) + 8hh + (i&7) of the half tile, nv of its keys are valid
+__device__ __forceinline__ void mask_pad_keys(f32x16& s, int nv) {
+  const int lim = nv - ((opaque_lane() >> 5) << 3);
+  const float ninf = opaque_minus_inf();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    int key = 32 * mt + 16 * (i >> 3) + 8 * hh + (i & 7);
-    if (key >= nv) s[i] = -INFINITY;
-  }
+  for (int i = 0; i < 16; ++i) s[i] = 16 * (i >> 3) + (i & 7) < lim ? s[i] : ninf;
 }
 
 // n / d for 0 <= n < 2^24, d >= 1, by way of the float reciprocal (exact: the estimate is off by one at most)
@@ -199,82 +216,119 @@ __device__ __forceinline__ int valid_slots(const Geo& q, int per_frame, int j) {
 
 struct Soft {
   float m;     // reference max (raw score units); -inf before the first tile
-  float top;   // largest score seen so far (the reference trails it by at most kLazy powers of two)
+  float top;   // largest score seen so far (the reference trails it by at most kLazy powers of two); +inf for a pad query
   float l;     // this lane's partial sum of probabilities
 };
 
-// One 64-key tile for one wave (32 queries).  kaddr[t] is this lane's LDS address of the K
-// operand of k-step t (swizzle already applied; the second 32 keys sit 8 KB further).  vt is
-// this lane's 16 bytes of the first operand group of the tile's V^T in global memory (operand
-// order: the 64 lanes' operands of (k-step t, channel group dt) are the contiguous KB number
-// 4t + dt of the tile, so every load of a wave is one contiguous KB).
-__device__ __forceinline__ bool compute_tile(const unsigned char* const (&kaddr)[8], const unsigned char* vt, int hh,
-                                             int nv, bool pad_query, float skip, const bf16x8 (&qf)[8],
-                                             f32x16 (&o)[4], Soft& st) {
+__device__ __forceinline__ bf16x8 lds_operand(unsigned addr) { return *(const lds_bf16x8*)(uintptr_t)addr; }
+
+// 16 bytes per lane from a uniform base
+__device__ __forceinline__ bf16x8 load_operand(__amdgpu_buffer_rsrc_t base, unsigned lane_offset, unsigned offset) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(base, lane_offset, offset, 0);
+  return __builtin_bit_cast(bf16x8, x);
+}
+
+// The scores of 32 keys against the wave's queries, S^T = K Q^T.  kaddr: this lane's LDS address of the operand of k-step
+// 0; the swizzle puts that of step t at kaddr ^ 32t.
+template <int NQ>
+__device__ __forceinline__ void half_scores(unsigned kaddr, int nv, const bf16x8 (&qf)[2][8], f32x16 (&s)[NQ]) {
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  f32x16 s0, s1;
-  bf16x8 va[4][4];
-  {
-    // S^T = K Q^T; all sixteen K operands are asked for before the first product, so the LDS
-    // latency is paid once per tile
-    bf16x8 ka[8], kb[8];
+  constexpr int AHEAD = 3;                            // operands on their way from LDS
+  bf16x8 k[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      ka[t] = *(const bf16x8*)(kaddr[t]);
-      kb[t] = *(const bf16x8*)(kaddr[t] + 32 * 256);
-    }
+  for (int t = 0; t < AHEAD; ++t) k[t] = lds_operand(kaddr ^ (32 * t));
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) s[h] = mfma(k[t], qf[h][t], t == 0 ? zero : s[h]);
+    if (t + AHEAD < 8) k[t + AHEAD] = lds_operand(kaddr ^ (32 * (t + AHEAD)));
     __builtin_amdgcn_sched_barrier(0);
+  }
+  if (nv < 32) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      s0 = mfma(ka[t], qf[t], t == 0 ? zero : s0);
-      s1 = mfma(kb[t], qf[t], t == 0 ? zero : s1);
-    }
+    for (int h = 0; h < NQ; ++h) mask_pad_keys(s[h], nv);
   }
-  if (nv < BS) {
-    mask_pad_half(s0, 0, nv, hh);
-    mask_pad_half(s1, 1, nv, hh);
+}
+
+// 32 keys (half a tile) for one wave: 64 queries, or the first 32 of them (NQ = 1: the others are pad slots).  v: the
+// half tile's V^T in global memory (operand order: the 64 lanes' operands of (k-step t, channel group dt) are the
+// contiguous KB number 4t + dt, so every load of a wave is one contiguous KB).
+template <int NQ>
+__device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v, int nv, float skip,
+                                          const bf16x8 (&qf)[2][8], f32x16 (&o)[2][4], Soft (&st)[2], int& kept) {
+  f32x16 s[NQ];
+  half_scores<NQ>(kaddr, nv, qf, s);
+  // online softmax over the 32 keys
+  float mx[NQ];
+  bool negligible = true;
+#pragma unroll
+  for (int h = 0; h < NQ; ++h) {
+    mx[h] = max_across_halves(max16(s[h], -INFINITY));   // finite: the half tile's first slot is valid
+    negligible = negligible && (mx[h] - st[h].top) * kC2 < -skip;
   }
-  // online softmax over the 64 keys
-  const float mx = max_across_halves(max16(s1, max16(s0, -INFINITY)));   // finite: slot 0 of a block is valid
   // A key whose score is more than `skip` powers of two below the query's best score so far
   // weighs less than 2^-skip of that query's largest term, in the normaliser and in the output.
   // skip = log2(keys in the row) + kDropLog2, so whatever is dropped from a row adds up to less
   // than 2^-kDropLog2 of that term: below the resolution of a bf16 result at any sequence length.
-  // When every key of the tile is that small for all 32 queries, the exponentials and the second
-  // product are skipped.  (Never the first time: top is -inf.)  Pad query slots have no say: their
-  // rows are zero, every score is 0, and nobody reads their output.
-  if (__all(pad_query || (mx - st.top) * kC2 < -skip)) return false;
-  // V^T operands: on their way while the exponentials are computed.  (Asking for them before the first product
-  // where tiles keep mattering was tried: a tile dropped after all then leaves loads in flight, the compiler has
-  // to wait for everything outstanding at the top of every tile, the ring's transfers included, and the common
-  // case lost more than the other gained.)
+  // When all 32 keys are that small for every query, the exponentials and the second
+  // product are skipped.  (Never the first time: top is -inf.)  Pad query slots have no say (their top is
+  // +inf): their rows are zero, every score is 0, and nobody reads their output.
+  if (__all(negligible)) return;
+  asm volatile("s_mov_b32 %0, 1" : "=s"(kept));   // (a scalar, whatever the compiler thinks)
+  // V^T operands: the first three on their way while the exponentials are computed, one more whenever registers fall
+  // free.  (Operand 4t + dt belongs to k-step t and channel group dt.)
+  const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc((void*)v, 0, -1, 0x00020000);
+  const unsigned lane16 = (unsigned)(opaque_lane() & 63) * 16;
+  bf16x8 va[8];
+  auto fetch = [&](int i) { va[i] = load_operand(vb, lane16 + (i & 3) * 1024, (i >> 2) * 4096); };
+  fetch(0);
+  fetch(1);
+  fetch(2);
+  __builtin_amdgcn_sched_barrier(0);
+  bool moves = false;
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) va[t][dt] = *(const bf16x8*)(vt + (t * 4 + dt) * 1024);
-  st.top = fmaxf(st.top, mx);
-  if (__any((mx - st.m) * kC2 > kLazy)) {
-    const float m_new = fmaxf(st.m, mx);
-    const float alpha = st.m == m_new ? 1.0f : __builtin_amdgcn_exp2f((st.m - m_new) * kC2);   // 0 the first time
-    st.m = m_new;
-    st.l *= alpha;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
+  for (int h = 0; h < NQ; ++h) {
+    st[h].top = fmaxf(st[h].top, mx[h]);
+    moves = moves || (mx[h] - st[h].m) * kC2 > kLazy;
   }
-  bf16x8 pf[4];
-  float ls = 0.f;
-  const float mc = st.m * kC2;
-  exp_pack(s0, mc, ls, pf[0], pf[1]);
-  exp_pack(s1, mc, ls, pf[2], pf[3]);
-  st.l += ls;
+  if (__any(moves)) {
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) {
+      const float m_new = fmaxf(st[h].m, mx[h]);
+      const float alpha = st[h].m == m_new ? 1.0f : __builtin_amdgcn_exp2f((st[h].m - m_new) * kC2);   // 0 the first time
+      st[h].m = m_new;
+      st[h].l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[h][dt][i] *= alpha;
+    }
+  }
+  bf16x8 p[NQ];
+#pragma unroll
+  for (int h = 0; h < NQ; ++h) {
+    p[h] = exp_pack(s[h], 0, st[h].m * kC2, st[h].l);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(3 + h);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   // O^T += V^T P^T
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int dt = 0; dt < 4; ++dt) {
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) o[dt] = mfma(va[t][dt], pf[t], o[dt]);
-  return true;
+    for (int h = 0; h < NQ; ++h) o[h][dt] = mfma(va[dt], p[h], o[h][dt]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (3 + NQ + dt < 8) fetch(3 + NQ + dt);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int h = 0; h < NQ; ++h) p[h] = exp_pack(s[h], 8, st[h].m * kC2, st[h].l);
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) o[h][dt] = mfma(va[4 + dt], p[h], o[h][dt]);
 }
 
 // How the frames that do not fill a group of `fg` are spread over workgroups.
@@ -309,7 +363,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
                                                                unsigned long long* __restrict__ tile_counts) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_TOTAL];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  int lane = threadIdx.x & 63;
   // Heads one after the other (the K/V of the heads in flight then fit the last-level cache);
   // inside a head a workgroup is one patch position and FG consecutive frames, and the frame
   // groups of one position follow each other on one XCD (workgroups are dealt round-robin to the
@@ -328,10 +382,12 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const long long bh = blockIdx.x / wg_per_head;
   // the tail workgroups (longer walks) come first within a head, the regular ones after them
   const int n = blockIdx.x - (int)(bh * wg_per_head) - plan.tail_wgs;   // < 0: tail workgroup n + tail_wgs
-  // waves w and w+4 share a SIMD: give them different query blocks.  part = which 32 queries of the block.
-  const int half = wave >> 2;
-  const int qblk = SUB == 1 ? (wave + 2 * half) & 3 : half;
-  const int part = SUB == 1 ? half : wave & 3;
+  // Four groups of 64 queries (a block, or half a block of 128), two waves each; waves w and w+4 share a SIMD: give them
+  // different groups.  The two waves of a group take its list entries in turn (part = which of the two).
+  const int part = wave >> 2;
+  const int group = (wave + 2 * part) & 3;
+  const int qblk = SUB == 1 ? group : group >> 1;
+  const int qsub = SUB == 1 ? 0 : group & 1;          // which 64 queries of the block
   // query block w of this workgroup: (position, frame), or none
   // (divisions of small non-negative numbers: by way of the float reciprocal)
   const int n_over_fgs = n >= 0 ? small_div(n >> 3, max(fgs, 1)) : 0;
@@ -351,9 +407,9 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   if (n >= 0 && slot_pos(0) >= per_frame) return;     // a regular workgroup past the last position: all of it leaves
   const int my_block = slot_block(qblk);
   const bool has_block = my_block >= 0;
-  // a wave without a query block, or whose 32 slots of it are all pad slots, only helps with the ring
-  const bool live = has_block && 32 * part < block_valid(q, has_block ? my_block : 0);
-  const int pos = has_block ? slot_pos(qblk) : 0;
+  // a wave without a query block, or whose 64 slots of it are all pad slots, only helps with the ring
+  const int q_valid = (has_block ? block_valid(q, my_block) : 0) - BS * qsub;   // valid queries of the group
+  const bool live = q_valid > 0;
   const long long qb = bh * q.g + (has_block ? my_block : 0);
   const int g = q.g;
   // The list of my query block: k columns at idx + (row) * k, or, with row_ptr (lists of any length, one head's
@@ -385,17 +441,18 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     const int u = s / qpos.vw, v = s - u * qpos.vw;
     return row_offset(where, q.H, bh, q_first + (long long)u * q_pitch + v) * 2;
   };
-  bf16x8 qf[8];
-  {
+  bf16x8 qf[2][8];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
     const int r = lane & 31, hh = lane >> 5;
-    const long long row = row_bytes(32 * part + r, q.in);
+    const long long row = row_bytes(BS * qsub + 32 * h + r, q.in);
     const unsigned char* qrow = Qp + max(row, 0LL);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      qf[t] = *(const bf16x8*)(qrow + (16 * t + 8 * hh) * 2);
+      qf[h][t] = *(const bf16x8*)(qrow + (16 * t + 8 * hh) * 2);
       if (row < 0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) qf[t][i] = (__bf16)0.f;
+        for (int i = 0; i < 8; ++i) qf[h][t][i] = (__bf16)0.f;
       }
     }
   }
@@ -404,7 +461,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const int bw = (g + 31) >> 5;
   unsigned* ulist = bitmap + 4 * bw;                  // union entries: key sub-block | (valid slots - 1) << 22 | membership << 28
   const int union_max = SUB * (LISTS ? g : min(g, FG * q.k));
-  int* ctrl = (int*)(smem + LDS_TOTAL - 128);         // [32]: ready[8], left[8], next_load, count, n_own, ..., live waves
+  int* ctrl = (int*)(smem + LDS_TOTAL - 128);         // [32]: ready[8], left[8], next_load, count[2], first[2], wcount[8], live groups, waves that gave up
   int* ready = ctrl;                                  // [RING]
   int* left = ctrl + 8;                               // [RING]
   int* next_load = ctrl + 16;
@@ -412,14 +469,14 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 
   // ---- union of the workgroup's lists (the first 256 entries of a list are asked for before the
   // bitmaps are cleared, so that the two latencies overlap)
-  const bool lister = live && part == 0;              // the wave that brings in the list of its query block
+  const bool lister = live && part == 0 && qsub == 0; // the wave that brings in the list of its query block
   int pre[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) pre[i] = lister && lane + 64 * i < k ? list[lane + 64 * i] : -1;
   for (int i = threadIdx.x; i < 4 * bw; i += 512) bitmap[i] = 0u;
   if (threadIdx.x < 32) ctrl[threadIdx.x] = threadIdx.x < RING ? -1 : 0;
   __syncthreads();
-  if (live && lane == 0) atomicOr(&ctrl[28], 1 << wave);   // which waves take tiles at all
+  if (live && part == 0 && lane == 0) atomicOr(&ctrl[28], 1 << group);   // which groups take tiles at all
   if (lister) {
     // (an entry that is no block number is left out: it must not reach the bitmap, let alone an address)
 #pragma unroll
@@ -589,31 +646,49 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     __syncthreads();
   }
 
+  // The first entry of a group's walk is the best start for its running maxima (its own block, as a rule).  One of the
+  // two waves takes it; the other looks at its scores before it starts, so that neither has to carry out tiles that the
+  // drop rule would spare it.  Not worth a product where a wave has few tiles.
+  const unsigned my_bit = live ? (1u << (28 + qblk)) : 0u;
+  int* first = wcount;                                // [4] that entry of each group, -1: nobody looks
+  {
+    int f = -1;
+    if (live && k * SUB >= kPeekTiles)
+      for (int base = 0; base < nU; base += 64) {
+        const unsigned long long m = __ballot(base + lane < nU && (ulist[min(base + lane, nU - 1)] & my_bit) != 0u);
+        if (m) {
+          f = base + (int)__builtin_ctzll(m);
+          break;
+        }
+      }
+    if (part == 0 && lane == 0) first[group] = f;
+  }
+  __syncthreads();
+
   // ---- per-lane constants
-  const int r = lane & 31, hh = lane >> 5;
-  const int krow = sigma(r);
-  const int ke = (hh ^ (krow & 15)) << 4;
-  int kofs[8];                                        // K operand offsets inside a slot, swizzle applied
-#pragma unroll
-  for (int t = 0; t < 8; ++t) kofs[t] = krow * 256 + ((32 * t) ^ ke);
   const unsigned ring_lds = (unsigned)(uintptr_t)(lds_bytes)smem;
-  unsigned koff[4];
-  tile_lane_offsets<256>(lane, koff);
+  const int krow = sigma(lane & 31);
+  const unsigned kbase = ring_lds + krow * 256 + (((lane >> 5) ^ (krow & 15)) << 4);   // K operand of k-step 0 in slot 0, swizzle applied
   const unsigned char* Kbh = Kp + bh * q.n_pad * (D * 2);
-  const unsigned char* Vlane = Vt + bh * q.n_pad * (D * 2) + lane * 16;
+  const unsigned char* Vbh = Vt + bh * q.n_pad * (D * 2);
+  const int live_groups = __builtin_amdgcn_readfirstlane(ctrl[28]);
+  int first_of[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) first_of[w] = __builtin_amdgcn_readfirstlane(first[w]);
   // one wave brings the K tile of union entry u into ring slot u % RING
-  const int live_waves = __builtin_amdgcn_readfirstlane(ctrl[28]);
   auto issue_tile = [&](int u) {
     const unsigned e = (unsigned)__builtin_amdgcn_readfirstlane((int)ulist[u]);
-    // how many waves will read the tile: the live waves of the query blocks that hold the entry
+    // how many waves will read the tile: one of each live group that holds the entry, and the second one where it looks
     int readers = 0;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      const int qb_w = SUB == 1 ? (w + 2 * (w >> 2)) & 3 : w >> 2;
-      readers += (live_waves >> w) & (int)(e >> (28 + qb_w)) & 1;
+    for (int w = 0; w < 4; ++w) {
+      const int holds = (live_groups >> w) & (int)(e >> (28 + (SUB == 1 ? w : w >> 1))) & 1;
+      readers += holds + (u == first_of[w] ? holds : 0);
     }
     if (lane == 0) __atomic_store_n(&left[u & (RING - 1)], readers, __ATOMIC_RELAXED);   // (before the transfer, hence before the slot is published)
     const long long j = (long long)(e & 0x3fffffu);
+    unsigned koff[4];
+    tile_lane_offsets<256>(opaque_lane(), koff);      // (made anew each time: four registers the tile loop can use)
     dma_tile(Kbh + j * K_TILE, ring_lds + (unsigned)(u & (RING - 1)) * SLOT, koff);
   };
   int pending = -1;
@@ -627,25 +702,35 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     }
   };
 
-  f32x16 o[4];
+  f32x16 o[2][4];
+  Soft st[2];
+  float nought;                                       // (a zero of its own: the compiler would keep a row of them for later uses)
+  asm volatile("v_mov_b32 %0, 0" : "=v"(nought));
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
-  Soft st;
-  st.m = -INFINITY;
-  st.top = -INFINITY;
-  st.l = 0.f;
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[h][dt][i] = nought;
+    st[h].m = -INFINITY;
+    st[h].top = 32 * h + (lane & 31) < q_valid ? -INFINITY : INFINITY;
+    st[h].l = nought;
+  }
   // Make the compiler wait for the Q fragments here, by touching them: its own counter
   // bookkeeping then knows they are in.  Otherwise it would wait for them at their first use
   // inside the tile loop, with a vmcnt that also drains the tile loads in flight.
 #pragma unroll
-  for (int t = 0; t < 8; ++t) asm volatile("" : "+v"(qf[t]));
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) asm volatile("" : "+v"(qf[h][t]));
 
-  const unsigned my_bit = live ? (1u << (28 + qblk)) : 0u;
-  const bool pad_query = 32 * part + r >= valid_slots(q, per_frame, pos);
   // a look at the whole control block: lane i holds ctrl[i]
-  auto look = [&]() -> int { return __atomic_load_n(ctrl + (lane & 31), __ATOMIC_RELAXED); };
+  const unsigned ctrl_lds = ring_lds + LDS_TOTAL - 128;
+  auto look = [&]() -> int {
+    unsigned at = (unsigned)(opaque_lane() & 31) * 4;
+    asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(ctrl_lds));   // (as one constant it would be kept in a register)
+    return __atomic_load_n((const lds_int*)(uintptr_t)at, __ATOMIC_RELAXED);
+  };
   // request the next tile if the ring has room, judging by a look c (which may be old: then the
   // compare-and-swap fails or the room is underestimated, both harmless)
   auto service = [&](int c) {
@@ -664,105 +749,165 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     pending = L;
   };
   bool gave_up = false;
-  int tiles_seen = 0, tiles_kept = 0;                 // (scalar registers; reported when the caller asks for the counts)
   int snap = look();
-  // The walk, 64 entries at a time: lane i holds entry base + i, a ballot tells which of them
-  // are mine.  Entries that are not mine cost nothing.
+  // wait until entry u is in its slot (false: the bounded wait ran out)
+  auto arrived = [&](int u) -> bool {
+    const int slot_i = u & (RING - 1);
+    publish();                                        // my last request has had a whole tile's time to land
+    if (__builtin_amdgcn_readlane(snap, slot_i) == u) return true;
+    int spins = 0;
+    for (;;) {
+      snap = look();
+      service(snap);
+      if (__builtin_amdgcn_readlane(snap, slot_i) == u) return true;
+      if (__builtin_amdgcn_readfirstlane(pending) >= 0) {
+        publish();                                    // idle anyway: wait for my own request and hand it over
+      } else {
+        __builtin_amdgcn_s_sleep(1);
+        if (++spins > kSpinLimit) return false;
+      }
+    }
+  };
+  // my reads of the slot of entry u are complete: one reader less
+  auto leave = [&](int u) {
+    wait_lds();
+    if (lane == 0) atomicSub(&left[u & (RING - 1)], 1);
+  };
+  const bool two = q_valid > 32;                      // else the second 32 queries are all pad slots
+  int tiles_seen = 0, tiles_kept = 0;                 // (scalar registers; reported when the caller asks for the counts)
+  if (live && part == 1 && first_of[group] >= 0) {
+    const int u = first_of[group];
+    gave_up = !arrived(u);
+    if (!gave_up) {
+      const int nv = (int)((__builtin_amdgcn_readfirstlane((int)ulist[u]) >> 22) & 63) + 1;
+#pragma unroll 1
+      for (int half = 0; half < 2 && 32 * half < nv; ++half) {
+        f32x16 s[2];
+        half_scores<2>(kbase + (unsigned)(u & (RING - 1)) * SLOT + half * (SLOT / 2), nv - 32 * half, qf, s);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) st[h].top = fmaxf(st[h].top, max_across_halves(max16(s[h], -INFINITY)));
+      }
+      leave(u);
+    }
+  }
+  // The walk, 64 entries at a time: lane i holds entry base + i, a ballot tells which of them are my group's, a second
+  // one which of those are mine (every other one).  Entries that are not mine cost nothing.
+  int before = 0;                                     // entries of my group in the chunks before
   for (int base = 0; base < nU && !gave_up; base += 64) {
-    const unsigned e_lane = base + lane < nU ? ulist[base + lane] : 0u;
-    unsigned long long mine = __ballot((e_lane & my_bit) != 0u);
+    const int at = base + opaque_lane();
+    const unsigned e_lane = ulist[min(at, nU - 1)];
+    const bool is_ours = at < nU && (e_lane & my_bit) != 0u;
+    const unsigned long long ours = __ballot(is_ours);
+    unsigned long long mine = __ballot(is_ours && ((before + lanes_before(ours) + part) & 1) == 0);
+    before += __popcll(ours);
     while (mine) {
       const int i = (int)__builtin_ctzll(mine);
       mine &= mine - 1;
       const int u = base + i;
-      const int slot_i = u & (RING - 1);
-      publish();                                      // my last request has had a whole tile's time to land
-      if (__builtin_amdgcn_readlane(snap, slot_i) != u) {
-        int spins = 0;
-        for (;;) {
-          snap = look();
-          service(snap);
-          if (__builtin_amdgcn_readlane(snap, slot_i) == u) break;
-          if (__builtin_amdgcn_readfirstlane(pending) >= 0) {
-            publish();                                // idle anyway: wait for my own request and hand it over
-          } else {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins > kSpinLimit) {
-              gave_up = true;
-              break;
-            }
-          }
-        }
-        if (gave_up) break;
+      if (!arrived(u)) {
+        gave_up = true;
+        break;
       }
-      const int fresh = look();                       // asked for now, used after the tile: its latency hides behind the tile
+      snap = look();                                  // asked for now, used after the tile: its latency hides behind the tile
       const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)e_lane, i);
-      {
-        const int nv = (int)((e >> 22) & 63u) + 1;
-        const unsigned char* slot = smem + slot_i * SLOT;
-        const unsigned char* kaddr[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) kaddr[t] = slot + kofs[t];
-        const bool kept = compute_tile(kaddr, Vlane + (long long)(e & 0x3fffffu) * V_TILE, hh, nv, pad_query, skip, qf, o, st);
-        tiles_seen += 1;
-        tiles_kept += kept ? 1 : 0;
+      const int nv = (int)((e >> 22) & 63u) + 1;
+      const unsigned kaddr = kbase + (unsigned)(u & (RING - 1)) * SLOT;
+      const unsigned char* v = Vbh + (long long)(e & 0x3fffffu) * V_TILE;
+      int kept = 0;
+#pragma unroll 1
+      for (int half = 0; half < 2 && 32 * half < nv; ++half) {
+        half_tile<2>(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, qf, o, st, kept);
       }
-      // my reads of the slot are complete: one reader less
-      wait_lds();
-      if (lane == 0) atomicSub(&left[slot_i], 1);
+      tiles_seen += 1;
+      tiles_kept += kept;
+      leave(u);
       // (Only waves that are waiting for a tile ask for tiles: having every wave look for room after each of
       // its tiles cost the busy ones more than the earlier requests saved.)
-      snap = fresh;
     }
   }
   publish();
   if (tile_counts != nullptr && lane == 0 && tiles_seen) {
-    atomicAdd(&tile_counts[0], (unsigned long long)tiles_seen);
-    atomicAdd(&tile_counts[1], (unsigned long long)tiles_kept);
+    atomicAdd(&tile_counts[0], (unsigned long long)(two ? 2 * tiles_seen : tiles_seen));
+    atomicAdd(&tile_counts[1], (unsigned long long)(two ? 2 * tiles_kept : tiles_kept));
   }
-  if (gave_up && lane == 0) atomicAdd(&g_wait_failures, 1ull);
-  __syncthreads();                                    // everyone is done with the ring: reuse it to stage the output
-  if (!live) {
+  if (gave_up && lane == 0) {
+    atomicAdd(&g_wait_failures, 1ull);
+    atomicOr(&ctrl[29], 1 << group);
+  }
+  __syncthreads();                                    // everyone is done with the ring: reuse it to put the halves together
+
+  // ---- the two waves of a group: each hands over what it has of 32 queries and puts the other 32 together
+  lane = opaque_lane();
+  const int r = lane & 31, hh = lane >> 5;
+  const int partner = part ? group : 4 + ((group + 2) & 3);
+  unsigned char* const given = smem + wave * (RING_BYTES / WAVES);      // 16 KB to hand over in
+  unsigned char* const taken = smem + partner * (RING_BYTES / WAVES);
+  float2* const ml = (float2*)(smem + RING_BYTES) + lane;               // [WAVES][64] reference and normaliser (the bitmaps are done with)
+  auto give = [&](const f32x16 (&x)[4], const Soft& sx) {
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        *(float4*)(given + ((dt * 4 + a) * 64 + lane) * 16) = make_float4(x[dt][4 * a], x[dt][4 * a + 1], x[dt][4 * a + 2], x[dt][4 * a + 3]);
+    ml[wave * 64] = make_float2(sx.m, sum_across_halves(sx.l));
+  };
+  if (part) give(o[0], st[0]);
+  else give(o[1], st[1]);
+  __syncthreads();
+  const bool failed = (ctrl[29] >> group) & 1;        // a wait ran out: say so with NaN rather than with wrong numbers
+  if (32 * part >= q_valid) {
     // 32 pad slots and nothing else: their rows of the reordered output are zeroed (in the original
     // order they do not exist)
     if (has_block && !direct) {
+      const long long row0 = qb * BLOCK + BS * qsub + 32 * part;
 #pragma unroll
       for (int it = 0; it < 8; ++it) {
         const int row = it * 4 + (lane >> 4), ch = lane & 15;
-        *(uint4*)(Op + (qb * BLOCK + 32 * part + row) * (D * 2) + ch * 16) = make_uint4(0u, 0u, 0u, 0u);
+        *(uint4*)(Op + (row0 + row) * (D * 2) + ch * 16) = make_uint4(0u, 0u, 0u, 0u);
       }
-      if (lse && lane < 32) lse[qb * BLOCK + 32 * part + lane] = 0.f;
+      if (lse && lane < 32) lse[row0 + lane] = 0.f;
     }
     return;
   }
 
-  // ---- epilogue: normalise, convert, stage through LDS, write rows of 256 B
-  unsigned char* stage = smem + wave * (RING_BYTES / WAVES);
-  {
-    const float lt = sum_across_halves(st.l);
-    const float inv = lt > 0.f ? 1.0f / lt : 0.f;     // 0 only in pad query slots whose wave skipped every tile
-    if (lse && hh == 0) lse[qb * BLOCK + 32 * part + r] = st.m * kScale + __logf(lt);
+  // ---- normalise, convert, stage through LDS, write rows of 256 B
+  auto finish = [&](const f32x16 (&x)[4], const Soft& sx) {
+    const float2 other = ml[partner * 64];
+    const float l_mine = sum_across_halves(sx.l), m_all = fmaxf(sx.m, other.x);
+    const float a_mine = l_mine > 0.f ? __builtin_amdgcn_exp2f((sx.m - m_all) * kC2) : 0.f;
+    const float a_other = other.y > 0.f ? __builtin_amdgcn_exp2f((other.x - m_all) * kC2) : 0.f;
+    const float lt = l_mine * a_mine + other.y * a_other;
+    const float inv = lt > 0.f ? 1.0f / lt : 0.f;     // 0 only in pad query slots whose waves skipped every tile, and for an empty list
+    if (lse && hh == 0) lse[qb * BLOCK + BS * qsub + 32 * part + r] = m_all * kScale + __logf(lt);
+    const float f_mine = a_mine * inv, f_other = a_other * inv;
+    uint2 w2[4][4];
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         // registers 4a..4a+3 are d = 32dt + 8a + 4hh + 0..3 of query r
-        f32x2 v0 = {o[dt][4 * a] * inv, o[dt][4 * a + 1] * inv};
-        f32x2 v1 = {o[dt][4 * a + 2] * inv, o[dt][4 * a + 3] * inv};
+        const float4 y = *(const float4*)(taken + ((dt * 4 + a) * 64 + lane) * 16);
+        f32x2 v0 = {x[dt][4 * a] * f_mine + y.x * f_other, x[dt][4 * a + 1] * f_mine + y.y * f_other};
+        f32x2 v1 = {x[dt][4 * a + 2] * f_mine + y.z * f_other, x[dt][4 * a + 3] * f_mine + y.w * f_other};
         bf16x2 b0 = __builtin_convertvector(v0, bf16x2);
         bf16x2 b1 = __builtin_convertvector(v1, bf16x2);
-        uint2 w2 = make_uint2(*(unsigned*)&b0, *(unsigned*)&b1);
-        if (gave_up) w2 = make_uint2(0x7fc07fc0u, 0x7fc07fc0u);   // a wait ran out: say so with NaN rather than with wrong numbers
-        *(uint2*)(stage + r * O_STRIDE + (32 * dt + 8 * a + 4 * hh) * 2) = w2;
+        w2[dt][a] = failed ? make_uint2(0x7fc07fc0u, 0x7fc07fc0u) : make_uint2(*(unsigned*)&b0, *(unsigned*)&b1);
       }
-  }
+    // (all of the partner's share has been read: its place serves to turn the rows)
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) *(uint2*)(taken + r * O_STRIDE + (32 * dt + 8 * a + 4 * hh) * 2) = w2[dt][a];
+  };
+  if (part) finish(o[1], st[1]);
+  else finish(o[0], st[0]);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int it = 0; it < 8; ++it) {
     const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    const long long orow = row_bytes(32 * part + row, q.out);
-    if (orow >= 0) *(uint4*)(Op + orow + ch * 16) = *(const uint4*)(stage + row * O_STRIDE + ch * 16);
+    const long long orow = row_bytes(BS * qsub + 32 * part + row, q.out);
+    if (orow >= 0) *(uint4*)(Op + orow + ch * 16) = *(const uint4*)(taken + row * O_STRIDE + ch * 16);
   }
 }
 
