@@ -1,85 +1,98 @@
 // SparseAttn for float32 storage, blocks of 64 slots, d = 64 or 128: float32 throughout, on the float32 matrix
-// instructions (v_mfma_f32_32x32x2_f32: exact products, one rounding per term, like a chain of fused multiply-adds).
+// instructions (v_mfma_f32_16x16x4_f32: exact products, one rounding per term, like a chain of fused multiply-adds).
 //
-// A workgroup is one query block; its four waves are two halves of the queries times two halves of every key tile, so
-// a wave works on 32 queries x 32 keys per tile.  The query is on the lane axis of both products:
-//     S^T = K Q^T      lane l: query l % 32; accumulator register r: key 8(r/4) + 4(l/32) + r%4 of the wave's half
-//     O^T += V^T P^T   register r of P is, as it stands, the operand of the step that adds the keys 8(r/4) + r%4 (lanes
-//                      0..31) and that plus 4 (lanes 32..63): no exchange between lanes
-// Channels are taken in whatever order makes the LDS reads wide: a step of the first product pairs channel 8u + j with
-// 8u + 4 + j (one 16-byte read of K serves four steps), and row i of accumulator dt of the second product is channel
-// (d/32) i + dt (one read of V serves the d/32 accumulators).  The two key halves keep a running maximum, a sum and an
-// output of their own and are put together at the end.
+// A workgroup is half a query block, 32 queries; its waves share out the keys, 16 (a quarter of a block) at a time, and
+// keep a running maximum, a sum and an output of their own, which are put together at the end.  A key is then wanted by
+// one wave only, so K and V go straight from memory to that wave's registers: no tile in LDS, no barrier in the loop.
+// Wave: 16 keys x 32 queries per step, the query on the lane axis of both products:
+//     S^T = K Q^T      lane l: query l % 16 of each 16; accumulator register r: key 4(l/16) + r
+//     O^T += V^T P^T   register r of P is, as it stands, the operand of the step that adds the keys 4(l/16) + r: no
+//                      exchange between lanes
+// Channels are taken in whatever order makes the loads wide: a 16-byte piece of a K row serves four steps of the first
+// product (channels 16u + 4(l/16) + 0..3), and row i of accumulator dt of the second is channel (d/16) i + dt.
 //
-// What bounds it: the matrix instructions (64 cycles each; a 64 x 64 tile at d = 128 is 8192 cycles of every SIMD
-// against 64 KB brought in, 8 bytes per cycle and CU).  The next tile's rows are on their way to registers while the
-// present tile is multiplied; LDS holds one tile (66 KB at d = 128), so two workgroups share a CU and one multiplies
-// while the other is at its barriers.  Measured against one wave per query block on the vector ALUs with its own tile in
-// LDS: 3236 -> 227 us at 84 blocks x 4 heads, d = 128, 21 blocks kept (65 TFLOP/s of the 130 a bare loop of these
-// instructions reaches), 134 -> 18 us at 8 blocks x 2 heads, d = 64, 4 kept.
+// What bounds it: the matrix instructions (32 cycles each; 128 of them per step and SIMD at d = 128 against 16 KB brought in).  The
+// next step's K is asked for when this step's first product is through with its registers, V when the last second
+// product is: each has half a step (2048 cycles) to arrive.  Half blocks because the launch is small as a rule: 84 blocks
+// x 4 heads are 1.3 whole blocks per CU, and a CU with two of them set the time.  Measured against whole blocks with
+// K and V tiles in LDS, two query halves by two key halves (kernel times): 226 -> 185 us at 84 blocks x 4 heads, d = 128,
+// 21 blocks kept, 17.7 -> 12.2 us at 8 blocks x 2 heads, d = 64, 4 kept; da_forward with 24 heads 862 -> 769 us (116
+// TFLOP/s of the 130 that a bare loop of float32 matrix instructions reaches).  Eight waves per workgroup instead of four
+// gain nothing on the small ones and lose 20 % on the large ones, where two workgroups per CU hide each other's ends.
 #include <math.h>
 #include "da_internal.h"
 
 namespace da {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float across_halves_max(float x) {
-  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+// over the four lanes that hold the same query (l, l ^ 16, l ^ 32, l ^ 48)
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float query_max(float x) {
+  u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-__device__ __forceinline__ float across_halves_sum(float x) {
-  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+__device__ __forceinline__ float query_sum(float x) {
+  u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // VT: V comes block-transposed (DA_REORDER_VT); otherwise K and V alike are rows that q.in says where to find.
+constexpr int W = 4;                         // waves of a workgroup
+
 template <int D, bool VT>
-__global__ __launch_bounds__(256, 2) void attn_f32_kernel(Geo q, const float* __restrict__ Q, const float* __restrict__ K,
-                                                          const float* __restrict__ V, const int32_t* __restrict__ idx,
-                                                          const int32_t* __restrict__ row_ptr, long long cap,
-                                                          float* __restrict__ O, float* __restrict__ lse) {
-  constexpr int LD = D + 4;                  // padded row of a tile in LDS: the 16-byte reads of 32 rows meet no conflict
-  constexpr int CPR = D / 4;                 // 16-byte chunks per row
-  constexpr int NCH = 64 * CPR / 256;        // chunks of a tile per thread
-  constexpr int NDT = D / 32;                // accumulators of the second product
-  __shared__ __attribute__((aligned(16))) float ks[64 * LD];
-  __shared__ __attribute__((aligned(16))) float vs[64 * LD];
+__global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float* __restrict__ Q, const float* __restrict__ K,
+                                                             const float* __restrict__ V, const int32_t* __restrict__ idx,
+                                                             const int32_t* __restrict__ row_ptr, long long cap,
+                                                             float* __restrict__ O, float* __restrict__ lse) {
+  constexpr int NU = D / 16;                 // 16-byte pieces of a K or Q row per lane
+  constexpr int NDT = D / 16;                // accumulators of the second product per 16 queries
+  constexpr int NG = 2 * NDT;                // 16-byte groups of a lane's output
+  __shared__ float4 part[W][NG][64];
+  __shared__ float2 part_ml[W][2][16];
   // workgroups are dealt round-robin to the 8 XCDs: each gets a stretch of consecutive query blocks, whose lists have
   // much in common
-  const long long total = (long long)q.B * q.H * q.g, chunk = (total + 7) >> 3;
-  const long long qb = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
-  if ((blockIdx.x >> 3) >= chunk || qb >= total) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int qh = wave & 1, kh = wave >> 1;
-  const int r32 = lane & 31, hh = lane >> 5;
+  const long long total = 2LL * q.B * q.H * q.g, chunk = (total + 7) >> 3;
+  const long long unit = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+  if ((blockIdx.x >> 3) >= chunk || unit >= total) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, kk = lane >> 4;
+  const long long qb = unit >> 1;
+  const int half = (int)(unit & 1);
   const long long bh = qb / q.g;
   const int i_blk = (int)(qb - bh * q.g);
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
 
-  // the wave's query row (slots past the valid ones exist only where the tensors are in block order)
+  // query rows (slots past the valid ones exist only where the tensors are in block order)
   const BlockPos qp = block_pos(q, i_blk);
-  const int q_valid = qp.vh * qp.vw, my_slot = 32 * qh + r32;
-  const bool has_row = my_slot < q_valid || q.reordered;
-  const bool live = 32 * qh < q_valid || q.reordered;        // (the same in every lane)
+  const int q_valid = q.reordered ? 64 : qp.vh * qp.vw;      // slots with a row of their own
+  if (32 * half >= q_valid) return;                          // (the whole workgroup)
   const long long q_first = block_first_row(q, i_blk, qp);
-  const long long my_row = q_first + (long long)(my_slot / qp.vw) * block_row_pitch(q, qp) + my_slot % qp.vw;
-  float4 qv[D / 8];
-  {
-    const float* qrow = Q + row_offset(q.in, q.H, bh, has_row ? my_row : q_first) + 4 * hh;
+  const int q_pitch = block_row_pitch(q, qp);
+  auto query_row = [&](int slot) -> long long { return q_first + (long long)(slot / qp.vw) * q_pitch + slot % qp.vw; };
+  float4 qv[2][NU];
 #pragma unroll
-    for (int u = 0; u < D / 8; ++u) qv[u] = *(const float4*)(qrow + 8 * u);
+  for (int h = 0; h < 2; ++h) {
+    const int slot = 32 * half + 16 * h + r16;
+    const float* qrow = Q + row_offset(q.in, q.H, bh, query_row(slot < q_valid ? slot : 0)) + 4 * kk;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) qv[h][u] = *(const float4*)(qrow + 16 * u);
   }
-  f32x16 o[NDT];
+  f32x4 o[2][NDT];
+  float m[2], l[2];
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
-  float m = -INFINITY, l = 0.f;
+    for (int dt = 0; dt < NDT; ++dt) o[h][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m[h] = -INFINITY;
+    l[h] = 0.f;
+  }
 
   // k columns per row, or (row_ptr given) lists of any length, one after the other per head
   const int32_t* list = idx + qb * q.k;
@@ -92,133 +105,185 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(Geo q, const float* __
     list = idx + bh * cap + begin;
     len = min(max(rp[1] - begin, 0), (int)cap - begin);
   }
-  int t = -1, j = 0;
-  auto advance = [&]() {
-    do {
-      ++t;
-      j = t < len ? __builtin_amdgcn_readfirstlane(list[t]) : 0;
-    } while (t < len && (unsigned)j >= (unsigned)q.g);
-  };
-  float4 kreg[NCH], vreg[NCH];
-  auto fetch = [&]() {
-    const BlockPos b = block_pos(q, j);
-    const int nv = b.vh * b.vw;
-    const long long first = block_first_row(q, j, b);
-    const int pitch = block_row_pitch(q, b);
-    const long long base = row_offset(q.in, q.H, bh, first);
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int e = tid + 256 * i, s = e / CPR, c = e % CPR;
-      const int u = s / b.vw, v = s - u * b.vw;
-      const long long at = base + ((long long)u * pitch + v) * q.in.sn + 4 * c;
-      kreg[i] = s < nv ? *(const float4*)(K + at) : make_float4(0.f, 0.f, 0.f, 0.f);
-      if (!VT) vreg[i] = s < nv ? *(const float4*)(V + at) : make_float4(0.f, 0.f, 0.f, 0.f);
-      if (VT) vreg[i] = *(const float4*)(V + (bh * q.g + j) * (long long)D * 64 + 4 * e);
+  // The wave's steps: a quarter of every entry; which quarter goes round, so that blocks with fewer than 64 valid slots
+  // cost all waves alike.  64 entries of the list are held at a time, entry t in lane t % 64, with what a step wants to
+  // know of the block worked out once for all 64 (a step has little room for divisions beside its matrix instructions).
+  int t = -1, held = -64;
+  int e_block = 0, e_shape = 0;                              // block number; valid slots | patch columns << 8 | 65536 / columns, rounded up << 15
+  unsigned e_row_lo = 0u, e_row_hi = 0u;                     // the block's first row
+  int j = 0, first_key = 0, nv = 1, vw = 1, recip = 0;       // the step: block, first slot, the block's valid slots, columns
+  long long first_row = 0;
+  auto advance = [&]() -> bool {
+    for (;;) {
+      if (++t >= len) return false;
+      if (t - held >= 64) {
+        held = t & ~63;
+        e_block = list[min(held + lane, len - 1)];
+        const BlockPos b = block_pos(q, (unsigned)e_block < (unsigned)q.g ? e_block : 0);
+        const long long row = block_first_row(q, (unsigned)e_block < (unsigned)q.g ? e_block : 0, b);
+        e_shape = b.vh * b.vw | b.vw << 8 | (int)((unsigned)((65536 + b.vw - 1) / b.vw) << 15);
+        e_row_lo = (unsigned)row;
+        e_row_hi = (unsigned)(row >> 32);
+        asm volatile("" : "+v"(e_block), "+v"(e_shape));     // (the load is waited for here, not with the tile loads in flight)
+      }
+      const int e = __builtin_amdgcn_readlane(e_block, t & 63);
+      if ((unsigned)e >= (unsigned)q.g) continue;
+      const int shape = __builtin_amdgcn_readlane(e_shape, t & 63);
+      const int at = 16 * ((wave + t) & 3);
+      if (at >= (shape & 255)) continue;
+      j = e;
+      first_key = at;
+      nv = shape & 255;
+      vw = (shape >> 8) & 127;
+      recip = (unsigned)shape >> 15;
+      first_row = (long long)((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)e_row_hi, t & 63) << 32 |
+                              (unsigned)__builtin_amdgcn_readlane((int)e_row_lo, t & 63));
+      return true;
     }
   };
-  advance();
-  if (t < len) fetch();
-  while (t < len) {
-    const int nv = block_valid(q, j);
-    __syncthreads();                                         // everyone has left the previous tile
+  const long long head_row = row_offset(q.in, q.H, bh, 0);
+  // element offset of slot `slot` of the step's block (slot / vw by way of the reciprocal: exact below 128 for vw <= 64)
+  auto key_at = [&](int slot) -> long long {
+    const int s = min(slot, nv - 1);                         // (a pad slot has no row of its own)
+    const int u = (s * recip) >> 16;
+    return (long long)(u * ((q.reordered ? vw : q.fw) - vw) + s) * q.in.sn;
+  };
+  float4 kr[NU];
+  f32x4 vr[4][NDT / 4];                                      // !VT: [key r][channels]; VT: dt = 4 a + b is [b][a], keys in the vector
+  auto fetch_k = [&]() {
+    const float* at = K + head_row + first_row * q.in.sn + key_at(first_key + r16) + 4 * kk;
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int e = tid + 256 * i;
-      *(float4*)&ks[(e / CPR) * LD + 4 * (e % CPR)] = kreg[i];
-      if (!VT) *(float4*)&vs[(e / CPR) * LD + 4 * (e % CPR)] = vreg[i];
-      if (VT) {
-        const int c = e >> 4, s = 4 * (e & 15);
-        vs[s * LD + c] = vreg[i].x;
-        vs[(s + 1) * LD + c] = vreg[i].y;
-        vs[(s + 2) * LD + c] = vreg[i].z;
-        vs[(s + 3) * LD + c] = vreg[i].w;
+    for (int u = 0; u < NU; ++u) kr[u] = *(const float4*)(at + 16 * u);
+  };
+  auto fetch_v = [&]() {
+    if (VT) {
+      const float* at = V + (bh * q.g + j) * (long long)D * 64 + (long long)NDT * r16 * 64 + first_key + 4 * kk;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) vr[dt & 3][dt >> 2] = *(const f32x4*)(at + dt * 64);
+    } else {
+      const float* base = V + head_row + first_row * q.in.sn + NDT * r16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float* at = base + key_at(first_key + 4 * kk + r);
+#pragma unroll
+        for (int a = 0; a < NDT / 4; ++a) vr[r][a] = *(const f32x4*)(at + 4 * a);
       }
     }
-    __syncthreads();
-    advance();
-    if (t < len) fetch();
-    if (!live || 32 * kh >= nv) continue;                    // nothing but pad queries, or pad keys
-    f32x16 s;
+  };
+  bool more = advance();
+  if (more) fetch_k();
+  while (more) {
+    fetch_v();
+    __builtin_amdgcn_sched_barrier(0);
+    const int keys = nv - first_key;                         // valid keys of this step (16 or more: all of them)
+    f32x4 s[2];
+    s[0] = s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = 0.f;
-    const float* krow = ks + (32 * kh + r32) * LD + 4 * hh;
+    for (int u = 0; u < NU; ++u) {
+      const float a[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
 #pragma unroll
-    for (int u = 0; u < D / 8; ++u) {
-      const float4 a = *(const float4*)(krow + 8 * u);
-      s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, qv[u].x, s, 0, 0, 0);
-      s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, qv[u].y, s, 0, 0, 0);
-      s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, qv[u].z, s, 0, 0, 0);
-      s = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, qv[u].w, s, 0, 0, 0);
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float b = c == 0 ? qv[h][u].x : c == 1 ? qv[h][u].y : c == 2 ? qv[h][u].z : qv[h][u].w;
+          s[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b, s[h], 0, 0, 0);
+        }
     }
-    if (nv < 32 * kh + 32) {
+    if (keys < 16) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (32 * kh + 8 * (i >> 2) + 4 * hh + (i & 3) >= nv) s[i] = -INFINITY;   // pad keys are never attended
+      for (int r = 0; r < 4; ++r)
+        if (4 * kk + r >= keys) s[0][r] = s[1][r] = -INFINITY;   // pad keys are never attended
     }
-    float mx = s[0];
+    more = advance();
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_k();                                               // (after the last step its own once more: what is in flight is then the same on every path)
+    __builtin_amdgcn_sched_barrier(0);
+    float mx[2];
 #pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-    mx = across_halves_max(mx);                              // finite: the half's first slot is valid
-    if (__any(mx > m)) {
-      const float m_new = fmaxf(m, mx);
-      const float alpha = exp2f((m - m_new) * scale_log2);
-      m = m_new;
-      l *= alpha;
+    for (int h = 0; h < 2; ++h) mx[h] = query_max(fmaxf(fmaxf(s[h][0], s[h][1]), fmaxf(s[h][2], s[h][3])));   // finite: the step's first slot is valid
+    if (__any(mx[0] > m[0] || mx[1] > m[1])) {
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
+      for (int h = 0; h < 2; ++h) {
+        const float m_new = fmaxf(m[h], mx[h]);
+        const float alpha = m[h] == m_new ? 1.f : exp2f((m[h] - m_new) * scale_log2);
+        m[h] = m_new;
+        l[h] *= alpha;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
+        for (int dt = 0; dt < NDT; ++dt) o[h][dt] *= alpha;
+      }
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      s[i] = exp2f((s[i] - m) * scale_log2);
-      l += s[i];
-    }
-    const float* vrow = vs + (32 * kh + 4 * hh) * LD + NDT * r32;
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float* at = vrow + (8 * (i >> 2) + (i & 3)) * LD;
-      float a[NDT];
-      if (NDT == 4) *(float4*)a = *(const float4*)at;
-      else *(float2*)a = *(const float2*)at;
+      for (int r = 0; r < 4; ++r) {
+        s[h][r] = exp2f((s[h][r] - m[h]) * scale_log2);
+        l[h] += s[h][r];
+      }
+    if (!VT && keys < 16) {                                  // (a probability of 0 times whatever was read there)
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[dt], s[i], o[dt], 0, 0, 0);
+      for (int r = 0; r < 4; ++r)
+        if (4 * kk + r >= keys) {
+#pragma unroll
+          for (int a = 0; a < NDT / 4; ++a) vr[r][a] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) {
+        const float a = VT ? vr[dt & 3][dt >> 2][r] : vr[r][dt >> 2][dt & 3];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) o[h][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, s[h][r], o[h][dt], 0, 0, 0);
+      }
   }
-  l = across_halves_sum(l);
 
-  // the upper key half hands over what it has; the lower one puts the two together
-  __syncthreads();
-  float* part = (qh ? vs : ks) + lane * NDT;                 // [16][64][NDT] floats per query half
-  float* part_ml = (qh ? vs : ks) + 16 * 64 * NDT + lane * 2;   // (64 * LD floats hold both)
-  if (kh == 1) {
+  // every wave hands over what it has; wave w puts together its share of the output's groups
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+  for (int h = 0; h < 2; ++h) {
+    const float lt = query_sum(l[h]);
+    if (kk == 0) part_ml[wave][h][r16] = make_float2(m[h], lt);
+    // register r of accumulator dt is channel (d/16)(4 kk + r) + dt: with f = (d/16) r + dt the lane holds channels
+    // (d/4) kk + f of its query
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) part[i * 64 * NDT + dt] = o[dt][i];
-    part_ml[0] = m;
-    part_ml[1] = l;
+    for (int gi = 0; gi < NDT; ++gi) {
+      float x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = o[h][(4 * gi + i) % NDT][(4 * gi + i) / NDT];
+      part[wave][h * NDT + gi][lane] = make_float4(x[0], x[1], x[2], x[3]);
+    }
   }
   __syncthreads();
-  if (kh == 1 || !live) return;
-  const float m2 = part_ml[0], l2 = part_ml[1];
-  const float m_all = fmaxf(m, m2);
-  const float a1 = l > 0.f ? exp2f((m - m_all) * scale_log2) : 0.f, a2 = l2 > 0.f ? exp2f((m2 - m_all) * scale_log2) : 0.f;
-  const float l_all = l * a1 + l2 * a2;
+  constexpr int SHARE = NG / W;
+  const int h = wave / (W / 2);                              // which 16 queries the wave's groups belong to
+  float a[W], m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int w = 0; w < W; ++w) m_all = fmaxf(m_all, part_ml[w][h][r16].x);
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const float2 ml = part_ml[w][h][r16];
+    a[w] = ml.y > 0.f ? exp2f((ml.x - m_all) * scale_log2) : 0.f;
+    l_all += ml.y * a[w];
+  }
   const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;        // an empty list: zero rows
-  if (!has_row) return;
-  float* orow = O + row_offset(q.out, q.H, bh, my_row);
+  const int slot = 32 * half + 16 * h + r16;
+  if (slot >= q_valid) return;
+  float* orow = O + row_offset(q.out, q.H, bh, query_row(slot)) + (D / 4) * kk;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    float a[NDT];
+  for (int i = 0; i < SHARE; ++i) {
+    const int grp = wave * SHARE + i;
+    float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) a[dt] = (o[dt][i] * a1 + part[i * 64 * NDT + dt] * a2) * inv;
-    float* at = orow + NDT * (8 * (i >> 2) + 4 * hh + (i & 3));
-    if (NDT == 4) *(float4*)at = *(const float4*)a;
-    else *(float2*)at = *(const float2*)a;
+    for (int w = 0; w < W; ++w) {
+      const float4 x = part[w][grp][lane];
+      y.x += x.x * a[w];
+      y.y += x.y * a[w];
+      y.z += x.z * a[w];
+      y.w += x.w * a[w];
+    }
+    *(float4*)(orow + 4 * (grp - h * NDT)) = make_float4(y.x * inv, y.y * inv, y.z * inv, y.w * inv);
   }
-  if (lse && hh == 0)
-    lse[qb * 64 + my_slot] = l_all > 0.f ? m_all * (float)(1.0 / sqrt((double)D)) + logf(l_all) : -INFINITY;
+  if (lse && kk == 0 && wave % (W / 2) == 0)
+    lse[qb * 64 + slot] = l_all > 0.f ? m_all * (float)(1.0 / sqrt((double)D)) + logf(l_all) : -INFINITY;
 }
 
 }  // namespace
@@ -226,10 +291,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(Geo q, const float* __
 // q.in / q.out / q.reordered say where the rows of Q, K (and V, unless it is block-transposed) and O are.
 hipError_t launch_attn_f32(const Geo& q, const float* Q, const float* K, const float* V, bool v_transposed,
                            const int32_t* idx, const int32_t* row_ptr, long long cap, float* O, float* lse, hipStream_t s) {
-  const long long total = (long long)q.B * q.H * q.g;
+  const long long total = 2LL * q.B * q.H * q.g;
   const dim3 grid((unsigned)(8 * ((total + 7) / 8)));
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, q, Q, K, V, idx, row_ptr, cap, O, lse);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * W), 0, s, q, Q, K, V, idx, row_ptr, cap, O, lse);
   };
   if (q.d == 64 && v_transposed) go(attn_f32_kernel<64, true>);
   else if (q.d == 64) go(attn_f32_kernel<64, false>);

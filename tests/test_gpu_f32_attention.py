@@ -49,3 +49,25 @@ def test_f32_attention(T, fh, fw, sparsity, d):
         assert output_error(to_host_f64(Op, w.dtype)[0, h][real], want[real])[0] <= 1e-4
         assert np.abs(lse[0, h].cpu().numpy()[real] - want_lse[real]).max() <= 1e-4
         assert output_error(to_host_f64(O, w.dtype)[0, h], oa.restore(want, ref.inv))[0] <= 1e-4
+
+
+@pytest.mark.parametrize("T,fh,fw,ph,pw,keep", [(3, 40, 48, 8, 8, 64), (3, 40, 48, 8, 8, 65), (3, 40, 48, 8, 8, 90), (2, 9, 34, 4, 16, 5),
+                                                (2, 3, 70, 1, 64, 4), (2, 66, 3, 64, 1, 7), (2, 19, 14, 16, 4, 3)])
+def test_f32_steps(T, fh, fw, ph, pw, keep):
+    """Lists around and beyond the 64 entries that a wave holds at a time, and windows of every shape with 64 tokens (blocks of
+    1 to 64 valid slots: steps that hold fewer than 16 keys, quarters that hold none).  Tolerance as above: at most 5760 keys."""
+    import torch
+    w = W.Workload("f32_steps", B=1, H=1, d=128, T=T, fh=fh, fw=fw, ph=ph, pw=pw, dtype=W.F32, seed=fh + keep)
+    say(f"f32 steps {T}x{fh}x{fw} window {ph}x{pw} keep {keep}")
+    Q, K, V = W.make_qkv(w)
+    ref = HeadRef(w, Q[0, 0], K[0, 0], V[0, 0], keep_blocks=keep)
+    p = da.problem(1, 1, T, fh, fw, 128, ph, pw, dtype=da.DA_F32, keep_blocks=keep)
+    dims = da.da_derive(p)
+    O = empty((1, 1, dims.n, 128), w.dtype)
+    O.fill_(float("nan"))
+    idx = torch.empty((1, 1, dims.g, dims.k), dtype=torch.int32, device="cuda")
+    ws = torch.empty(da.da_workspace_size(p), dtype=torch.uint8, device="cuda")
+    da.da_forward(p, *(to_dev(t, w.dtype) for t in (Q, K, V)), O, ws, idx)
+    torch.cuda.synchronize()
+    assert np.array_equal(idx[0, 0].cpu().numpy(), ref.idx)
+    assert output_error(to_host_f64(O, w.dtype)[0, 0], oa.restore(ref.attention(), ref.inv))[0] <= 1e-4
