@@ -12,7 +12,8 @@
 // Workgroup = 8 wavefronts, two per SIMD: while one is in its softmax (vector ALU) the other keeps the matrix pipe
 // busy, and the pairing hides LDS latency, the wait for V and the waits of the ring protocol.  A wavefront owns 64
 // queries (a block) and every other entry of that block's list; the two waves of a block put their sums together at the
-// end.  (With 32 queries and every entry per wave, a key tile is read from LDS and its V from L2 twice: V alone was 128
+// end.  (Launches of few workgroups share some of them out among two or four, with four or eight waves per block:
+// share_out.)  (With 32 queries and every entry per wave, a key tile is read from LDS and its V from L2 twice: V alone was 128
 // KB per tile step over a path of 64 bytes per cycle and CU.  Measured on 24 heads x 1980 blocks, 198 kept: 21.6 -> 19.8
 // ms where nothing is dropped, 12.0 -> 11.8 ms on peaked inputs.)  64 queries are 128 registers of output, 64 of Q and
 // 32 of scores, which leaves 32 for everything else at two waves per SIMD: tiles are taken 32 keys at a time, operands
@@ -94,7 +95,7 @@ constexpr float kC2 = 0.08838834764831845f * 1.4426950408889634f;   // log2(e)/s
 constexpr float kLazy = 8.0f;                     // move the running max only past this many powers of two
 constexpr float kDropLog2 = 14.0f;                // all keys dropped from a row together weigh less than 2^-14 of its largest term
 constexpr int kSpinLimit = 1 << 20;
-constexpr int kPeekTiles = 16;                      // lists of at least so many tiles: both waves of a group look at the first one
+constexpr int kPeekTiles = 8;                       // lists of at least so many tiles per wave: all waves of a group look at the first one
 
 // Waves whose bounded wait for a tile ran out since the library was loaded (their rows were written as NaN).
 // No valid input makes that happen; the host can ask (da_wait_failures).
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
                                                                const int32_t* __restrict__ idx,
                                                                const int32_t* __restrict__ row_ptr, long long cap,
                                                                unsigned char* __restrict__ Op, float* __restrict__ lse,
-                                                               int balance, float skip, int direct,
+                                                               int balance, float skip, int direct, int wide, int split,
                                                                unsigned long long* __restrict__ tile_counts) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_TOTAL];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -379,13 +380,24 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const int pos_per_xcd = (per_frame + 7) >> 3;
   const int regular = 8 * pos_per_xcd * fgs;
   const int wg_per_head = regular + plan.tail_wgs;
-  const long long bh = blockIdx.x / wg_per_head;
+  // The first `wide` workgroups are whole ones.  The others share the four groups of 64 queries of a whole one between
+  // them, 2^split of them (sub = which), and put twice or four times as many waves to a group; the shares of a whole one
+  // stay on its XCD.
+  const int narrow = max((int)blockIdx.x - wide, 0);
+  const int lsub = (int)blockIdx.x < wide ? 0 : split;
+  const int sub = lsub ? (narrow >> 3) & ((1 << lsub) - 1) : 0;
+  const int whole = lsub ? wide + (narrow >> (3 + lsub)) * 8 + (narrow & 7) : (int)blockIdx.x;
+  const long long bh = whole / wg_per_head;
+  if (bh >= (long long)q.B * q.H) return;             // (the last eight whole ones need not be eight)
   // the tail workgroups (longer walks) come first within a head, the regular ones after them
-  const int n = blockIdx.x - (int)(bh * wg_per_head) - plan.tail_wgs;   // < 0: tail workgroup n + tail_wgs
-  // Four groups of 64 queries (a block, or half a block of 128), two waves each; waves w and w+4 share a SIMD: give them
-  // different groups.  The two waves of a group take its list entries in turn (part = which of the two).
-  const int part = wave >> 2;
-  const int group = (wave + 2 * part) & 3;
+  const int n = whole - (int)(bh * wg_per_head) - plan.tail_wgs;   // < 0: tail workgroup n + tail_wgs
+  // Four groups of 64 queries (a block, or half a block of 128), two waves each (in a share: two groups, four waves
+  // each, or one group, eight waves); waves w and w+4 share a SIMD: give them different groups where there are some.
+  // The waves of a group take its list entries in turn (part = which of them).
+  const int groups = 4 >> lsub, parts = 2 << lsub;
+  const int part = wave >> (2 - lsub);
+  const int lgroup = (wave + (lsub ? wave >> 2 : 2 * part)) & (groups - 1);   // number of the group in this workgroup
+  const int group = sub * groups + lgroup;            // and in the whole one
   const int qblk = SUB == 1 ? group : group >> 1;
   const int qsub = SUB == 1 ? 0 : group & 1;          // which 64 queries of the block
   // query block w of this workgroup: (position, frame), or none
@@ -400,11 +412,18 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     return fgs * FG + (w - small_div(w, plan.rem) * plan.rem);
   };
   // block number of query block w, -1 if the slot is empty
+  const int first_slot = sub * groups / SUB, last_slot = (sub * groups + groups - 1) / SUB;   // those of this workgroup
   auto slot_block = [&](int w) -> int {
     const int p = slot_pos(w), fr = slot_frame(w);
-    return p < per_frame && fr < q.T ? fr * per_frame + p : -1;
+    return w >= first_slot && w <= last_slot && p < per_frame && fr < q.T ? fr * per_frame + p : -1;
   };
-  if (n >= 0 && slot_pos(0) >= per_frame) return;     // a regular workgroup past the last position: all of it leaves
+  // a regular workgroup past the last position, or a share without a block: all of it leaves
+  if (n >= 0 && slot_pos(0) >= per_frame) return;
+  {
+    bool any = false;
+    for (int w = first_slot; w <= last_slot; ++w) any = any || slot_block(w) >= 0;
+    if (!any) return;
+  }
   const int my_block = slot_block(qblk);
   const bool has_block = my_block >= 0;
   // a wave without a query block, or whose 64 slots of it are all pad slots, only helps with the ring
@@ -469,7 +488,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 
   // ---- union of the workgroup's lists (the first 256 entries of a list are asked for before the
   // bitmaps are cleared, so that the two latencies overlap)
-  const bool lister = live && part == 0 && qsub == 0; // the wave that brings in the list of its query block
+  const bool lister = live && part == 0 && (qsub == 0 || groups == 1); // the wave that brings in the list of its query block
   int pre[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) pre[i] = lister && lane + 64 * i < k ? list[lane + 64 * i] : -1;
@@ -586,7 +605,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   // walk goes by ascending key.  Every stretch of the walk then holds every block's fair share.
   // The softmax does not care about the order of the keys.  (Skipped when the two extra
   // arrays it needs do not fit in LDS; the walk is then in ascending order.)
-  if (balance) {
+  if (balance && first_slot != last_slot) {
     unsigned* rest = ulist + n_own;                   // the own blocks keep their place in front
     const int nR = nU - n_own;
     unsigned* upos = ulist + union_max;               // position of an entry inside its class
@@ -647,13 +666,13 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   }
 
   // The first entry of a group's walk is the best start for its running maxima (its own block, as a rule).  One of the
-  // two waves takes it; the other looks at its scores before it starts, so that neither has to carry out tiles that the
+  // group's waves takes it; the others look at its scores before they start, so that none has to carry out tiles that the
   // drop rule would spare it.  Not worth a product where a wave has few tiles.
   const unsigned my_bit = live ? (1u << (28 + qblk)) : 0u;
   int* first = wcount;                                // [4] that entry of each group, -1: nobody looks
   {
     int f = -1;
-    if (live && k * SUB >= kPeekTiles)
+    if (live && k * SUB >= kPeekTiles * parts)
       for (int base = 0; base < nU; base += 64) {
         const unsigned long long m = __ballot(base + lane < nU && (ulist[min(base + lane, nU - 1)] & my_bit) != 0u);
         if (m) {
@@ -678,12 +697,12 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   // one wave brings the K tile of union entry u into ring slot u % RING
   auto issue_tile = [&](int u) {
     const unsigned e = (unsigned)__builtin_amdgcn_readfirstlane((int)ulist[u]);
-    // how many waves will read the tile: one of each live group that holds the entry, and the second one where it looks
+    // how many waves will read the tile: one of each live group that holds the entry, and the others where they look
     int readers = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const int holds = (live_groups >> w) & (int)(e >> (28 + (SUB == 1 ? w : w >> 1))) & 1;
-      readers += holds + (u == first_of[w] ? holds : 0);
+      readers += holds + (u == first_of[w] ? holds * (parts - 1) : 0);
     }
     if (lane == 0) __atomic_store_n(&left[u & (RING - 1)], readers, __ATOMIC_RELAXED);   // (before the transfer, hence before the slot is published)
     const long long j = (long long)(e & 0x3fffffu);
@@ -775,7 +794,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   };
   const bool two = q_valid > 32;                      // else the second 32 queries are all pad slots
   int tiles_seen = 0, tiles_kept = 0;                 // (scalar registers; reported when the caller asks for the counts)
-  if (live && part == 1 && first_of[group] >= 0) {
+  if (live && part > 0 && first_of[group] >= 0) {
     const int u = first_of[group];
     gave_up = !arrived(u);
     if (!gave_up) {
@@ -791,14 +810,14 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     }
   }
   // The walk, 64 entries at a time: lane i holds entry base + i, a ballot tells which of them are my group's, a second
-  // one which of those are mine (every other one).  Entries that are not mine cost nothing.
+  // one which of those are mine (every other one, or fourth, or eighth).  Entries that are not mine cost nothing.
   int before = 0;                                     // entries of my group in the chunks before
   for (int base = 0; base < nU && !gave_up; base += 64) {
     const int at = base + opaque_lane();
     const unsigned e_lane = ulist[min(at, nU - 1)];
     const bool is_ours = at < nU && (e_lane & my_bit) != 0u;
     const unsigned long long ours = __ballot(is_ours);
-    unsigned long long mine = __ballot(is_ours && ((before + lanes_before(ours) + part) & 1) == 0);
+    unsigned long long mine = __ballot(is_ours && ((before + lanes_before(ours)) & (parts - 1)) == part);
     before += __popcll(ours);
     while (mine) {
       const int i = (int)__builtin_ctzll(mine);
@@ -836,24 +855,66 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   }
   __syncthreads();                                    // everyone is done with the ring: reuse it to put the halves together
 
-  // ---- the two waves of a group: each hands over what it has of 32 queries and puts the other 32 together
   lane = opaque_lane();
   const int r = lane & 31, hh = lane >> 5;
-  const int partner = part ? group : 4 + ((group + 2) & 3);
-  unsigned char* const given = smem + wave * (RING_BYTES / WAVES);      // 16 KB to hand over in
-  unsigned char* const taken = smem + partner * (RING_BYTES / WAVES);
   float2* const ml = (float2*)(smem + RING_BYTES) + lane;               // [WAVES][64] reference and normaliser (the bitmaps are done with)
+  // ---- where a group has more than two waves: the upper half of them hands over what it has, the lower half adds it to
+  // its own, until two are left (four waves hand over 32 KB each at first: the ring's place holds that)
+  for (int half = parts >> 1; half >= 2; half >>= 1) {
+    unsigned char* const place = smem + ((part & (half - 1)) * groups + lgroup) * (RING_BYTES / 4);
+    float2* const pml = ml + ((part & (half - 1)) * groups + lgroup) * 128;
+    if (part >= half && part < 2 * half) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+            *(float4*)(place + (((h * 4 + dt) * 4 + a) * 64 + lane) * 16) =
+                make_float4(o[h][dt][4 * a], o[h][dt][4 * a + 1], o[h][dt][4 * a + 2], o[h][dt][4 * a + 3]);
+        pml[h * 64] = make_float2(st[h].m, st[h].l);
+      }
+    }
+    __syncthreads();
+    if (part < half) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float2 other = pml[h * 64];
+        const float m_all = fmaxf(st[h].m, other.x);
+        const float a_mine = st[h].m == m_all ? 1.f : __builtin_amdgcn_exp2f((st[h].m - m_all) * kC2);
+        const float a_other = other.x == m_all ? 1.f : __builtin_amdgcn_exp2f((other.x - m_all) * kC2);
+        st[h].m = m_all;
+        st[h].l = st[h].l * a_mine + other.y * a_other;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            const float4 y = *(const float4*)(place + (((h * 4 + dt) * 4 + a) * 64 + lane) * 16);
+            o[h][dt][4 * a] = o[h][dt][4 * a] * a_mine + y.x * a_other;
+            o[h][dt][4 * a + 1] = o[h][dt][4 * a + 1] * a_mine + y.y * a_other;
+            o[h][dt][4 * a + 2] = o[h][dt][4 * a + 2] * a_mine + y.z * a_other;
+            o[h][dt][4 * a + 3] = o[h][dt][4 * a + 3] * a_mine + y.w * a_other;
+          }
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- the (last) two waves of a group: each hands over what it has of 32 queries and puts the other 32 together
+  unsigned char* const given = smem + (part * groups + lgroup) * (RING_BYTES / WAVES);      // 16 KB to hand over in
+  unsigned char* const taken = smem + ((part ^ 1) * groups + lgroup) * (RING_BYTES / WAVES);
   auto give = [&](const f32x16 (&x)[4], const Soft& sx) {
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int a = 0; a < 4; ++a)
         *(float4*)(given + ((dt * 4 + a) * 64 + lane) * 16) = make_float4(x[dt][4 * a], x[dt][4 * a + 1], x[dt][4 * a + 2], x[dt][4 * a + 3]);
-    ml[wave * 64] = make_float2(sx.m, sum_across_halves(sx.l));
+    ml[(part * groups + lgroup) * 64] = make_float2(sx.m, sum_across_halves(sx.l));
   };
-  if (part) give(o[0], st[0]);
-  else give(o[1], st[1]);
+  if (part == 0) give(o[1], st[1]);
+  else if (part == 1) give(o[0], st[0]);
   __syncthreads();
+  if (part > 1) return;                               // (put together with another wave's)
   const bool failed = (ctrl[29] >> group) & 1;        // a wait ran out: say so with NaN rather than with wrong numbers
   if (32 * part >= q_valid) {
     // 32 pad slots and nothing else: their rows of the reordered output are zeroed (in the original
@@ -872,7 +933,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 
   // ---- normalise, convert, stage through LDS, write rows of 256 B
   auto finish = [&](const f32x16 (&x)[4], const Soft& sx) {
-    const float2 other = ml[partner * 64];
+    const float2 other = ml[((part ^ 1) * groups + lgroup) * 64];
     const float l_mine = sum_across_halves(sx.l), m_all = fmaxf(sx.m, other.x);
     const float a_mine = l_mine > 0.f ? __builtin_amdgcn_exp2f((sx.m - m_all) * kC2) : 0.f;
     const float a_other = other.y > 0.f ? __builtin_amdgcn_exp2f((other.x - m_all) * kC2) : 0.f;
@@ -911,6 +972,44 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   }
 }
 
+// Which workgroups of a launch are whole (the first `wide`) and into how many shares (2^split) the others go.
+//
+// A workgroup fills a CU, so a launch of few comes in rounds of kCUs, and the last round takes as long as a full one
+// however few are in it.  A share of half of the queries puts twice as many waves to each list.  It is done in about
+// 0.6 of the time (key tiles are shared by fewer, and a ring of eight tiles looks less far ahead of more waves), a
+// quarter in about 0.45, so:
+//   - halves where the last round is at most half full (two halves fit where one whole did): 120 workgroups of 60 tiles
+//     158 -> 121 us, 315 of 315 tiles 1197 -> 988 us, 360 of 15 tiles 156 -> 139 us (times of da_forward); at 168 and 240
+//     in the last round 105 -> 119 and 177 -> 201 us;
+//   - quarters where all of the launch is at most a quarter of a round: 60 of 240 tiles 415 -> 188 us (halves 257), 15
+//     of 15 tiles 77 -> 57 us (63);
+//   - nothing after more than kMaxRounds rounds: workgroups differ in length, and by then they no longer end together
+//     (1575 workgroups, 39 in the last round: 4790 us either way).
+struct Share {
+  long long wide, grid;
+  int split;
+};
+constexpr int kCUs = 256;
+constexpr int kMaxRounds = 4;
+inline Share share_out(const Geo& q) {
+  const int per_frame = q.gh * q.gw;
+  const TailPlan plan = tail_plan(q, 4 * BS / q.block);
+  const long long per_head = 8LL * ((per_frame + 7) / 8) * plan.full_groups + plan.tail_wgs;
+  const long long bh = (long long)q.B * q.H, total = bh * per_head;
+  const long long live = bh * ((long long)per_frame * plan.full_groups + plan.tail_wgs);   // (the others leave at once)
+  const int last_round = (int)(live % kCUs);
+  Share s = {total, total, 0};
+  if (live > kMaxRounds * kCUs || last_round == 0 || 2 * last_round > kCUs) return s;
+  s.split = 4 * live <= kCUs ? 2 : 1;
+  // the last `last_round` live ones are shared out
+  for (int got = 0; got < last_round;) {
+    const long long n = --s.wide % per_head - plan.tail_wgs;
+    got += n < 0 || (n & 7) + 8 * ((n >> 3) / plan.full_groups) < per_frame;
+  }
+  s.grid = s.wide + (((total - s.wide + 7) / 8 * 8) << s.split);
+  return s;
+}
+
 }  // namespace ring
 
 // LDS left beside the ring: four bitmaps of g bits, the union list (at most min(g, 4k) entries)
@@ -929,15 +1028,15 @@ int attn_bf16_ring_fits(const Geo& q, bool any_length) {
 hipError_t launch_attn_bf16_ring(const Geo& q, const void* Qp, const void* Kp, const void* Vt, const int32_t* idx,
                                  const int32_t* row_ptr, long long cap, void* Op, float* lse, bool direct,
                                  unsigned long long* tile_counts, hipStream_t s) {
-  const int per_frame = q.gh * q.gw;
-  const int sub = q.block / ring::BS, fg = 4 / sub;
-  const ring::TailPlan plan = ring::tail_plan(q, fg);
-  unsigned grid = (unsigned)((long long)q.B * q.H * (8 * ((per_frame + 7) / 8) * plan.full_groups + plan.tail_wgs));
+  const int sub = q.block / ring::BS;
+  const ring::Share share = ring::share_out(q);
+  const unsigned grid = (unsigned)share.grid;
   const int balance = attn_bf16_ring_fits(q, row_ptr != nullptr) == 2 ? 1 : 0;
   const float skip = log2f((float)q.k * (float)q.block) + ring::kDropLog2;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), 0, s, q, (const unsigned char*)Qp, (const unsigned char*)Kp,
-                       (const unsigned char*)Vt, idx, row_ptr, cap, (unsigned char*)Op, lse, balance, skip, direct ? 1 : 0, tile_counts);
+                       (const unsigned char*)Vt, idx, row_ptr, cap, (unsigned char*)Op, lse, balance, skip, direct ? 1 : 0,
+                       (int)share.wide, share.split, tile_counts);
   };
   if (sub == 1 && !row_ptr) go(ring::attn_bf16_ring_kernel<1, false>);
   else if (sub == 1) go(ring::attn_bf16_ring_kernel<1, true>);
