@@ -6,6 +6,7 @@
 // depend on the launch shape:  acc = acc + x (one rounding per add), mean = acc / valid.
 // Q and K are read once and never again by this pass: the loads are marked non-temporal, so the stream does not
 // push anything else out of the L2 (measured on the headline shape: 5.4 -> 5.8 TB/s).
+#include <type_traits>
 #include "da_internal.h"
 
 #pragma clang fp contract(off)
@@ -126,6 +127,73 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(Geo q, const uint4* 
   for (int j = 0; j < N; ++j) dst[j] = MAXP ? acc[j] : acc[j] / cnt;   // IEEE division (correctly rounded is the compiler default for HIP)
 }
 
+// The same for launches that are too small to fill the chip (kSmallWaves) on grids that leave patch rows of fewer than
+// eight tokens: there a wave's turns at memory, one after the other, are the time, not the bytes, and pool_kernel takes
+// up to 64 of them where a patch row is cut (one token at a time; four where all are eight wide).  Here a lane owns 8
+// bytes of a block's rows instead of 16, which makes twice as many waves, and the loads of 64 tokens are all on their
+// way before the first is used, whatever the block's extent (slots past the last valid one read that again).  The order
+// of the sums is the same, token by token.  da_forward, one 30x52 frame, 48 heads: 109 -> 91 us; three of them in
+// float32, 4 heads: 115 -> 107 us; where every patch is eight wide (48x80, 24 heads) 109 us either way and on the
+// smallest 21.4 -> 22.5 us, so those stay with pool_kernel.
+template <int DT, bool REORDER, bool MAXP>
+__global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, const uint2* __restrict__ Q, const uint2* __restrict__ K,
+                                                                     float* __restrict__ q_pool, float* __restrict__ k_pool,
+                                                                     uint2* __restrict__ Qp, uint2* __restrict__ Kp, int cpr,
+                                                                     long long items) {
+  constexpr int N = Vec<DT>::N / 2;
+  constexpr int AHEAD = 64;
+  const long long item = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (item >= items) return;
+  const uint2* X = blockIdx.y ? K : Q;
+  float* out = blockIdx.y ? k_pool : q_pool;
+  const long long blk = item / cpr;   // over bh * g
+  const int c = (int)(item - blk * cpr);
+  const long long bh = blk / q.g;
+  const int i = (int)(blk - bh * q.g);
+  const BlockPos b = block_pos(q, i);
+  const int nv = b.vh * b.vw;
+  const unsigned sn = (unsigned)(q.in.sn / N);                            // pieces between consecutive rows of the source (the launcher has seen that it fits)
+  const int skip = block_row_pitch(q, b) - b.vw;                          // rows between a patch row's last token and the next one's first
+  const int recip = (65536 + b.vw - 1) / b.vw;                            // slot / vw by way of the reciprocal: exact below 256
+  const uint2* src = X + row_offset(q.in, q.H, bh, block_first_row(q, i, b)) / N + c;
+  uint2* const dbase = blockIdx.y ? Kp : Qp;          // NULL: this tensor is only pooled
+  const bool wr = REORDER && dbase != nullptr;
+  uint2* dstp = wr ? dbase + (blk * q.block) * cpr + c : nullptr;   // slot 0 of the block
+  float acc[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) acc[j] = MAXP ? -INFINITY : 0.f;
+  for (int s0 = 0; s0 < nv; s0 += AHEAD) {
+    uint2 r[AHEAD];
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t) {
+      const int s = min(s0 + t, nv - 1);
+      r[t] = src[(unsigned long long)(unsigned)(((s * recip) >> 16) * skip + s) * sn];
+    }
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t) {
+      const bool in = s0 + t < nv;
+      if (wr && s0 + t < q.block) dstp[(long long)(s0 + t) * cpr] = in ? r[t] : make_uint2(0u, 0u);
+      float f[Vec<DT>::N];
+      Vec<DT>::widen(make_uint4(r[t].x, r[t].y, 0u, 0u), f);
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const float with = MAXP ? (f[j] > acc[j] ? f[j] : acc[j]) : acc[j] + f[j];
+        acc[j] = in ? with : acc[j];
+      }
+    }
+  }
+  if (wr)
+    for (int sl = (nv + AHEAD - 1) / AHEAD * AHEAD; sl < q.block; ++sl) dstp[(long long)sl * cpr] = make_uint2(0u, 0u);
+  const float cnt = (float)nv;
+  float* dst = out + blk * q.d + c * N;
+#pragma unroll
+  for (int j = 0; j < N; ++j) dst[j] = MAXP ? acc[j] : acc[j] / cnt;
+}
+
+// Below this many waves of pool_kernel in all.  (1008 waves 243 -> 225 us, 2016 waves 391 -> 386 us, from 2940 on no
+// difference either way.)
+constexpr long long kSmallWaves = 2048;
+
 hipError_t launch_pool(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, hipStream_t s) {
   return launch_pool_reorder(q, Q, K, q_pool, k_pool, nullptr, nullptr, s);
 }
@@ -136,9 +204,27 @@ hipError_t launch_pool_reorder(const Geo& q, const void* Q, const void* K, float
   size_t es = q.dtype == DA_BF16 ? 2 : 4;
   int cpr = (int)(q.d * es / 16);
   long long items = (long long)q.B * q.H * q.g * cpr;
-  dim3 grid((unsigned)((items + kPoolThreads - 1) / kPoolThreads), 2);
   const bool re = Qp != nullptr || Kp != nullptr;
   const bool mx = q.pool == DA_POOL_MAX;
+  const bool cut = q.fw % q.pw != 0 || q.pw % 8 != 0;   // some patch rows are not a multiple of eight tokens
+  if (cut && 2 * items < 64 * kSmallWaves && q.block >= 64 && q.block <= 128 && q.in.sn < (1LL << 31)) {
+    const dim3 grid((unsigned)((2 * items + kPoolThreads - 1) / kPoolThreads), 2);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(kPoolThreads), 0, s, q, (const uint2*)Q, (const uint2*)K, q_pool, k_pool, (uint2*)Qp,
+                         (uint2*)Kp, 2 * cpr, 2 * items);
+    };
+    auto pick = [&](auto dt) {
+      constexpr int DT = decltype(dt)::value;
+      if (re && mx) go(pool_small_kernel<DT, true, true>);
+      else if (re) go(pool_small_kernel<DT, true, false>);
+      else if (mx) go(pool_small_kernel<DT, false, true>);
+      else go(pool_small_kernel<DT, false, false>);
+    };
+    if (q.dtype == DA_BF16) pick(std::integral_constant<int, DA_BF16>());
+    else pick(std::integral_constant<int, DA_F32>());
+    return hipGetLastError();
+  }
+  dim3 grid((unsigned)((items + kPoolThreads - 1) / kPoolThreads), 2);
 #define DA_POOL_LAUNCH(DT, RE, MX)                                                                                    \
   hipLaunchKernelGGL((pool_kernel<DT, RE, MX>), grid, dim3(kPoolThreads), 0, s, q, (const uint4*)Q, (const uint4*)K,  \
                      q_pool, k_pool, (uint4*)Qp, (uint4*)Kp, cpr, items)
