@@ -86,8 +86,8 @@ hipError_t launch_pool_reorder(const Geo& q, const void* Q, const void* K, float
                                void* Kp, hipStream_t s);
 hipError_t launch_draft_logits(const Geo& q, const float* q_pool, const float* k_pool, float* logits, hipStream_t s);
 hipError_t launch_row_softmax(const Geo& q, const float* logits, float* draft, hipStream_t s);
-// slack: kSelectSlack bytes behind `scores` may be read (their values are not used); without it the last few rows go
-// through a second launch that stays inside the array
+// slack: kSelectSlack bytes behind `scores` may be read (their values are not used); without it the last few rows stay
+// inside the array
 constexpr size_t kSelectSlack = 64 * 64 * sizeof(float);
 hipError_t launch_select(const Geo& q, const float* scores, int32_t* idx, uint8_t* mask, bool slack, hipStream_t s);
 hipError_t launch_all_lists(const Geo& q, int32_t* idx, int32_t* row_ptr, long long head_stride, hipStream_t s);

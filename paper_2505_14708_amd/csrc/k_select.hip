@@ -76,11 +76,11 @@ __global__ __launch_bounds__(64) void select_kernel(const float* __restrict__ sc
 
 
 // Keys in registers: KPL keys per lane, column of key i of lane l is l + 64 i.
-// READ_ON: a column past the end of the row may be read from the rows that follow (the launcher gives this
-// instantiation only rows for which that stays inside the array).
-template <int KPL, bool READ_ON>
+// A column past the end of the row may be read from the rows that follow in the first `read_on` rows (the launcher has
+// seen that this stays inside the array).
+template <int KPL>
 __global__ __launch_bounds__(64, KPL == 64 ? 4 : 1) void select_reg_kernel(const float* __restrict__ scores, int32_t* __restrict__ idx,
-                                                        uint8_t* __restrict__ mask, int g, int k) {
+                                                        uint8_t* __restrict__ mask, int g, int k, long long read_on) {
   const long long row = blockIdx.x;
   const int lane = threadIdx.x;
   const float* in = scores + row * g;
@@ -91,8 +91,17 @@ __global__ __launch_bounds__(64, KPL == 64 ? 4 : 1) void select_reg_kernel(const
     // base plus constants, two registers instead of two per load, and twice as many rows fit a SIMD.  The rows so
     // close to the end of the array that this would leave it read their last column instead.
     float x[KPL];
+    if (KPL == 64) {                                    // (both ways in one kernel: with a branch for each the registers run out)
+      const int last = row < read_on ? 64 * KPL - 1 : g - 1;
 #pragma unroll
-    for (int i = 0; i < KPL; ++i) x[i] = READ_ON ? in[lane + 64 * i] : in[min(lane + 64 * i, g - 1)];
+      for (int i = 0; i < KPL; ++i) x[i] = in[(unsigned)min(lane + 64 * i, last)];
+    } else if (row < read_on) {
+#pragma unroll
+      for (int i = 0; i < KPL; ++i) x[i] = in[lane + 64 * i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < KPL; ++i) x[i] = in[min(lane + 64 * i, g - 1)];
+    }
 #pragma unroll
     for (int i = 0; i < KPL; ++i)
       key[i] = lane + 64 * i < g ? order_key(x[i]) : 0u;   // a column past the end never counts: every trial value is > 0
@@ -166,14 +175,11 @@ static void launch_select_reg(const Geo& q, long long rows, const float* scores,
                               hipStream_t s) {
   // rows whose 64 * KPL columns starting at the row's first all lie inside the array: all but the last few, or all
   // of them when the caller vouches for kSelectSlack readable bytes behind the array
+  // (the last few are in the same launch: one of their own behind it cost 6.5 us however few they were)
   const long long spill = 64LL * KPL - q.g;           // columns read past the end of a row (>= 0)
   const long long last = spill > 0 && !slack ? (spill + q.g - 1) / q.g : 0;
   const long long head = rows > last ? rows - last : 0;
-  if (head > 0)
-    hipLaunchKernelGGL((select_reg_kernel<KPL, true>), dim3((unsigned)head), dim3(64), 0, s, scores, idx, mask, q.g, q.k);
-  if (rows > head)
-    hipLaunchKernelGGL((select_reg_kernel<KPL, false>), dim3((unsigned)(rows - head)), dim3(64), 0, s, scores + head * q.g,
-                       idx + head * q.k, mask ? mask + head * q.g : nullptr, q.g, q.k);
+  hipLaunchKernelGGL((select_reg_kernel<KPL>), dim3((unsigned)rows), dim3(64), 0, s, scores, idx, mask, q.g, q.k, head);
 }
 
 hipError_t launch_select(const Geo& q, const float* scores, int32_t* idx, uint8_t* mask, bool slack, hipStream_t s) {
