@@ -8,6 +8,7 @@
 // per head turns the counts into the row offsets (keys equal to the threshold are taken in row-major order
 // until the budget is used up; a row left empty keeps its best column), and every row writes its kept
 // columns in ascending order with an ordered ballot compaction.  Exact and deterministic.
+#include <algorithm>
 #include <mutex>
 #include "da_internal.h"
 
@@ -23,7 +24,11 @@ constexpr int kBins = 2048;
 constexpr int kHistThreads = 256;
 constexpr int kKeysPerThread = 16;                    // keys a thread of the histogram pass takes
 constexpr int kChunk = kHistThreads * kKeysPerThread;
-constexpr int kChunksPerGroup = 8;                    // chunks a workgroup takes before it adds its counts to the head's
+// Chunks a workgroup takes before it adds its counts to the head's: up to eight, as long as kHistGroups workgroups are
+// left (four per CU).  A chunk is two turns at memory and at the LDS counters, and with eight of them one after the other
+// in one workgroup per CU there is nothing to fill the waits: a pass over 8 maps of 1020 x 1020 28 -> 18 us.
+constexpr int kChunksPerGroup = 8;
+constexpr int kHistGroups = 1024;
 
 __device__ inline unsigned gkey(float x) {
   unsigned u = __float_as_uint(x);
@@ -55,10 +60,10 @@ __global__ void zero_words_kernel(unsigned* p, long long n) {
 }
 
 // hist[bh][pass][bin] += number of keys of head bh whose higher digits equal the state's prefix and whose
-// digit of this pass is `bin`.  One workgroup takes kChunk consecutive scores of one head.
+// digit of this pass is `bin`.  One workgroup takes per_group * kChunk consecutive scores of one head.
 template <int PASS>
 __global__ __launch_bounds__(kHistThreads) void hist_kernel(const float* __restrict__ scores, unsigned* __restrict__ hist,
-                                                           const SelState* __restrict__ state, long long g2) {
+                                                           const SelState* __restrict__ state, long long g2, int per_group) {
   constexpr int pass = PASS;
   __shared__ unsigned lh[kBins];
   const long long bh = blockIdx.y;
@@ -66,8 +71,8 @@ __global__ __launch_bounds__(kHistThreads) void hist_kernel(const float* __restr
   const unsigned want = pass == 0 ? 0u : above_of(state[bh].prefix, pass);
   __syncthreads();
   const float* in = scores + bh * g2;
-  for (int c = 0; c < kChunksPerGroup; ++c) {
-    const long long base = ((long long)blockIdx.x * kChunksPerGroup + c) * kChunk;
+  for (int c = 0; c < per_group; ++c) {
+    const long long base = ((long long)blockIdx.x * per_group + c) * kChunk;
     if (base >= g2) break;
     float x[kKeysPerThread];
 #pragma unroll
@@ -405,13 +410,14 @@ hipError_t launch_select_global(const Geo& q, long long budget, long long cap, c
   unsigned long long* eq_bits = (unsigned long long*)(base + off);
   const long long words = bh * 3 * kBins + bh * 2;     // the histograms and, right behind them, the search state
   hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, hist, words);
-  const long long per_group = (long long)kChunk * kChunksPerGroup;
-  const unsigned chunks = (unsigned)((g2 + per_group - 1) / per_group);
+  const long long all_chunks = (g2 + kChunk - 1) / kChunk;
+  const int per_group = (int)std::min<long long>(std::max<long long>(all_chunks * bh / kHistGroups, 1), kChunksPerGroup);
+  const unsigned chunks = (unsigned)((all_chunks + per_group - 1) / per_group);
   for (int pass = 0; pass < 3; ++pass) {
     const dim3 grid(chunks, (unsigned)bh);
-    if (pass == 0) hipLaunchKernelGGL(hist_kernel<0>, grid, dim3(kHistThreads), 0, s, scores, hist, state, g2);
-    if (pass == 1) hipLaunchKernelGGL(hist_kernel<1>, grid, dim3(kHistThreads), 0, s, scores, hist, state, g2);
-    if (pass == 2) hipLaunchKernelGGL(hist_kernel<2>, grid, dim3(kHistThreads), 0, s, scores, hist, state, g2);
+    if (pass == 0) hipLaunchKernelGGL(hist_kernel<0>, grid, dim3(kHistThreads), 0, s, scores, hist, state, g2, per_group);
+    if (pass == 1) hipLaunchKernelGGL(hist_kernel<1>, grid, dim3(kHistThreads), 0, s, scores, hist, state, g2, per_group);
+    if (pass == 2) hipLaunchKernelGGL(hist_kernel<2>, grid, dim3(kHistThreads), 0, s, scores, hist, state, g2, per_group);
     hipLaunchKernelGGL(resolve_kernel, dim3((unsigned)bh), dim3(256), 0, s, hist, state, pass, (unsigned)budget);
   }
   const unsigned rows = (unsigned)rows_n;
