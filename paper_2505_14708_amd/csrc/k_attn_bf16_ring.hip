@@ -89,6 +89,7 @@ constexpr int RING_BYTES = RING * SLOT;           // 128 KB
 constexpr int LDS_TOTAL = 160 * 1024;
 constexpr int AUX_BYTES = LDS_TOTAL - RING_BYTES; // bitmaps + union list + ring state
 constexpr int WAVES = 8;
+constexpr int NQ = 2;                             // tiles of 32 queries per wave
 constexpr int O_STRIDE = D * 2 + 16;              // padded row stride of the output staging area
 constexpr float kScale = 0.08838834764831845f;                      // 1/sqrt(128)
 constexpr float kC2 = 0.08838834764831845f * 1.4426950408889634f;   // log2(e)/sqrt(128)
@@ -174,21 +175,16 @@ __device__ __forceinline__ float sum_across_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// exp / sum / pack of 8 scores (registers o .. o+7 of an accumulator tile) into one P operand
-__device__ __forceinline__ bf16x8 exp_pack(const f32x16& s, int o, float mc, float& lsum) {
+// exp / sum / pack of two scores (registers o, o + 1 of an accumulator tile) into elements e, e + 1 of a P operand
+__device__ __forceinline__ void exp_pair(const f32x16& s, int o, float mc, float& lsum, bf16x8& p, int e) {
   const bf16x2 kOnes = {(__bf16)1.0f, (__bf16)1.0f};
-  bf16x8 p;
-#pragma unroll
-  for (int i = 0; i < 8; i += 2) {
-    float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[o + i], kC2, -mc));
-    float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[o + i + 1], kC2, -mc));
-    f32x2 pp = {p0, p1};
-    bf16x2 pb = __builtin_convertvector(pp, bf16x2);
-    lsum = __builtin_amdgcn_fdot2_f32_bf16(pb, kOnes, lsum, false);   // the sum of what the second product sees
-    p[i] = pb[0];
-    p[i + 1] = pb[1];
-  }
-  return p;
+  float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[o], kC2, -mc));
+  float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[o + 1], kC2, -mc));
+  f32x2 pp = {p0, p1};
+  bf16x2 pb = __builtin_convertvector(pp, bf16x2);
+  lsum = __builtin_amdgcn_fdot2_f32_bf16(pb, kOnes, lsum, false);   // the sum of what the second product sees
+  p[e] = pb[0];
+  p[e + 1] = pb[1];
 }
 
 // pad keys out of the softmax: accumulator register i is key 16(i>>3) + 8hh + (i&7) of the half tile, nv of its keys are valid
@@ -232,7 +228,6 @@ __device__ __forceinline__ bf16x8 load_operand(__amdgpu_buffer_rsrc_t base, unsi
 
 // The scores of 32 keys against the wave's queries, S^T = K Q^T.  kaddr: this lane's LDS address of the operand of k-step
 // 0; the swizzle puts that of step t at kaddr ^ 32t.
-template <int NQ>
 __device__ __forceinline__ void half_scores(unsigned kaddr, int nv, const bf16x8 (&qf)[2][8], f32x16 (&s)[NQ]) {
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   constexpr int AHEAD = 3;                            // operands on their way from LDS
@@ -253,14 +248,12 @@ __device__ __forceinline__ void half_scores(unsigned kaddr, int nv, const bf16x8
   }
 }
 
-// 32 keys (half a tile) for one wave: 64 queries, or the first 32 of them (NQ = 1: the others are pad slots).  v: the
-// half tile's V^T in global memory (operand order: the 64 lanes' operands of (k-step t, channel group dt) are the
-// contiguous KB number 4t + dt, so every load of a wave is one contiguous KB).
-template <int NQ>
+// 32 keys (half a tile) for one wave.  v: the half tile's V^T in global memory (operand order: the 64 lanes' operands of
+// (k-step t, channel group dt) are the contiguous KB number 4t + dt, so every load of a wave is one contiguous KB).
 __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v, int nv, float skip,
                                           const bf16x8 (&qf)[2][8], f32x16 (&o)[2][4], Soft (&st)[2], int& kept) {
   f32x16 s[NQ];
-  half_scores<NQ>(kaddr, nv, qf, s);
+  half_scores(kaddr, nv, qf, s);
   // online softmax over the 32 keys
   float mx[NQ];
   bool negligible = true;
@@ -277,6 +270,7 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   // product are skipped.  (Never the first time: top is -inf.)  Pad query slots have no say (their top is
   // +inf): their rows are zero, every score is 0, and nobody reads their output.
   if (__all(negligible)) return;
+  __builtin_amdgcn_s_setprio(1);
   asm volatile("s_mov_b32 %0, 1" : "=s"(kept));   // (a scalar, whatever the compiler thinks)
   // V^T operands: the first three on their way while the exponentials are computed, one more whenever registers fall
   // free.  (Operand 4t + dt belongs to k-step t and channel group dt.)
@@ -310,26 +304,36 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   bf16x8 p[NQ];
 #pragma unroll
   for (int h = 0; h < NQ; ++h) {
-    p[h] = exp_pack(s[h], 0, st[h].m * kC2, st[h].l);
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) exp_pair(s[h], i, st[h].m * kC2, st[h].l, p[h], i);
     __builtin_amdgcn_sched_barrier(0);
     fetch(3 + h);
     __builtin_amdgcn_sched_barrier(0);
   }
-  // O^T += V^T P^T
+  // O^T += V^T P^T.  The second half of the probabilities is made between the first half's matrix instructions, a pair
+  // after each: the wave has vector work while the pipe is busy and need not find a partner that has.  Together with the
+  // raised priority (from here to the end of the tile a wave is in the way of nobody who waits for V or a tile; by itself
+  // worth 0.5 to 1 %, the order by itself nothing), nothing dropped: 24 heads x 1980 blocks 21.1 -> 20.9 ms, 8x16 windows
+  // 20.2 -> 19.6 ms, 5 heads x 1260 blocks 4.79 -> 4.66 ms, dense 480p 2.00 -> 1.94 ms; peaked 720p 12.85 -> 12.91 ms
+  // (two runs of one side differ by as much), 480p 3.00 -> 2.95 ms.
+  bf16x8 p2[NQ];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) {
 #pragma unroll
-    for (int h = 0; h < NQ; ++h) o[h][dt] = mfma(va[dt], p[h], o[h][dt]);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int h = 0; h < NQ; ++h) {
+      o[h][dt] = mfma(va[dt], p[h], o[h][dt]);
+      __builtin_amdgcn_sched_barrier(0);
+      exp_pair(s[h], 8 + 2 * dt, st[h].m * kC2, st[h].l, p2[h], 2 * dt);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if (3 + NQ + dt < 8) fetch(3 + NQ + dt);
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
-  for (int h = 0; h < NQ; ++h) p[h] = exp_pack(s[h], 8, st[h].m * kC2, st[h].l);
-#pragma unroll
   for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-    for (int h = 0; h < NQ; ++h) o[h][dt] = mfma(va[4 + dt], p[h], o[h][dt]);
+    for (int h = 0; h < NQ; ++h) o[h][dt] = mfma(va[4 + dt], p2[h], o[h][dt]);
+  __builtin_amdgcn_s_setprio(0);
 }
 
 // How the frames that do not fill a group of `fg` are spread over workgroups.
@@ -802,7 +806,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 #pragma unroll 1
       for (int half = 0; half < 2 && 32 * half < nv; ++half) {
         f32x16 s[2];
-        half_scores<2>(kbase + (unsigned)(u & (RING - 1)) * SLOT + half * (SLOT / 2), nv - 32 * half, qf, s);
+        half_scores(kbase + (unsigned)(u & (RING - 1)) * SLOT + half * (SLOT / 2), nv - 32 * half, qf, s);
 #pragma unroll
         for (int h = 0; h < 2; ++h) st[h].top = fmaxf(st[h].top, max_across_halves(max16(s[h], -INFINITY)));
       }
@@ -835,7 +839,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
       int kept = 0;
 #pragma unroll 1
       for (int half = 0; half < 2 && 32 * half < nv; ++half) {
-        half_tile<2>(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, qf, o, st, kept);
+        half_tile(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, qf, o, st, kept);
       }
       tiles_seen += 1;
       tiles_kept += kept;
