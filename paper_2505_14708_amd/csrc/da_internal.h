@@ -26,9 +26,9 @@ struct Geo {
   int reordered;
 };
 
-// element offset of row `row` of (batch, head) number bh
+// element offset of row `row` of (batch, head) number bh (B * H is below 2^31: a 32-bit division, a fifth of a 64-bit one)
 __host__ __device__ inline long long row_offset(const Rows& r, int H, long long bh, long long row) {
-  const long long b = bh / H, h = bh - b * H;
+  const unsigned b = (unsigned)bh / (unsigned)H, h = (unsigned)bh - b * (unsigned)H;
   return b * r.sb + h * r.sh + row * r.sn;
 }
 

@@ -450,8 +450,15 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     skip = log2f((float)max(k, 1) * (float)BLOCK) + kDropLog2;
   }
 
+  // The first 256 entries of the lists are asked for before anything else: everything up to the walk waits for them.
+  const bool lister = live && part == 0 && (qsub == 0 || groups == 1); // the wave that brings in the list of its query block
+  int pre[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) pre[i] = lister && lane + 64 * i < k ? list[lane + 64 * i] : -1;
+  __builtin_amdgcn_sched_barrier(0);
+
   // Q fragments (B operand): lane (query r, half-wave hh) holds d = 16t + 8hh .. +7.  Asked for
-  // first, so that they arrive while the lists are being merged.
+  // next, so that they arrive while the lists are being merged.
   // With `direct`, Qp and Op are the caller's Q and O (q.in, q.out: in the original token order as a rule): the
   // reordering of Q and the restoring of O (Algorithms 1 and 2) are then this kernel's addressing, slot -> row.
   const BlockPos qpos = block_pos(q, has_block ? my_block : 0);
@@ -490,12 +497,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   int* next_load = ctrl + 16;
   int* count = ctrl + 17;                             // [2]
 
-  // ---- union of the workgroup's lists (the first 256 entries of a list are asked for before the
-  // bitmaps are cleared, so that the two latencies overlap)
-  const bool lister = live && part == 0 && (qsub == 0 || groups == 1); // the wave that brings in the list of its query block
-  int pre[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) pre[i] = lister && lane + 64 * i < k ? list[lane + 64 * i] : -1;
+  // ---- union of the workgroup's lists
   for (int i = threadIdx.x; i < 4 * bw; i += 512) bitmap[i] = 0u;
   if (threadIdx.x < 32) ctrl[threadIdx.x] = threadIdx.x < RING ? -1 : 0;
   __syncthreads();

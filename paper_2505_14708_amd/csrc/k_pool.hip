@@ -142,14 +142,14 @@ __global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, cons
                                                                      long long items) {
   constexpr int N = Vec<DT>::N / 2;
   constexpr int AHEAD = 64;
-  const long long item = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const unsigned item = blockIdx.x * kPoolThreads + threadIdx.x;   // (few: 32 bits hold them, and 64-bit divisions are five times as long)
   if (item >= items) return;
   const uint2* X = blockIdx.y ? K : Q;
   float* out = blockIdx.y ? k_pool : q_pool;
-  const long long blk = item / cpr;   // over bh * g
-  const int c = (int)(item - blk * cpr);
-  const long long bh = blk / q.g;
-  const int i = (int)(blk - bh * q.g);
+  const unsigned in_head = item / (unsigned)cpr;   // over bh * g
+  const int c = (int)(item - in_head * (unsigned)cpr);
+  const long long blk = in_head, bh = in_head / (unsigned)q.g;
+  const int i = (int)(in_head - (unsigned)bh * (unsigned)q.g);
   const BlockPos b = block_pos(q, i);
   const int nv = b.vh * b.vw;
   const unsigned sn = (unsigned)(q.in.sn / N);                            // pieces between consecutive rows of the source (the launcher has seen that it fits)
