@@ -19,6 +19,7 @@
 // 21 blocks kept, 17.7 -> 12.2 us at 8 blocks x 2 heads, d = 64, 4 kept; da_forward with 24 heads 862 -> 769 us (116
 // TFLOP/s of the 130 that a bare loop of float32 matrix instructions reaches).  Eight waves per workgroup instead of four
 // gain nothing on the small ones and lose 20 % on the large ones, where two workgroups per CU hide each other's ends.
+#include <float.h>
 #include <math.h>
 #include "da_internal.h"
 
@@ -90,7 +91,6 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
   for (int h = 0; h < 2; ++h) {
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) o[h][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m[h] = -INFINITY;
     l[h] = 0.f;
   }
 
@@ -171,6 +171,10 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
     }
   };
   bool more = advance();
+  // The reference of a wave that has keys starts at the lowest finite value, not at minus infinity: all scores of its first
+  // steps may be minus infinity (finite operands whose product leaves the range), and those keys weigh exp2(-inf) = 0,
+  // not exp2(-inf + inf).
+  m[0] = m[1] = more ? -FLT_MAX : -INFINITY;
   if (more) fetch_k();
   while (more) {
     fetch_v();
@@ -200,7 +204,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
     __builtin_amdgcn_sched_barrier(0);
     float mx[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) mx[h] = query_max(fmaxf(fmaxf(s[h][0], s[h][1]), fmaxf(s[h][2], s[h][3])));   // finite: the step's first slot is valid
+    for (int h = 0; h < 2; ++h) mx[h] = query_max(fmaxf(fmaxf(s[h][0], s[h][1]), fmaxf(s[h][2], s[h][3])));
     if (__any(mx[0] > m[0] || mx[1] > m[1])) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -264,7 +268,8 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
     a[w] = ml.y > 0.f ? exp2f((ml.x - m_all) * scale_log2) : 0.f;
     l_all += ml.y * a[w];
   }
-  const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;        // an empty list: zero rows
+  // an empty list: zero rows; keys that all score minus infinity (or NaN): no softmax is defined, NaN
+  const float inv = l_all > 0.f ? 1.0f / l_all : m_all == -INFINITY ? 0.f : NAN;
   const int slot = 32 * half + 16 * h + r16;
   if (slot >= q_valid) return;
   float* orow = O + row_offset(q.out, q.H, bh, query_row(slot)) + (D / 4) * kk;
