@@ -63,6 +63,7 @@
 // The running max only moves (and O is rescaled) when a row max exceeds it by more than 2^8 in
 // the exponent's units; until then probabilities are formed against the stale max, which is
 // exact after the final division because numerator and denominator share it.
+#include <float.h>
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -212,7 +213,10 @@ __device__ __forceinline__ int valid_slots(const Geo& q, int per_frame, int j) {
 }
 
 struct Soft {
-  float m;     // reference max (raw score units); -inf before the first tile
+  // Reference max (raw score units).  Before the first tile the lowest finite value and not minus infinity: all scores of a
+  // half tile may be minus infinity (finite operands whose product leaves the range), and those keys weigh exp2(-inf) = 0,
+  // not exp2(-inf + inf).
+  float m;
   float top;   // largest score seen so far (the reference trails it by at most kLazy powers of two); +inf for a pad query
   float l;     // this lane's partial sum of probabilities
 };
@@ -259,7 +263,7 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   bool negligible = true;
 #pragma unroll
   for (int h = 0; h < NQ; ++h) {
-    mx[h] = max_across_halves(max16(s[h], -INFINITY));   // finite: the half tile's first slot is valid
+    mx[h] = max_across_halves(max16(s[h], -INFINITY));
     negligible = negligible && (mx[h] - st[h].top) * kC2 < -skip;
   }
   // A key whose score is more than `skip` powers of two below the query's best score so far
@@ -267,7 +271,7 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   // skip = log2(keys in the row) + kDropLog2, so whatever is dropped from a row adds up to less
   // than 2^-kDropLog2 of that term: below the resolution of a bf16 result at any sequence length.
   // When all 32 keys are that small for every query, the exponentials and the second
-  // product are skipped.  (Never the first time: top is -inf.)  Pad query slots have no say (their top is
+  // product are skipped.  (Never while top is -inf, unless all 32 scores are.)  Pad query slots have no say (their top is
   // +inf): their rows are zero, every score is 0, and nobody reads their output.
   if (__all(negligible)) return;
   __builtin_amdgcn_s_setprio(1);
@@ -737,7 +741,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[h][dt][i] = nought;
-    st[h].m = -INFINITY;
+    st[h].m = -FLT_MAX;
     st[h].top = 32 * h + (lane & 31) < q_valid ? -INFINITY : INFINITY;
     st[h].l = nought;
   }
@@ -944,7 +948,8 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     const float a_mine = l_mine > 0.f ? __builtin_amdgcn_exp2f((sx.m - m_all) * kC2) : 0.f;
     const float a_other = other.y > 0.f ? __builtin_amdgcn_exp2f((other.x - m_all) * kC2) : 0.f;
     const float lt = l_mine * a_mine + other.y * a_other;
-    const float inv = lt > 0.f ? 1.0f / lt : 0.f;     // 0 only in pad query slots whose waves skipped every tile, and for an empty list
+    const float inv = lt > 0.f ? 1.0f / lt : 0.f;     // 0 only in pad query slots whose waves skipped every tile, for an empty list and
+    const bool none = lt == 0.f && before > 0 && 32 * part + r < q_valid;   // for keys that all score minus infinity: no softmax is defined, NaN
     if (lse && hh == 0) lse[qb * BLOCK + BS * qsub + 32 * part + r] = m_all * kScale + __logf(lt);
     const float f_mine = a_mine * inv, f_other = a_other * inv;
     uint2 w2[4][4];
@@ -958,7 +963,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         f32x2 v1 = {x[dt][4 * a + 2] * f_mine + y.z * f_other, x[dt][4 * a + 3] * f_mine + y.w * f_other};
         bf16x2 b0 = __builtin_convertvector(v0, bf16x2);
         bf16x2 b1 = __builtin_convertvector(v1, bf16x2);
-        w2[dt][a] = failed ? make_uint2(0x7fc07fc0u, 0x7fc07fc0u) : make_uint2(*(unsigned*)&b0, *(unsigned*)&b1);
+        w2[dt][a] = failed || none ? make_uint2(0x7fc07fc0u, 0x7fc07fc0u) : make_uint2(*(unsigned*)&b0, *(unsigned*)&b1);
       }
     // (all of the partner's share has been read: its place serves to turn the rows)
 #pragma unroll

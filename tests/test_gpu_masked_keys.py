@@ -25,7 +25,9 @@ PATTERNS = {
 
 
 @pytest.mark.parametrize("pattern", list(PATTERNS))
-@pytest.mark.parametrize("dtype,H,T,pw,keep", [(W.F32, 1, 4, 8, 10 ** 6), (W.F32, 1, 4, 8, 3)])
+@pytest.mark.parametrize("dtype,H,T,pw,keep", [(W.F32, 1, 4, 8, 10 ** 6), (W.F32, 1, 4, 8, 3), (W.BF16, 1, 4, 8, 10 ** 6),
+                                               (W.BF16, 1, 4, 8, 3), (W.BF16, 1, 18, 8, 10 ** 6), (W.BF16, 1, 4, 16, 10 ** 6),
+                                               (W.BF16, 1, 66, 8, 40), (W.BF16, 2, 66, 8, 3)])
 def test_masked_keys(dtype, H, T, pw, keep, pattern):
     import torch
     w = W.Workload("masked", B=1, H=H, d=128, T=T, fh=16, fw=32 if pw == 16 else 16, pw=pw, dtype=dtype, seed=T)
@@ -71,7 +73,7 @@ def test_masked_keys(dtype, H, T, pw, keep, pattern):
     assert da.da_wait_failures() == 0
 
 
-@pytest.mark.parametrize("dtype", [W.F32])
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
 def test_nothing_but_masked_keys(dtype):
     """Rows whose keys all score minus infinity have no softmax and stay NaN; rows without any key at all are zero."""
     import torch
