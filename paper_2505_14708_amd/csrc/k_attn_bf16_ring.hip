@@ -67,6 +67,7 @@
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
+#include <type_traits>
 #include "da_internal.h"
 
 namespace da {
@@ -90,7 +91,6 @@ constexpr int RING_BYTES = RING * SLOT;           // 128 KB
 constexpr int LDS_TOTAL = 160 * 1024;
 constexpr int AUX_BYTES = LDS_TOTAL - RING_BYTES; // bitmaps + union list + ring state
 constexpr int WAVES = 8;
-constexpr int NQ = 2;                             // tiles of 32 queries per wave
 constexpr int O_STRIDE = D * 2 + 16;              // padded row stride of the output staging area
 constexpr float kScale = 0.08838834764831845f;                      // 1/sqrt(128)
 constexpr float kC2 = 0.08838834764831845f * 1.4426950408889634f;   // log2(e)/sqrt(128)
@@ -230,8 +230,11 @@ __device__ __forceinline__ bf16x8 load_operand(__amdgpu_buffer_rsrc_t base, unsi
   return __builtin_bit_cast(bf16x8, x);
 }
 
+// NQ: how many of the wave's two tiles of 32 queries are worked on (1 where the second holds nothing but pad slots)
+
 // The scores of 32 keys against the wave's queries, S^T = K Q^T.  kaddr: this lane's LDS address of the operand of k-step
 // 0; the swizzle puts that of step t at kaddr ^ 32t.
+template <int NQ>
 __device__ __forceinline__ void half_scores(unsigned kaddr, int nv, const bf16x8 (&qf)[2][8], f32x16 (&s)[NQ]) {
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   constexpr int AHEAD = 3;                            // operands on their way from LDS
@@ -254,10 +257,11 @@ __device__ __forceinline__ void half_scores(unsigned kaddr, int nv, const bf16x8
 
 // 32 keys (half a tile) for one wave.  v: the half tile's V^T in global memory (operand order: the 64 lanes' operands of
 // (k-step t, channel group dt) are the contiguous KB number 4t + dt, so every load of a wave is one contiguous KB).
+template <int NQ>
 __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v, int nv, float skip,
                                           const bf16x8 (&qf)[2][8], f32x16 (&o)[2][4], Soft (&st)[2], int& kept) {
   f32x16 s[NQ];
-  half_scores(kaddr, nv, qf, s);
+  half_scores<NQ>(kaddr, nv, qf, s);
   // online softmax over the 32 keys
   float mx[NQ];
   bool negligible = true;
@@ -804,60 +808,77 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   };
   const bool two = q_valid > 32;                      // else the second 32 queries are all pad slots
   int tiles_seen = 0, tiles_kept = 0;                 // (scalar registers; reported when the caller asks for the counts)
-  if (live && part > 0 && first_of[group] >= 0) {
-    const int u = first_of[group];
-    gave_up = !arrived(u);
-    if (!gave_up) {
-      const int nv = (int)((__builtin_amdgcn_readfirstlane((int)ulist[u]) >> 22) & 63) + 1;
-#pragma unroll 1
-      for (int half = 0; half < 2 && 32 * half < nv; ++half) {
-        f32x16 s[2];
-        half_scores(kbase + (unsigned)(u & (RING - 1)) * SLOT + half * (SLOT / 2), nv - 32 * half, qf, s);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) st[h].top = fmaxf(st[h].top, max_across_halves(max16(s[h], -INFINITY)));
-      }
-      leave(u);
-    }
-  }
-  // The walk, 64 entries at a time: lane i holds entry base + i, a ballot tells which of them are my group's, a second
-  // one which of those are mine (every other one, or fourth, or eighth).  Entries that are not mine cost nothing.
   int before = 0;                                     // entries of my group in the chunks before
-  for (int base = 0; base < nU && !gave_up; base += 64) {
-    const int at = base + opaque_lane();
-    const unsigned e_lane = ulist[min(at, nU - 1)];
-    const bool is_ours = at < nU && (e_lane & my_bit) != 0u;
-    const unsigned long long ours = __ballot(is_ours);
-    unsigned long long mine = __ballot(is_ours && ((before + lanes_before(ours)) & (parts - 1)) == part);
-    before += __popcll(ours);
-    while (mine) {
-      const int i = (int)__builtin_ctzll(mine);
-      mine &= mine - 1;
-      const int u = base + i;
-      if (!arrived(u)) {
-        gave_up = true;
-        break;
-      }
-      snap = look();                                  // asked for now, used after the tile: its latency hides behind the tile
-      const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)e_lane, i);
-      const int nv = (int)((e >> 22) & 63u) + 1;
-      const unsigned kaddr = kbase + (unsigned)(u & (RING - 1)) * SLOT;
-      const unsigned char* v = Vbh + (long long)(e & 0x3fffffu) * V_TILE;
-      int kept = 0;
+  auto walk = [&](auto queries) {
+    constexpr int NQ = decltype(queries)::value;
+    if (live && part > 0 && first_of[group] >= 0) {
+      const int u = first_of[group];
+      gave_up = !arrived(u);
+      if (!gave_up) {
+        const int nv = (int)((__builtin_amdgcn_readfirstlane((int)ulist[u]) >> 22) & 63) + 1;
 #pragma unroll 1
-      for (int half = 0; half < 2 && 32 * half < nv; ++half) {
-        half_tile(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, qf, o, st, kept);
+        for (int half = 0; half < 2 && 32 * half < nv; ++half) {
+          f32x16 s[NQ];
+          half_scores<NQ>(kbase + (unsigned)(u & (RING - 1)) * SLOT + half * (SLOT / 2), nv - 32 * half, qf, s);
+#pragma unroll
+          for (int h = 0; h < NQ; ++h) st[h].top = fmaxf(st[h].top, max_across_halves(max16(s[h], -INFINITY)));
+        }
+        leave(u);
       }
-      tiles_seen += 1;
-      tiles_kept += kept;
-      leave(u);
-      // (Only waves that are waiting for a tile ask for tiles: having every wave look for room after each of
-      // its tiles cost the busy ones more than the earlier requests saved.)
     }
+    // The walk, 64 entries at a time: lane i holds entry base + i, a ballot tells which of them are my group's, a second
+    // one which of those are mine (every other one, or fourth, or eighth).  Entries that are not mine cost nothing.
+    for (int base = 0; base < nU && !gave_up; base += 64) {
+      const int at = base + opaque_lane();
+      const unsigned e_lane = ulist[min(at, nU - 1)];
+      const bool is_ours = at < nU && (e_lane & my_bit) != 0u;
+      const unsigned long long ours = __ballot(is_ours);
+      unsigned long long mine = __ballot(is_ours && ((before + lanes_before(ours)) & (parts - 1)) == part);
+      before += __popcll(ours);
+      while (mine) {
+        const int i = (int)__builtin_ctzll(mine);
+        mine &= mine - 1;
+        const int u = base + i;
+        if (!arrived(u)) {
+          gave_up = true;
+          break;
+        }
+        snap = look();                                // asked for now, used after the tile: its latency hides behind the tile
+        const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)e_lane, i);
+        const int nv = (int)((e >> 22) & 63u) + 1;
+        const unsigned kaddr = kbase + (unsigned)(u & (RING - 1)) * SLOT;
+        const unsigned char* v = Vbh + (long long)(e & 0x3fffffu) * V_TILE;
+        int kept = 0;
+#pragma unroll 1
+        for (int half = 0; half < 2 && 32 * half < nv; ++half) {
+          half_tile<NQ>(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, qf, o, st, kept);
+        }
+        tiles_seen += NQ;
+        tiles_kept += NQ * kept;
+        leave(u);
+        // (Only waves that are waiting for a tile ask for tiles: having every wave look for room after each of
+        // its tiles cost the busy ones more than the earlier requests saved.)
+      }
+    }
+  };
+  // A wave whose second 32 queries are all pad slots (one block in seven on a 30x52 grid) leaves them out.  Measured against
+  // working on them: 30x52 with 21 frames, 24 heads 2.87 -> 2.82 ms, 9 frames, 8 heads 380 -> 365 us, matrix instructions 7.53e7
+  // -> 7.04e7 and, dense with 3 heads, 6.17e7 -> 5.73e7 (its time, 1.91 ms, stays: other workgroups set it).  One loop for
+  // each: as a branch around the tile, in one loop, the two leave the registers in different places and 150 of them go
+  // through memory.
+  if (two) {
+    walk(std::integral_constant<int, 2>());
+  } else {
+    walk(std::integral_constant<int, 1>());
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[1][dt][i] = nought;    // (not kept through the loop)
   }
   publish();
   if (tile_counts != nullptr && lane == 0 && tiles_seen) {
-    atomicAdd(&tile_counts[0], (unsigned long long)(two ? 2 * tiles_seen : tiles_seen));
-    atomicAdd(&tile_counts[1], (unsigned long long)(two ? 2 * tiles_kept : tiles_kept));
+    atomicAdd(&tile_counts[0], (unsigned long long)tiles_seen);
+    atomicAdd(&tile_counts[1], (unsigned long long)tiles_kept);
   }
   if (gave_up && lane == 0) {
     atomicAdd(&g_wait_failures, 1ull);
