@@ -1,0 +1,56 @@
+"""The rounding of the bf16 attention against the plain evaluation at the same precision: scores and sums exact, probabilities
+taken relative to the row's largest score and rounded to bf16, normalised by the sum of what was rounded, outputs rounded to
+bf16.  The kernel keeps a reference per wave and lets it trail, so its probabilities round elsewhere; its error against
+float64 (2-norm over all heads) is to be no larger than the plain evaluation's.  Short lists, shared out among up to eight
+waves, where a wave's first tile is most of what it sees."""
+import numpy as np
+import pytest
+
+from oracle import draft_attention as oa
+from paper_2505_14708_amd import binding as da
+from paper_2505_14708_amd import workloads as W
+from gpu_util import HeadRef, empty, say, to_dev, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+
+def _round(x):
+    return W.storage_to_f64(W.f32_to_bf16_bits(x.astype(np.float32)), W.BF16)
+
+
+def _plain(ref):
+    qp, kp, vp = (ref.permuted64(x) for x in "qkv")
+    block, valid = ref.block, (ref.perm >= 0).reshape(-1, ref.block)
+    out = np.zeros_like(qp)
+    for i, kept in enumerate(ref.idx):
+        keys = np.concatenate([j * block + np.nonzero(valid[j])[0] for j in kept])
+        S = qp[i * block:(i + 1) * block] @ kp[keys].T / np.sqrt(qp.shape[1])
+        P = _round(np.exp(S - S.max(axis=1, keepdims=True)))
+        out[i * block:(i + 1) * block] = _round((P @ vp[keys]) / P.sum(axis=1, keepdims=True))
+    return out
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+@pytest.mark.parametrize("T,fh,fw,pw,H,keep,gain", [(1, 30, 52, 8, 2, 14, 0.25), (1, 30, 52, 8, 2, 14, 0.03125), (1, 13, 63, 8, 4, 4, 0.25),
+                                                    (2, 46, 30, 8, 2, 12, 0.25), (2, 30, 41, 16, 2, 6, 0.25)])
+def test_error_against_float64(T, fh, fw, pw, H, keep, gain, seed):
+    import torch
+    w = W.Workload("precision", B=1, H=H, d=128, T=T, fh=fh, fw=fw, pw=pw, seed=seed)
+    say(f"precision {T}x{fh}x{fw} window 8x{pw} heads {H} keep {keep} gain {gain} seed {seed}")
+    Q, K, V = W.make_qkv(w)
+    Q = W.to_storage(W.storage_to_f64(Q, w.dtype) * gain, w.dtype)
+    p = da.problem(1, H, T, fh, fw, 128, 8, pw, keep_blocks=keep)
+    dims = da.da_derive(p)
+    O = empty((1, H, dims.n, 128), w.dtype)
+    ws = torch.empty(da.da_workspace_size(p), dtype=torch.uint8, device="cuda")
+    da.da_forward(p, *(to_dev(x, w.dtype) for x in (Q, K, V)), O, ws)
+    torch.cuda.synchronize()
+    got = to_host_f64(O, w.dtype)[0]
+    kernel = plain = 0.0
+    for h in range(H):
+        ref = HeadRef(w, Q[0, h], K[0, h], V[0, h], keep_blocks=keep)
+        want = oa.restore(ref.attention(), ref.inv)
+        kernel += ((got[h] - want) ** 2).sum()
+        plain += ((oa.restore(_plain(ref), ref.inv) - want) ** 2).sum()
+    say(f"  error over the plain evaluation's: {(kernel / plain) ** 0.5:.4f}")
+    assert kernel <= plain
