@@ -14,10 +14,13 @@ heads of 128, 8x8 pooling, 90 % sparsity, bf16.  Prints ONE JSON line.
                  frac           EFFECTIVE flop 4*N*N*d*H*(k/g) / launch time / peak, for the launch
                                 da_forward makes (queries read, outputs written in the original
                                 token order): the figure the build target names;
-                 executed.frac  flop of the matrix instructions the kernel actually issued (it counts
-                                its tiles: da_sparse_attn_ex) / the same time / peak.  Padding adds
+                 executed.frac  flop of the matrix instructions the kernel issued, from its own tile
+                                counts (da_sparse_attn_ex) / the same time / peak.  Padding adds
                                 work, the kernel's drop rule takes work away; on these peaked
-                                synthetic inputs it takes away a lot;
+                                synthetic inputs it takes away a lot.  (Tiles of at most 32 valid keys
+                                are half the work: the first product's are counted from the lists, the
+                                second product's taken to be dropped as often as the others.  The one
+                                look per list that further waves take at its first tile is left out);
                  no_drop.frac   the same launch, same block lists, with Q scaled by 2^-5 so that the
                                 scores of a row lie close together and nothing is dropped: what the
                                 kernel does on inputs whose attention is not peaked.
@@ -237,7 +240,13 @@ def main():
             da.da_sparse_attn_ex(p, q_in, Kp, Vt, idx, O, None, 1, counts)
             torch.cuda.synchronize()
             seen, kept = (int(x) for x in counts.cpu().numpy())
-            return seen, kept, 16.0 * (seen + kept) * FLOP_PER_MFMA
+            return seen, kept, (16.0 - 8.0 * short / seen) * (seen + kept) * FLOP_PER_MFMA
+
+        # how many of the tiles have at most 32 valid keys (a tile is 32 queries x 64 slots of a kept key block)
+        valid = torch.empty(g, dtype=torch.int32, device="cuda")
+        da.da_build_perm(p, None, None, valid)
+        is_short = (valid - 1) % 64 < 32
+        short = int((is_short[idx.view(w.B * w.H, g, k).long()].sum(2) * ((valid + 31) // 32)).sum())
 
         direct = lambda: da.da_sparse_attn_ex(p, dQ, Kp, Vt, idx, O, None, 1, None)
         timed(direct, args.warmup)

@@ -171,11 +171,13 @@ int da_sparse_attn(const da_problem* p, const void* Qp, const void* Kp, const vo
  * original_order = 1 (DA_BF16 only): Q and O are the caller's [B,H,N,d] tensors in the ORIGINAL token order; the
  *   kernel reads each query row from, and writes each output row to, its original place, which is what da_forward
  *   does (Kp and Vt are still the reordered tensors; lse, if given, stays in slot order).  0: as da_sparse_attn.
- * tile_counts (DEVICE, two uint64, may be NULL; DA_BF16 only): the kernel ADDS to [0] the number of tiles
- *   (32 queries x 64 keys) its waves went through and to [1] the number of those of which any 32 keys' exponentials
- *   and second product were carried out (the others fell to the drop rule described above).  The caller clears it.
- *   Each tile is 16 matrix instructions for the first product and, if carried out, up to 16 for the second (half of
- *   either for a key block of at most 32 valid slots).
+ * tile_counts (DEVICE, two uint64, may be NULL; DA_BF16 only): the kernel ADDS to [0] the number of tiles (32 queries x
+ *   64 keys) its waves went through and to [1] how many tiles' worth of exponentials and second product were carried out:
+ *   a tile whose 32 first or last keys fell to the drop rule described above counts half (rounded to whole tiles per
+ *   wavefront where only 32 queries are valid).  The caller clears it.  Each tile is 16 matrix instructions for the first
+ *   product and, in [1], 16 for the second; 8 and 8 for a key block (or the second half of one of 128 slots) of at most 32
+ *   valid slots, which counts as one tile all the same.  Not counted: a list's first tile is looked at by each of the waves
+ *   that share the list (16 instructions more for each but one of them) where it has at least eight tiles per wave.
  */
 int da_sparse_attn_ex(const da_problem* p, const void* Q, const void* Kp, const void* Vt, const int32_t* idx, void* O,
                       float* lse, int original_order, uint64_t* tile_counts, void* stream);

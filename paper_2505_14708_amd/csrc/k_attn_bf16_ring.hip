@@ -280,7 +280,7 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   // +inf): their rows are zero, every score is 0, and nobody reads their output.
   if (__all(negligible)) return;
   __builtin_amdgcn_s_setprio(1);
-  asm volatile("s_mov_b32 %0, 1" : "=s"(kept));   // (a scalar, whatever the compiler thinks)
+  asm volatile("s_add_u32 %0, %0, 1" : "+s"(kept) : : "scc");   // (a scalar, whatever the compiler thinks)
   // V^T operands: the first three on their way while the exponentials are computed, one more whenever registers fall
   // free.  (Operand 4t + dt belongs to k-step t and channel group dt.)
   const __amdgpu_buffer_rsrc_t vb = __builtin_amdgcn_make_buffer_rsrc((void*)v, 0, -1, 0x00020000);
@@ -809,7 +809,10 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     if (lane == 0) atomicSub(&left[u & (RING - 1)], 1);
   };
   const bool two = q_valid > 32;                      // else the second 32 queries are all pad slots
-  int tiles_seen = 0, tiles_kept = 0;                 // (scalar registers; reported when the caller asks for the counts)
+  // Tiles of 32 queries and 64 keys gone through and, from bit 16 on, half tiles carried out, the only half of a tile with at
+  // most 32 valid keys for two (one scalar register, reported when the caller asks for the counts: the union has at most
+  // AUX_BYTES / 4 = 2^13 entries, and a wave counts 2 and 4 for each)
+  unsigned tally = 0u;
   int before = 0;                                     // entries of my group in the chunks before
   // Where a wave has few tiles, its reference follows every larger score in the first of them: the first half is little to go
   // by, and the largest probabilities, which count most, round best when they are 1.  (Error against float64 over that of
@@ -861,8 +864,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
           half_tile<NQ>(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, lazy, qf, o, st, kept);
         }
         lazy = kLazy;
-        tiles_seen += NQ;
-        tiles_kept += NQ * kept;
+        tally += NQ + ((unsigned)(nv > 32 ? NQ * kept : 2 * NQ * kept) << 16);
         leave(u);
         // (Only waves that are waiting for a tile ask for tiles: having every wave look for room after each of
         // its tiles cost the busy ones more than the earlier requests saved.)
@@ -884,9 +886,9 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
       for (int i = 0; i < 16; ++i) o[1][dt][i] = nought;    // (not kept through the loop)
   }
   publish();
-  if (tile_counts != nullptr && lane == 0 && tiles_seen) {
-    atomicAdd(&tile_counts[0], (unsigned long long)tiles_seen);
-    atomicAdd(&tile_counts[1], (unsigned long long)tiles_kept);
+  if (tile_counts != nullptr && lane == 0 && tally) {
+    atomicAdd(&tile_counts[0], (unsigned long long)(tally & 0xffffu));
+    atomicAdd(&tile_counts[1], (unsigned long long)(((tally >> 16) + (part & 1)) >> 1));   // (odd: up in one wave, down in the other)
   }
   if (gave_up && lane == 0) {
     atomicAdd(&g_wait_failures, 1ull);
