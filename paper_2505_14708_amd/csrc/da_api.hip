@@ -80,7 +80,7 @@ bool global_budget(const da_problem* p, const Geo& q, long long* budget, long lo
 }
 
 struct Workspace {
-  size_t qp, kp, vt, op, q_pool, k_pool, logits, idx, row_ptr, select, total;
+  size_t kp, vt, q_pool, k_pool, logits, idx, row_ptr, select, total;
 };
 
 // lists_cap > 0: the whole-map selection (lists of any length, `lists_cap` entries per head) instead of k per row
@@ -89,13 +89,13 @@ Workspace plan_workspace(const Geo& q, long long lists_cap = 0) {
   size_t bh = (size_t)q.B * q.H;
   size_t big = align_up(bh * (size_t)q.n_pad * q.d * elem_size(q));
   size_t pooled = align_up(bh * (size_t)q.g * q.d * sizeof(float));
-  // the bf16 attention kernel reads Q and writes O in the original token order: no reordered copies of them
-  const bool direct = q.dtype == DA_BF16;
+  // Reordered copies of K and V for the bf16 attention; it reads Q and writes O where they are.  (The float32 attention reads
+  // K and V where they are as well.  The room for four copies that da_workspace_size has always stated for it stays part of
+  // the interface, unused.)
   size_t off = 0;
-  w.qp = off; off += direct ? 0 : big;   // (float32: qp, kp, vt and op are not used; the size callers were told stays)
   w.kp = off; off += big;
   w.vt = off; off += big;
-  w.op = off; off += direct ? 0 : big;
+  if (q.dtype == DA_F32) off = 4 * big;
   w.q_pool = off; off += pooled;
   w.k_pool = off; off += pooled;
   w.logits = off; off += align_up(bh * (size_t)q.g * q.g * sizeof(float) + kSelectSlack);   // (the selector may read on past a row's end)
@@ -304,8 +304,7 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
     if (bf16 && !k_in_place && (e = launch_permute(q, K, kp, DA_REORDER_ROWS, s)) != hipSuccess) return DA_ERR_HIP;
     e = launch_all_lists(q, idx, row_ptr, whole_map ? cap : (long long)q.g * q.g, s);
   } else {
-    if ((e = launch_pool_reorder(q, Q, K, q_pool, k_pool, nullptr, bf16 && !k_in_place ? kp : nullptr, s)) !=
-        hipSuccess)
+    if ((e = launch_pool_reorder(q, Q, K, q_pool, k_pool, bf16 && !k_in_place ? kp : nullptr, s)) != hipSuccess)
       return DA_ERR_HIP;
     if ((e = launch_draft_logits(q, q_pool, k_pool, logits, s)) != hipSuccess) return DA_ERR_HIP;
     // guided sparsity: k per row, or the threshold over the whole map (Section 3.2.2)

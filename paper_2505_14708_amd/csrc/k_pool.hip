@@ -45,14 +45,13 @@ struct Vec<DA_F32> {
 
 constexpr int kPoolThreads = 64;
 
-// grid.x covers (bh, block, chunk) items; grid.y = 0 for Q, 1 for K.  With REORDER the tokens are
-// also written, as they go by, to their slots of the reordered tensors Qp, Kp (Algorithm 1), pad
-// slots zeroed: pooling and reordering then read Q and K once between them.
+// grid.x covers (bh, block, chunk) items; grid.y = 0 for Q, 1 for K.  With REORDER the tokens of K are
+// also written, as they go by, to their slots of the reordered tensor Kp (Algorithm 1), pad
+// slots zeroed: pooling and reordering then read K once between them.
 template <int DT, bool REORDER, bool MAXP>
 __global__ __launch_bounds__(kPoolThreads) void pool_kernel(Geo q, const uint4* __restrict__ Q, const uint4* __restrict__ K,
                                                    float* __restrict__ q_pool, float* __restrict__ k_pool,
-                                                   uint4* __restrict__ Qp, uint4* __restrict__ Kp, int cpr,
-                                                   long long items) {
+                                                   uint4* __restrict__ Kp, int cpr, long long items) {
   constexpr int N = Vec<DT>::N;
   long long item = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (item >= items) return;
@@ -67,9 +66,8 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(Geo q, const uint4* 
   const long long sn = q.in.sn / N;
   const long long pitch = block_row_pitch(q, b);
   const uint4* src = X + row_offset(q.in, q.H, bh, block_first_row(q, i, b)) / N + c;
-  uint4* const dbase = blockIdx.y ? Kp : Qp;          // NULL: this tensor is only pooled
-  const bool wr = REORDER && dbase != nullptr;
-  uint4* dstp = wr ? dbase + (blk * q.block) * cpr + c : nullptr;   // slot 0 of the block
+  const bool wr = REORDER && blockIdx.y;               // (Q is only pooled)
+  uint4* dstp = wr ? Kp + (blk * q.block) * cpr + c : nullptr;   // slot 0 of the block
   float acc[N];
 #pragma unroll
   for (int j = 0; j < N; ++j) acc[j] = MAXP ? -INFINITY : 0.f;
@@ -138,8 +136,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(Geo q, const uint4* 
 template <int DT, bool REORDER, bool MAXP>
 __global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, const uint2* __restrict__ Q, const uint2* __restrict__ K,
                                                                      float* __restrict__ q_pool, float* __restrict__ k_pool,
-                                                                     uint2* __restrict__ Qp, uint2* __restrict__ Kp, int cpr,
-                                                                     long long items) {
+                                                                     uint2* __restrict__ Kp, int cpr, long long items) {
   constexpr int N = Vec<DT>::N / 2;
   constexpr int AHEAD = 64;
   const unsigned item = blockIdx.x * kPoolThreads + threadIdx.x;   // (few: 32 bits hold them, and 64-bit divisions are five times as long)
@@ -156,9 +153,8 @@ __global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, cons
   const int skip = block_row_pitch(q, b) - b.vw;                          // rows between a patch row's last token and the next one's first
   const int recip = (65536 + b.vw - 1) / b.vw;                            // slot / vw by way of the reciprocal: exact below 256
   const uint2* src = X + row_offset(q.in, q.H, bh, block_first_row(q, i, b)) / N + c;
-  uint2* const dbase = blockIdx.y ? Kp : Qp;          // NULL: this tensor is only pooled
-  const bool wr = REORDER && dbase != nullptr;
-  uint2* dstp = wr ? dbase + (blk * q.block) * cpr + c : nullptr;   // slot 0 of the block
+  const bool wr = REORDER && blockIdx.y;               // (Q is only pooled)
+  uint2* dstp = wr ? Kp + (blk * q.block) * cpr + c : nullptr;   // slot 0 of the block
   float acc[N];
 #pragma unroll
   for (int j = 0; j < N; ++j) acc[j] = MAXP ? -INFINITY : 0.f;
@@ -195,51 +191,37 @@ __global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, cons
 constexpr long long kSmallWaves = 2048;
 
 hipError_t launch_pool(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, hipStream_t s) {
-  return launch_pool_reorder(q, Q, K, q_pool, k_pool, nullptr, nullptr, s);
+  return launch_pool_reorder(q, Q, K, q_pool, k_pool, nullptr, s);
 }
 
-// Qp, Kp: each may be NULL (that tensor is then only pooled)
-hipError_t launch_pool_reorder(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, void* Qp,
-                               void* Kp, hipStream_t s) {
+// Kp may be NULL (K is then only pooled); given, dtype is DA_BF16
+hipError_t launch_pool_reorder(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, void* Kp,
+                               hipStream_t s) {
   size_t es = q.dtype == DA_BF16 ? 2 : 4;
   int cpr = (int)(q.d * es / 16);
   long long items = (long long)q.B * q.H * q.g * cpr;
-  const bool re = Qp != nullptr || Kp != nullptr;
-  const bool mx = q.pool == DA_POOL_MAX;
   const bool cut = q.fw % q.pw != 0 || q.pw % 8 != 0;   // some patch rows are not a multiple of eight tokens
-  if (cut && 2 * items < 64 * kSmallWaves && q.block >= 64 && q.block <= 128 && q.in.sn < (1LL << 31)) {
-    const dim3 grid((unsigned)((2 * items + kPoolThreads - 1) / kPoolThreads), 2);
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, grid, dim3(kPoolThreads), 0, s, q, (const uint2*)Q, (const uint2*)K, q_pool, k_pool, (uint2*)Qp,
-                         (uint2*)Kp, 2 * cpr, 2 * items);
-    };
-    auto pick = [&](auto dt) {
-      constexpr int DT = decltype(dt)::value;
-      if (re && mx) go(pool_small_kernel<DT, true, true>);
-      else if (re) go(pool_small_kernel<DT, true, false>);
-      else if (mx) go(pool_small_kernel<DT, false, true>);
-      else go(pool_small_kernel<DT, false, false>);
-    };
-    if (q.dtype == DA_BF16) pick(std::integral_constant<int, DA_BF16>());
-    else pick(std::integral_constant<int, DA_F32>());
-    return hipGetLastError();
-  }
-  dim3 grid((unsigned)((items + kPoolThreads - 1) / kPoolThreads), 2);
-#define DA_POOL_LAUNCH(DT, RE, MX)                                                                                    \
-  hipLaunchKernelGGL((pool_kernel<DT, RE, MX>), grid, dim3(kPoolThreads), 0, s, q, (const uint4*)Q, (const uint4*)K,  \
-                     q_pool, k_pool, (uint4*)Qp, (uint4*)Kp, cpr, items)
-#define DA_POOL_PICK(DT)                                          \
-  if (re && mx) DA_POOL_LAUNCH(DT, true, true);                   \
-  else if (re) DA_POOL_LAUNCH(DT, true, false);                   \
-  else if (mx) DA_POOL_LAUNCH(DT, false, true);                   \
-  else DA_POOL_LAUNCH(DT, false, false)
-  if (q.dtype == DA_BF16) {
-    DA_POOL_PICK(DA_BF16);
-  } else {
-    DA_POOL_PICK(DA_F32);
-  }
-#undef DA_POOL_PICK
-#undef DA_POOL_LAUNCH
+  const bool small = cut && 2 * items < 64 * kSmallWaves && q.block >= 64 && q.block <= 128 && q.in.sn < (1LL << 31);
+  auto pick = [&](auto dt, auto reorder, auto max_pool) {
+    constexpr int DT = decltype(dt)::value;
+    constexpr bool RE = decltype(reorder)::value, MX = decltype(max_pool)::value;
+    if (small)
+      hipLaunchKernelGGL((pool_small_kernel<DT, RE, MX>), dim3((unsigned)((2 * items + kPoolThreads - 1) / kPoolThreads), 2),
+                         dim3(kPoolThreads), 0, s, q, (const uint2*)Q, (const uint2*)K, q_pool, k_pool, (uint2*)Kp, 2 * cpr,
+                         2 * items);
+    else
+      hipLaunchKernelGGL((pool_kernel<DT, RE, MX>), dim3((unsigned)((items + kPoolThreads - 1) / kPoolThreads), 2),
+                         dim3(kPoolThreads), 0, s, q, (const uint4*)Q, (const uint4*)K, q_pool, k_pool, (uint4*)Kp, cpr, items);
+  };
+  auto pick_max = [&](auto dt, auto reorder) {
+    if (q.pool == DA_POOL_MAX) pick(dt, reorder, std::true_type());
+    else pick(dt, reorder, std::false_type());
+  };
+  const std::integral_constant<int, DA_BF16> bf16;
+  const std::integral_constant<int, DA_F32> f32;
+  if (q.dtype != DA_BF16) pick_max(f32, std::false_type());
+  else if (Kp) pick_max(bf16, std::true_type());
+  else pick_max(bf16, std::false_type());
   return hipGetLastError();
 }
 
