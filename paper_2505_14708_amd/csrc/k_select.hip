@@ -9,6 +9,7 @@
 // ...): a counting pass is then one compare per key, whose lane mask is counted on the scalar
 // unit.  Longer rows keep their keys in LDS, or recompute them from global memory.
 #include "da_internal.h"
+#include "select_rows.h"
 
 namespace da {
 
@@ -173,12 +174,9 @@ hipError_t launch_all_lists(const Geo& q, int32_t* idx, int32_t* row_ptr, long l
 template <int KPL>
 static void launch_select_reg(const Geo& q, long long rows, const float* scores, int32_t* idx, uint8_t* mask, bool slack,
                               hipStream_t s) {
-  // rows whose 64 * KPL columns starting at the row's first all lie inside the array: all but the last few, or all
-  // of them when the caller vouches for kSelectSlack readable bytes behind the array
-  // (the last few are in the same launch: one of their own behind it cost 6.5 us however few they were)
-  const long long spill = 64LL * KPL - q.g;           // columns read past the end of a row (>= 0)
-  const long long last = spill > 0 && !slack ? (spill + q.g - 1) / q.g : 0;
-  const long long head = rows > last ? rows - last : 0;
+  // (the last few rows, which stay inside the array, are in the same launch: one of their own behind it cost 6.5 us however
+  // few they were)
+  const long long head = rows_that_read_on(rows, q.g, 64LL * KPL, slack);
   hipLaunchKernelGGL((select_reg_kernel<KPL>), dim3((unsigned)rows), dim3(64), 0, s, scores, idx, mask, q.g, q.k, head);
 }
 

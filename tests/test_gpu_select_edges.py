@@ -1,5 +1,5 @@
-"""Selection where a launch takes another turn: rows around the lengths that one register or one more per lane holds, in an
-array with nothing behind it (the last rows then stay inside it; a single row is all last); and the whole-map histograms
+"""Selection where a launch takes another turn: rows around the lengths that one register or one more per lane holds, without
+slack vouched for behind the array (the last rows then read other columns; a single row is all last); and the whole-map histograms
 with one to eight chunks of a map per workgroup.  Scores with many ties, infinities and NaN.  Against the oracle."""
 import numpy as np
 import pytest
