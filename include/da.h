@@ -156,6 +156,8 @@ int da_permute(const da_problem* p, const void* X, void* Y, int mode, void* stre
  * term (the cut is log2(block * k) + 14 powers of two).  The result differs from the full sum by less
  * than a bf16 rounding of the output; how much work is saved depends on how peaked the attention is
  * (nothing is dropped when all scores of a row are within that range of each other).
+ * A score that leaves float32 at its lower end (finite inputs, for instance a mask put into one channel of K) weighs
+ * nothing; a row whose scores all do is NaN.
  * The bf16 kernel keeps the block lists of four query blocks (two when block = 128) in LDS, which
  * bounds the problem: roughly g/2 + 4*min(g, 4k) bytes must fit in 32 KB (g up to about 7000 with
  * nothing dropped, far more when k << g), and g * block / 64 < 2^22; larger problems return DA_ERR_UNSUPPORTED.  Its waits for tiles are

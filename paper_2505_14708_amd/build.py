@@ -34,8 +34,8 @@ def _compile(src: str) -> str:
     obj = os.path.join(OBJ_DIR, os.path.splitext(os.path.basename(src))[0] + ".o")
     extra = ["-ffp-contract=off"] if src in STRICT_FP else []
     if src == "k_attn_bf16_ring.hip":
-        # all MFMA results in ordinary vector registers: the softmax reads the scores many times and
-        # a 32-query wave has the registers for it
+        # all MFMA results in ordinary vector registers: the softmax reads the scores many times, and the
+        # state of 64 queries fits the 256 that a wave has at two waves per SIMD
         extra += ["-mllvm", "-amdgpu-mfma-vgpr-form"]
     if src == "k_attn_bf16_ring.hip":
         extra.append("-fno-honor-nans")   # no NaN canonicalisation around max(); infinities stay exact

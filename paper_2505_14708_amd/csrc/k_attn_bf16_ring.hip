@@ -218,7 +218,10 @@ struct Soft {
   // half tile may be minus infinity (finite operands whose product leaves the range), and those keys weigh exp2(-inf) = 0,
   // not exp2(-inf + inf).
   float m;
-  float top;   // largest score seen so far (the reference trails it by at most kLazy powers of two); +inf for a pad query
+  // Largest score seen so far, in what was carried out and in a first tile that was only looked at; +inf for a pad query.  (The
+  // reference trails the scores the wave has carried out by at most kLazy powers of two; it may start up to the drop rule's
+  // cut below a score that was only looked at.)
+  float top;
   float l;     // this lane's partial sum of probabilities
 };
 
@@ -321,10 +324,9 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   }
   // O^T += V^T P^T.  The second half of the probabilities is made between the first half's matrix instructions, a pair
   // after each: the wave has vector work while the pipe is busy and need not find a partner that has.  Together with the
-  // raised priority (from here to the end of the tile a wave is in the way of nobody who waits for V or a tile; by itself
-  // worth 0.5 to 1 %, the order by itself nothing), nothing dropped: 24 heads x 1980 blocks 21.1 -> 20.9 ms, 8x16 windows
-  // 20.2 -> 19.6 ms, 5 heads x 1260 blocks 4.79 -> 4.66 ms, dense 480p 2.00 -> 1.94 ms; peaked 720p 12.85 -> 12.91 ms
-  // (two runs of one side differ by as much), 480p 3.00 -> 2.95 ms.
+  // raised priority (from here to the end of the tile a wave is in the way of nobody who waits for V or a tile; neither is
+  // worth 1 % alone), nothing dropped: 8x16 windows 20.2 -> 19.6 ms, 5 heads x 1260 blocks 4.79 -> 4.66 ms, dense 480p 2.00 ->
+  // 1.94 ms.  24 heads x 1980 blocks (21.1 -> 20.9 ms) and peaked inputs change by no more than two runs of one side differ.
   bf16x8 p2[NQ];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) {
@@ -439,7 +441,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   }
   const int my_block = slot_block(qblk);
   const bool has_block = my_block >= 0;
-  // a wave without a query block, or whose 64 slots of it are all pad slots, only helps with the ring
+  // a wave without a query block, or whose 64 slots of it are all pad slots, takes no tiles
   const int q_valid = (has_block ? block_valid(q, my_block) : 0) - BS * qsub;   // valid queries of the group
   const bool live = q_valid > 0;
   const long long qb = bh * q.g + (has_block ? my_block : 0);
@@ -1027,6 +1029,9 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 //     of 15 tiles 77 -> 57 us (63);
 //   - nothing after more than kMaxRounds rounds: workgroups differ in length, and by then they no longer end together
 //     (1575 workgroups, 39 in the last round: 4790 us either way).
+// Only the last round is shared out.  Halves for all of a launch are better still on some launches of one to two rounds (294
+// dense workgroups 1920 -> 1682 us, 360 of 240 tiles 902 -> 821 us) and worse on others, and quarters for all of 441 dense ones
+// cost 1975 -> 2454 us; what tells them apart is not known.
 struct Share {
   long long wide, grid;
   int split;
