@@ -70,6 +70,7 @@
 #include <string.h>
 #include <type_traits>
 #include "da_internal.h"
+#include "ring_turns.h"
 
 namespace da {
 namespace ring {
@@ -839,13 +840,13 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
       }
     }
     // The walk, 64 entries at a time: lane i holds entry base + i, a ballot tells which of them are my group's, a second
-    // one which of those are mine (every other one, or fourth, or eighth).  Entries that are not mine cost nothing.
+    // one which of those are mine (wave_of_turn: every other one, or fourth, or eighth).  Entries that are not mine cost nothing.
     for (int base = 0; base < nU && !gave_up; base += 64) {
       const int at = base + opaque_lane();
       const unsigned e_lane = ulist[min(at, nU - 1)];
       const bool is_ours = at < nU && (e_lane & my_bit) != 0u;
       const unsigned long long ours = __ballot(is_ours);
-      unsigned long long mine = __ballot(is_ours && ((before + lanes_before(ours)) & (parts - 1)) == part);
+      unsigned long long mine = __ballot(is_ours && wave_of_turn(before + lanes_before(ours), SUB, parts) == part);
       before += __popcll(ours);
       while (mine) {
         const int i = (int)__builtin_ctzll(mine);
