@@ -1,6 +1,7 @@
 // Reordering by pi (Algorithm 1) and restoring by pi^-1 (Algorithm 2) as pure data movement.
 // HBM-bound: every element is read once and written once in 16-byte pieces; the index
 // arithmetic is done on the fly, no index array is read.
+#include <type_traits>
 #include "da_internal.h"
 
 namespace da {
@@ -83,25 +84,31 @@ __global__ __launch_bounds__(256) void permute_vt_kernel(Geo q, const E* __restr
   int cpr = q.d / PER;
   const chunk16* Xc = (const chunk16*)(X + row_offset(q.in, q.H, bh, block_first_row(q, i, b)));   // the block's first row
   const long long sn = q.in.sn / PER, pitch = block_row_pitch(q, b);
-  // (a thread's four chunks of a 16 KB block are all on their way before the first is put down: 12.3 -> 11.3 us at 1344
-  // blocks, 15.2 -> 14.0 us at 2016; larger launches as before, where other workgroups fill the waits)
-  for (int e0 = threadIdx.x; e0 < q.block * cpr; e0 += 4 * 256) {
-    chunk16 val[4];
+  // A thread's four chunks of a 16 KB block are all on their way before the first is put down: 12.3 -> 11.3 us at 1344 blocks,
+  // 15.2 -> 14.0 us at 2016; larger launches as before, where other workgroups fill the waits.  Blocks of no more than a chunk
+  // per thread (4x4 windows, say) have nothing to ask for ahead: 7920 of them with 8 heads 103.5 -> 100 us one at a time.
+  auto bring = [&](auto ahead) {
+    constexpr int AHEAD = decltype(ahead)::value;
+    for (int e0 = threadIdx.x; e0 < q.block * cpr; e0 += AHEAD * 256) {
+      chunk16 val[AHEAD];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int e = e0 + 256 * j, s = e / cpr, c = e - s * cpr;
-      val[j] = make_uint4(0, 0, 0, 0);
-      if (s < nv) {                                    // (nv <= block: such an e is below block * cpr as well)
-        const int u = s / b.vw, v = s - u * b.vw;
-        val[j] = load_once(&Xc[((long long)u * pitch + v) * sn + c]);
+      for (int j = 0; j < AHEAD; ++j) {
+        const int e = e0 + 256 * j, s = e / cpr, c = e - s * cpr;
+        val[j] = make_uint4(0, 0, 0, 0);
+        if (s < nv) {                                  // (nv <= block: such an e is below block * cpr as well)
+          const int u = s / b.vw, v = s - u * b.vw;
+          val[j] = load_once(&Xc[((long long)u * pitch + v) * sn + c]);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < AHEAD; ++j) {
+        const int e = e0 + 256 * j, s = e / cpr, c = e - s * cpr;
+        if (s < q.block) *(chunk16*)(tile + s * ld + c * PER) = val[j];
       }
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int e = e0 + 256 * j, s = e / cpr, c = e - s * cpr;
-      if (s < q.block) *(chunk16*)(tile + s * ld + c * PER) = val[j];
-    }
-  }
+  };
+  if (q.block * cpr > 256) bring(std::integral_constant<int, 4>());
+  else bring(std::integral_constant<int, 1>());
   __syncthreads();
   E* out = Y + (bh * q.g + i) * (long long)q.d * q.block;
   if (OPERAND) {
