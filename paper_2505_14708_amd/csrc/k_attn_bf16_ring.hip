@@ -469,35 +469,22 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   for (int i = 0; i < 4; ++i) pre[i] = lister && lane + 64 * i < k ? list[lane + 64 * i] : -1;
   __builtin_amdgcn_sched_barrier(0);
 
-  // Q fragments (B operand): lane (query r, half-wave hh) holds d = 16t + 8hh .. +7.  Asked for
-  // next, so that they arrive while the lists are being merged.
   // With `direct`, Qp and Op are the caller's Q and O (q.in, q.out: in the original token order as a rule): the
   // reordering of Q and the restoring of O (Algorithms 1 and 2) are then this kernel's addressing, slot -> row.
   const BlockPos qpos = block_pos(q, has_block ? my_block : 0);
   const long long q_first = block_first_row(q, has_block ? my_block : 0, qpos);
   const int q_pitch = block_row_pitch(q, qpos);
-  // byte offset of the row of slot s of my query block in Qp / Op, or -1 (a pad slot has no row of its own there)
-  auto row_bytes = [&](int s, const Rows& where) -> long long {
-    if (!direct) return (qb * BLOCK + s) * (long long)(D * 2);
-    if (s >= qpos.vh * qpos.vw) return -1;
-    const int u = s / qpos.vw, v = s - u * qpos.vw;
-    return row_offset(where, q.H, bh, q_first + (long long)u * q_pitch + v) * 2;
+  // slots of my query block with a row of their own there (a pad slot has none in the original order)
+  const int rows_there = direct ? qpos.vh * qpos.vw : BLOCK;
+  // where the row of slot 0 of my query block is, in bytes, and how many bytes slot s lies behind it
+  auto row_base = [&](const Rows& where) -> long long {
+    return 2 * (direct ? row_offset(where, q.H, bh, q_first) : qb * BLOCK * (long long)D);
   };
-  bf16x8 qf[2][8];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int r = lane & 31, hh = lane >> 5;
-    const long long row = row_bytes(BS * qsub + 32 * h + r, q.in);
-    const unsigned char* qrow = Qp + max(row, 0LL);
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      qf[h][t] = *(const bf16x8*)(qrow + (16 * t + 8 * hh) * 2);
-      if (row < 0) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) qf[h][t][i] = (__bf16)0.f;
-      }
-    }
-  }
+  auto row_after = [&](const Rows& where, int s, bool there) -> long long {
+    if (!there) return s * (D * 2);
+    const int u = (s * ((65536 + qpos.vw - 1) / qpos.vw)) >> 16;   // s / vw by way of the reciprocal: exact below 256
+    return (long long)(u * (q_pitch - qpos.vw) + s) * (where.sn * 2);
+  };
 
   unsigned* bitmap = (unsigned*)(smem + RING_BYTES);  // [FG][bw] one bitmap of kept key blocks per query block
   const int bw = (g + 31) >> 5;
@@ -522,6 +509,20 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     for (int e = lane + 256; e < k; e += 64) {
       int j = list[e];
       if ((unsigned)j < (unsigned)g) atomicOr(&bitmap[qblk * bw + (j >> 5)], 1u << (j & 31));
+    }
+  }
+  // Q comes in by way of the ring, which is empty until the walk: 64 rows per group in a slot, as a K tile lies there, the
+  // rows dealt to the group's waves.  (Every wave for itself and straight to registers, 64 rows are twice the bytes and 16 loads
+  // that touch 32 rows each: asking for them took 1.4 to 1.9 us of a workgroup, 0.5 with 32 queries per wave.  da_forward, 48
+  // heads, one 48x80 frame with 5 % kept 146 -> 138 us, four frames 691 -> 663 us; one 30x52 frame, half kept, 122.4 -> 119.8 us.)
+  const unsigned ring_lds = (unsigned)(uintptr_t)(lds_bytes)smem;
+  const unsigned q_lds = ring_lds + (unsigned)lgroup * SLOT;
+  if (live) {
+    const unsigned char* const q0 = Qp + row_base(q.in);
+    for (int it = part; it < 16; it += parts) {
+      const int row = 4 * it + (lane >> 4);
+      const int slot = min(BS * qsub + row, rows_there - 1);   // (what has no row of its own is zeroed below)
+      dma16(q0 + row_after(q.in, slot, direct) + (((lane & 15) ^ (row & 15)) << 4), q_lds + it * 1024);
     }
   }
   __syncthreads();
@@ -597,7 +598,24 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
       if (lane == 0) count[1] = __popcll(nz) + __popcll(n2);
     }
   }
+  wait_vm0();                                         // (my share of Q has landed)
   __syncthreads();
+  // Q fragments (B operand): lane (query r, half-wave hh) holds d = 16t + 8hh .. +7.  (Read by all before the first tile is
+  // asked for: barriers lie between.)
+  bf16x8 qf[2][8];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = 32 * h + (lane & 31);
+    const unsigned at = q_lds + row * 256 + (((lane >> 5) ^ (row & 15)) << 4);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) qf[h][t] = lds_operand(at ^ (32 * t));
+    if (direct && row >= q_valid) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) qf[h][t][i] = (__bf16)0.f;
+    }
+  }
   {
     int at = count[1];
     for (int w = 0; w < wave; ++w) at += wcount[w];
@@ -704,7 +722,6 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   __syncthreads();
 
   // ---- per-lane constants
-  const unsigned ring_lds = (unsigned)(uintptr_t)(lds_bytes)smem;
   const int krow = sigma(lane & 31);
   const unsigned kbase = ring_lds + krow * 256 + (((lane >> 5) ^ (krow & 15)) << 4);   // K operand of k-step 0 in slot 0, swizzle applied
   const unsigned char* Kbh = Kp + bh * q.n_pad * (D * 2);
@@ -754,9 +771,8 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     st[h].top = 32 * h + (lane & 31) < q_valid ? -INFINITY : INFINITY;
     st[h].l = nought;
   }
-  // Make the compiler wait for the Q fragments here, by touching them: its own counter
-  // bookkeeping then knows they are in.  Otherwise it would wait for them at their first use
-  // inside the tile loop, with a vmcnt that also drains the tile loads in flight.
+  // The Q fragments are in by here, and the compiler is to know: else it would wait for them at their first use inside the
+  // tile loop, on every trip.
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1009,12 +1025,17 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   else finish(o[0], st[0]);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+  unsigned char* const o0 = Op + row_base(q.out);
+  auto write_rows = [&](auto there) {
 #pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    const long long orow = row_bytes(BS * qsub + 32 * part + row, q.out);
-    if (orow >= 0) *(uint4*)(Op + orow + ch * 16) = *(const uint4*)(taken + row * O_STRIDE + ch * 16);
-  }
+    for (int it = 0; it < 8; ++it) {
+      const int row = it * 4 + (lane >> 4), ch = lane & 15, slot = BS * qsub + 32 * part + row;
+      if (!there || slot < rows_there)
+        *(uint4*)(o0 + row_after(q.out, slot, there) + ch * 16) = *(const uint4*)(taken + row * O_STRIDE + ch * 16);
+    }
+  };
+  if (direct) write_rows(std::true_type());
+  else write_rows(std::false_type());
 }
 
 // Which workgroups of a launch are whole (the first `wide`) and into how many shares (2^split) the others go.
