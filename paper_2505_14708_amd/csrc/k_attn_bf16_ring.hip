@@ -5,20 +5,21 @@
 // Why tiles are shared.  With 64 queries against a 64-key tile the arithmetic intensity is
 // 64 flop per byte of K/V, far below the machine balance, and a kernel in which every query
 // block streams its own tiles is bound by the memory fabric.  Query blocks at the same patch
-// position in consecutive frames keep largely the same key blocks, so a workgroup takes four
+// position in consecutive frames keep largely the same key blocks, so a workgroup takes eight
 // such blocks and walks the UNION of their lists once: every K tile of the union is brought
-// into LDS once for all four, and the V tiles they fetch meet in L2.
+// into LDS once for all eight, and the V tiles they fetch meet in L2.
 //
 // Workgroup = 8 wavefronts, two per SIMD: while one is in its softmax (vector ALU) the other keeps the matrix pipe
 // busy, and the pairing hides LDS latency, the wait for V and the waits of the ring protocol.  A wavefront owns 64
-// queries (a block) and every other entry of that block's list; the two waves of a block put their sums together at the
-// end.  (Launches of few workgroups share some of them out among two or four, with four or eight waves per block:
-// share_out.)  (With 32 queries and every entry per wave, a key tile is read from LDS and its V from L2 twice: V alone was 128
-// KB per tile step over a path of 64 bytes per cycle and CU.  Measured on 24 heads x 1980 blocks, 198 kept: 21.6 -> 19.8
-// ms where nothing is dropped, 12.0 -> 11.8 ms on peaked inputs.)  64 queries are 128 registers of output, 64 of Q and
-// 32 of scores, which leaves 32 for everything else at two waves per SIMD: tiles are taken 32 keys at a time, operands
-// arrive just ahead of their use, and what can be made anew in the loop is not kept (opaque_lane).  The two waves of a
-// SIMD belong to different query blocks so that they are rarely in the same phase.
+// queries (a block) and all of its list.  (Launches of few workgroups share them out among two, four or eight, with as many
+// waves to a block, which take its entries in turn and put their sums together at the end: share_out.)  With four blocks to a
+// workgroup and two waves to a block, as the halves of a shared one still are, the union of four lists was 1.48 lists long
+// and that of eight is 2.1, so a wave's tile cost 1.4 times the bytes; there was twice the fixed part per query, and the sums of two
+// waves to join.  24 heads x 1980 blocks, 198 kept: 13.4 -> 12.4 ms peaked, 21.7 -> 20.5 ms where nothing is dropped; dense, 3
+// heads x 588 blocks 1.91 -> 1.74 ms.
+// 64 queries are 128 registers of output, 64 of Q and 32 of scores, which leaves 32 for everything else at two
+// waves per SIMD: tiles are taken 32 keys at a time, operands arrive just ahead of their use, and what can be made anew in
+// the loop is not kept (opaque_lane).
 //
 // Per 32 keys a wave computes
 //     S^T = K Q^T      (32 keys x 64 queries: 2 MFMA tiles of 32x32, 8 k-steps over d)
@@ -39,7 +40,7 @@
 // in the tile loop:
 //   ready[s]   union entry whose K tile slot s holds (set once the tile has landed)
 //   left[s]    how many waves have yet to read the tile in slot s (set when the tile is asked for: one
-//              wave of each query block that holds the entry; every reader takes one off when it
+//              wave of each group of queries that holds the entry; every reader takes one off when it
 //              is through): at zero the slot may be overwritten
 //   next_load  entries are requested strictly in order, entry L once its slot L % 8 is free, by the waves
 //              that are waiting for a tile: the one that notices first claims it with a compare-and-
@@ -99,6 +100,7 @@ constexpr float kC2 = 0.08838834764831845f * 1.4426950408889634f;   // log2(e)/s
 constexpr float kLazy = 8.0f;                     // move the running max only past this many powers of two
 constexpr float kDropLog2 = 14.0f;                // all keys dropped from a row together weigh less than 2^-14 of its largest term
 constexpr int kSpinLimit = 1 << 20;
+constexpr int kValidBit = 18, kMemberBit = 24;       // fields of a union entry (key sub-blocks are numbered below 2^18)
 constexpr int kPeekTiles = 8;                       // lists of at least so many tiles per wave: all waves of a group look at the first one
 
 // Waves whose bounded wait for a tile ran out since the library was loaded (their rows were written as NaN).
@@ -198,13 +200,18 @@ __device__ __forceinline__ void mask_pad_keys(f32x16& s, int nv) {
   for (int i = 0; i < 16; ++i) s[i] = 16 * (i >> 3) + (i & 7) < lim ? s[i] : ninf;
 }
 
-// n / d for 0 <= n < 2^24, d >= 1, by way of the float reciprocal (exact: the estimate is off by one at most)
+// n / d for 0 <= n < 2^27, d >= 1, n / d < 2^20, by way of the float reciprocal (exact: the estimate is off by one at most)
 __device__ __forceinline__ int small_div(int n, int d) {
   int qt = (int)((float)n * __frcp_rn((float)d));
   const int rem = n - qt * d;
   qt += rem >= d ? 1 : 0;
   qt -= rem < 0 ? 1 : 0;
   return qt;
+}
+
+// how many lanes below this one are set in m
+__device__ __forceinline__ int lanes_before(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
 }
 
 // valid slots of block j (blocks are numbered below 2^22)
@@ -348,26 +355,109 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   __builtin_amdgcn_s_setprio(0);
 }
 
-// How the frames that do not fill a group of `fg` are spread over workgroups.
-struct TailPlan {
-  int full_groups;   // groups of fg frames
-  int rem;           // frames left over (0: no tail workgroups)
-  int per_wg;        // positions per tail workgroup
-  int tail_wgs;      // tail workgroups per head
-};
-__host__ __device__ inline TailPlan tail_plan(const Geo& q, int fg) {
-  TailPlan p;
-  p.full_groups = q.T / fg;
-  p.rem = q.T - p.full_groups * fg;
-  p.per_wg = p.rem ? fg / p.rem : 1;
-  const int per_frame = q.gh * q.gw;
-  p.tail_wgs = p.rem ? (per_frame + p.per_wg - 1) / p.per_wg : 0;
-  return p;
+// Puts the n union entries at `list` in the order of the walk (see there), by all eight waves.  The scratch is the ring's place,
+// which holds nothing yet; ends with a barrier.  Number within the class: a wave takes a stretch of the list, 64 entries at a
+// time; rank by key: kBuckets buckets of keys, and inside a bucket by comparison (whatever the order in which waves reach
+// the counters, the result is the same).
+constexpr int kBuckets = 2048;
+__device__ __forceinline__ void spread_walk(unsigned char* scratch, unsigned* list, int n, int wave, int lane) {
+  int* const of_class = (int*)scratch;                // [WAVES][256] entries of a class in each wave's stretch, then before it
+  float* const inv_total = (float*)(scratch + 8192);  // [256]
+  int* const start = (int*)(scratch + 16384);         // [kBuckets + 1] entries per bucket, then where it starts
+  int* const wave_sum = (int*)(scratch + 28672);      // [WAVES]
+  int* const number = (int*)(scratch + 32768);        // [n]
+  uint2* const slots = (uint2*)(scratch + 65536);     // [n] key and entry
+  const int t = threadIdx.x;
+  for (int i = t; i < WAVES * 256; i += 512) of_class[i] = 0;
+  for (int i = t; i < kBuckets; i += 512) start[i] = 0;
+  __syncthreads();
+  const int stretch = ((n + 511) >> 9) << 6;
+  for (int base = wave * stretch; base < min(n, (wave + 1) * stretch); base += 64) {
+    const int i = base + lane;
+    const int m = i < n ? (int)(list[i] >> kMemberBit) : 0;
+    unsigned long long same = ~0ull;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const unsigned long long has = __ballot((m >> b) & 1);
+      same &= (m >> b) & 1 ? has : ~has;
+    }
+    const int before = lanes_before(same), c = of_class[wave * 256 + m];
+    if (i < n) number[i] = c + before;
+    asm volatile("" ::: "memory");
+    if (before == 0) of_class[wave * 256 + m] = c + __popcll(same);
+    asm volatile("" ::: "memory");
+  }
+  __syncthreads();
+  if (t < 256) {
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      const int c = of_class[w * 256 + t];
+      of_class[w * 256 + t] = sum;
+      sum += c;
+    }
+    inv_total[t] = 1.0f / (float)max(sum, 1);
+  }
+  __syncthreads();
+  // key of entry e, number p of its class (below 1 but for rounding), and the bucket of a key
+  auto key_of = [&](unsigned e, int p) -> float {
+    const int m = (int)(e >> kMemberBit);
+    const float u = (float)m * 0.618034f;
+    return ((float)p + (u - floorf(u))) * inv_total[m];
+  };
+  auto bucket_of = [](float key) -> int { return min((int)(key * (float)kBuckets), kBuckets - 1); };
+  for (int i = t; i < n; i += 512) {
+    const unsigned e = list[i];
+    const int p = number[i] + of_class[(i / stretch) * 256 + (int)(e >> kMemberBit)];
+    number[i] = p | atomicAdd(&start[bucket_of(key_of(e, p))], 1) << 16;
+  }
+  __syncthreads();
+  {
+    int c[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      c[j] = sum;
+      sum += start[4 * t + j];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int x = __shfl_up(incl, o);
+      incl += lane >= o ? x : 0;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int at = incl - sum;
+    for (int w = 0; w < wave; ++w) at += wave_sum[w];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) start[4 * t + j] = at + c[j];
+    if (t == 511) start[kBuckets] = n;
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += 512) {
+    const unsigned e = list[i];
+    const float key = key_of(e, number[i] & 0xffff);
+    slots[start[bucket_of(key)] + (number[i] >> 16)] = make_uint2(__float_as_uint(key), e);
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += 512) {
+    const uint2 mine = slots[i];
+    const float key = __uint_as_float(mine.x);
+    const int bucket = bucket_of(key), lo = start[bucket], hi = start[bucket + 1];
+    int rank = lo;
+    for (int x = lo; x < hi; ++x) {
+      const uint2 other = slots[x];
+      const float its = __uint_as_float(other.x);
+      rank += its < key || (its == key && other.y < mine.y) ? 1 : 0;
+    }
+    list[rank] = mine.y;
+  }
+  __syncthreads();
 }
 
 // SUB = 64-token sub-blocks per block (1: 8x8 patches, 2: 128-token blocks such as 8x16 patches).  A block of
-// 128 is two K tiles and two V tiles in a row, and its queries are four waves' worth: the workgroup then takes two
-// query blocks (two consecutive frames) instead of four, and a key block enters the union walk as two entries.
+// 128 is two K tiles and two V tiles in a row, and its queries are two waves' worth: the workgroup then takes four
+// query blocks (four consecutive frames) instead of eight, and a key block enters the union walk as two entries.
 // LISTS: the kept blocks come as lists of any length (row_ptr) instead of k per row.
 template <int SUB, bool LISTS>
 __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const unsigned char* __restrict__ Qp,
@@ -376,71 +466,43 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
                                                                const int32_t* __restrict__ idx,
                                                                const int32_t* __restrict__ row_ptr, long long cap,
                                                                unsigned char* __restrict__ Op, float* __restrict__ lse,
-                                                               int balance, float skip, int direct, int wide, int split,
+                                                               float skip, int direct, Share share,
                                                                unsigned long long* __restrict__ tile_counts) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_TOTAL];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
   // Heads one after the other (the K/V of the heads in flight then fit the last-level cache);
-  // inside a head a workgroup is one patch position and FG consecutive frames, and the frame
+  // inside a head a unit is one patch position and FG consecutive frames, and the frame
   // groups of one position follow each other on one XCD (workgroups are dealt round-robin to the
   // 8 XCDs).
-  constexpr int FG = 4 / SUB;                         // query blocks (frames) per workgroup
+  constexpr int LOG_FG = SUB == 1 ? 3 : 2;
+  constexpr int FG = 1 << LOG_FG;                     // query blocks (frames) per unit
   constexpr int BLOCK = BS * SUB;                     // slots per block
-  // The frames that do not fill a group (T mod FG of them) are taken position by position into
-  // workgroups of their own, FG / (T mod FG) positions each: their lists have little in common, but
-  // a workgroup with one live query block out of four would cost as much as a full one.
   const int per_frame = q.gh * q.gw;
-  const TailPlan plan = tail_plan(q, FG);
-  const int fgs = plan.full_groups;
-  const int pos_per_xcd = (per_frame + 7) >> 3;
-  const int regular = 8 * pos_per_xcd * fgs;
-  const int wg_per_head = regular + plan.tail_wgs;
-  // The first `wide` workgroups are whole ones.  The others share the four groups of 64 queries of a whole one between
-  // them, 2^split of them (sub = which), and put twice or four times as many waves to a group; the shares of a whole one
-  // stay on its XCD.
-  const int narrow = max((int)blockIdx.x - wide, 0);
-  const int lsub = (int)blockIdx.x < wide ? 0 : split;
-  const int sub = lsub ? (narrow >> 3) & ((1 << lsub) - 1) : 0;
-  const int whole = lsub ? wide + (narrow >> (3 + lsub)) * 8 + (narrow & 7) : (int)blockIdx.x;
-  const long long bh = whole / wg_per_head;
-  if (bh >= (long long)q.B * q.H) return;             // (the last eight whole ones need not be eight)
-  // the tail workgroups (longer walks) come first within a head, the regular ones after them
-  const int n = whole - (int)(bh * wg_per_head) - plan.tail_wgs;   // < 0: tail workgroup n + tail_wgs
-  // Four groups of 64 queries (a block, or half a block of 128), two waves each (in a share: two groups, four waves
-  // each, or one group, eight waves); waves w and w+4 share a SIMD: give them different groups where there are some.
+  const int per_head = units_per_head(q.T, FG, per_frame);
+  // The eight groups of 64 queries of a unit are shared between 2^lsub workgroups, with 2^lsub waves to a group.
+  const ShareOf mine_is = share_of(share, (int)blockIdx.x);
+  const int lsub = mine_is.lsub, sub = mine_is.sub;
+  const long long bh = mine_is.unit / per_head;
+  if (bh >= (long long)q.B * q.H) return;             // (the last eight units need not be eight)
+  const UnitPlace place = unit_place(mine_is.unit - (int)bh * per_head, q.T, LOG_FG, per_frame);
+  // waves w and w+4 share a SIMD: they have different groups where there are some.
   // The waves of a group take its list entries in turn (part = which of them).
-  const int groups = 4 >> lsub, parts = 2 << lsub;
-  const int part = wave >> (2 - lsub);
-  const int lgroup = (wave + (lsub ? wave >> 2 : 2 * part)) & (groups - 1);   // number of the group in this workgroup
-  const int group = sub * groups + lgroup;            // and in the whole one
-  const int qblk = SUB == 1 ? group : group >> 1;
+  const int groups = 8 >> lsub, parts = 1 << lsub;
+  const int part = wave >> (3 - lsub);
+  const int lgroup = (wave + (wave >> 2) * (lsub ? 3 - lsub : 0)) & (groups - 1);   // number of the group in this workgroup
+  const int group = sub * groups + lgroup;            // and in the unit
   const int qsub = SUB == 1 ? 0 : group & 1;          // which 64 queries of the block
-  // query block w of this workgroup: (position, frame), or none
-  // (divisions of small non-negative numbers: by way of the float reciprocal)
-  const int n_over_fgs = n >= 0 ? small_div(n >> 3, max(fgs, 1)) : 0;
-  auto slot_pos = [&](int w) -> int {
-    if (n >= 0) return (n & 7) + 8 * n_over_fgs;
-    return w < plan.per_wg * plan.rem ? (n + plan.tail_wgs) * plan.per_wg + small_div(w, plan.rem) : per_frame;
-  };
-  auto slot_frame = [&](int w) -> int {
-    if (n >= 0) return FG * ((n >> 3) - n_over_fgs * fgs) + w;
-    return fgs * FG + (w - small_div(w, plan.rem) * plan.rem);
-  };
-  // block number of query block w, -1 if the slot is empty
-  const int first_slot = sub * groups / SUB, last_slot = (sub * groups + groups - 1) / SUB;   // those of this workgroup
+  const int first_slot = sub * groups / SUB;          // query blocks of this workgroup: so many from this one on
+  const int blocks = max(groups / SUB, 1);
+  const int lblock = group / SUB - first_slot;        // my query block's number among them
+  // block number of query block w of this workgroup, -1 if the place is empty (then all after it are)
   auto slot_block = [&](int w) -> int {
-    const int p = slot_pos(w), fr = slot_frame(w);
-    return w >= first_slot && w <= last_slot && p < per_frame && fr < q.T ? fr * per_frame + p : -1;
+    const int p = place.pos0 + ((first_slot + w) >> place.lg), fr = place.frame0 + ((first_slot + w) & ((1 << place.lg) - 1));
+    return w < blocks && p < per_frame ? fr * per_frame + p : -1;
   };
-  // a regular workgroup past the last position, or a share without a block: all of it leaves
-  if (n >= 0 && slot_pos(0) >= per_frame) return;
-  {
-    bool any = false;
-    for (int w = first_slot; w <= last_slot; ++w) any = any || slot_block(w) >= 0;
-    if (!any) return;
-  }
-  const int my_block = slot_block(qblk);
+  if (slot_block(0) < 0) return;                      // past the last position
+  const int my_block = slot_block(lblock);
   const bool has_block = my_block >= 0;
   // a wave without a query block, or whose 64 slots of it are all pad slots, takes no tiles
   const int q_valid = (has_block ? block_valid(q, my_block) : 0) - BS * qsub;   // valid queries of the group
@@ -486,29 +548,28 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     return (long long)(u * (q_pitch - qpos.vw) + s) * (where.sn * 2);
   };
 
-  unsigned* bitmap = (unsigned*)(smem + RING_BYTES);  // [FG][bw] one bitmap of kept key blocks per query block
+  unsigned* bitmap = (unsigned*)(smem + RING_BYTES);  // [blocks][bw] one bitmap of kept key blocks per query block
   const int bw = (g + 31) >> 5;
-  unsigned* ulist = bitmap + 4 * bw;                  // union entries: key sub-block | (valid slots - 1) << 22 | membership << 28
-  const int union_max = SUB * (LISTS ? g : min(g, FG * q.k));
-  int* ctrl = (int*)(smem + LDS_TOTAL - 128);         // [32]: ready[8], left[8], next_load, count[2], first[2], wcount[8], live groups, waves that gave up
+  unsigned* ulist = bitmap + blocks * bw;             // union entries: key sub-block | (valid slots - 1) << 18 | membership << 24
+  int* ctrl = (int*)(smem + LDS_TOTAL - 128);         // [32]: ready[8], left[8], next_load, count[2], mixed, (1 unused), wcount[8], live groups, waves that gave up
   int* ready = ctrl;                                  // [RING]
   int* left = ctrl + 8;                               // [RING]
   int* next_load = ctrl + 16;
   int* count = ctrl + 17;                             // [2]
 
   // ---- union of the workgroup's lists
-  for (int i = threadIdx.x; i < 4 * bw; i += 512) bitmap[i] = 0u;
+  for (int i = threadIdx.x; i < blocks * bw; i += 512) bitmap[i] = 0u;
   if (threadIdx.x < 32) ctrl[threadIdx.x] = threadIdx.x < RING ? -1 : 0;
   __syncthreads();
-  if (live && part == 0 && lane == 0) atomicOr(&ctrl[28], 1 << group);   // which groups take tiles at all
+  if (live && part == 0 && lane == 0) atomicOr(&ctrl[28], 1 << lgroup);   // which groups take tiles at all
   if (lister) {
     // (an entry that is no block number is left out: it must not reach the bitmap, let alone an address)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if ((unsigned)pre[i] < (unsigned)g) atomicOr(&bitmap[qblk * bw + (pre[i] >> 5)], 1u << (pre[i] & 31));
+      if ((unsigned)pre[i] < (unsigned)g) atomicOr(&bitmap[lblock * bw + (pre[i] >> 5)], 1u << (pre[i] & 31));
     for (int e = lane + 256; e < k; e += 64) {
       int j = list[e];
-      if ((unsigned)j < (unsigned)g) atomicOr(&bitmap[qblk * bw + (j >> 5)], 1u << (j & 31));
+      if ((unsigned)j < (unsigned)g) atomicOr(&bitmap[lblock * bw + (j >> 5)], 1u << (j & 31));
     }
   }
   // Q comes in by way of the ring, which is empty until the walk: 64 rows per group in a slot, as a K tile lies there, the
@@ -537,22 +598,17 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     bool own = false;
 #pragma unroll
     for (int w = 0; w < FG; ++w) own = own || j == own_j[w];
-    unsigned m4 = 0;
-    if (j < g && own == want_own) {
-#pragma unroll
-      for (int w = 0; w < FG; ++w) m4 |= ((bitmap[w * bw + (j >> 5)] >> (j & 31)) & 1u) << w;
-    }
-    return m4;
+    unsigned m = 0;
+    if (j < g && own == want_own)
+      for (int w = 0; w < blocks; ++w) m |= ((bitmap[w * bw + (j >> 5)] >> (j & 31)) & 1u) << w;
+    return m;
   };
   // a key block becomes one entry per 64-slot sub-block that holds a valid slot (in a row)
   auto second = [&](int j) -> bool { return SUB == 2 && j < g && valid_slots(q, per_frame, j) > BS; };
-  auto put_entries = [&](int at, int j, unsigned m4, bool two) {
+  auto put_entries = [&](int at, int j, unsigned m, bool two) {
     const int nvb = valid_slots(q, per_frame, j);
-    ulist[at] = (unsigned)(j * SUB) | ((unsigned)(min(nvb, BS) - 1) << 22) | (m4 << 28);
-    if (two) ulist[at + 1] = (unsigned)(j * SUB + 1) | ((unsigned)(nvb - BS - 1) << 22) | (m4 << 28);
-  };
-  auto lanes_before = [&](unsigned long long m) -> int {
-    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+    ulist[at] = (unsigned)(j * SUB) | ((unsigned)(min(nvb, BS) - 1) << kValidBit) | (m << kMemberBit);
+    if (two) ulist[at + 1] = (unsigned)(j * SUB + 1) | ((unsigned)(nvb - BS - 1) << kValidBit) | (m << kMemberBit);
   };
   // every wave takes a contiguous eighth of the key blocks, 64 at a time: count, then place
   int* wcount = ctrl + 20;                            // [WAVES]
@@ -568,8 +624,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         const int word = base + lane;
         unsigned v = 0u;
         if (word < w_hi) {
-#pragma unroll
-          for (int w = 0; w < FG; ++w) v |= bitmap[w * bw + word];
+          for (int w = 0; w < blocks; ++w) v |= bitmap[w * bw + word];
 #pragma unroll
           for (int w = 0; w < FG; ++w)
             if (own_j[w] >= 0 && (own_j[w] >> 5) == word) v &= ~(1u << (own_j[w] & 31));
@@ -591,10 +646,10 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
       int j = -1;
 #pragma unroll
       for (int w = 0; w < FG; ++w) j = lane == w ? own_j[w] : j;
-      const unsigned m4 = j >= 0 ? membership(j, true) : 0u;
-      const bool two = m4 != 0u && second(j);
-      const unsigned long long nz = __ballot(m4 != 0u), n2 = __ballot(two);
-      if (m4) put_entries(lanes_before(nz) + lanes_before(n2), j, m4, two);
+      const unsigned m = j >= 0 ? membership(j, true) : 0u;
+      const bool two = m != 0u && second(j);
+      const unsigned long long nz = __ballot(m != 0u), n2 = __ballot(two);
+      if (m) put_entries(lanes_before(nz) + lanes_before(n2), j, m, two);
       if (lane == 0) count[1] = __popcll(nz) + __popcll(n2);
     }
   }
@@ -619,97 +674,43 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   {
     int at = count[1];
     for (int w = 0; w < wave; ++w) at += wcount[w];
+    unsigned all = 0;
+    for (int w = 0; w < blocks; ++w) all |= slot_block(w) >= 0 ? 1u << w : 0u;
+    bool some = false;
     for (int c = c_lo; c < c_hi; ++c) {
       const int j = c * 64 + lane;
-      const unsigned m4 = membership(j, false);
-      const bool two = m4 != 0u && second(j);
-      const unsigned long long nz = __ballot(m4 != 0u), n2 = __ballot(two);
-      if (m4) put_entries(at + lanes_before(nz) + lanes_before(n2), j, m4, two);
+      const unsigned m = membership(j, false);
+      const bool two = m != 0u && second(j);
+      const unsigned long long nz = __ballot(m != 0u), n2 = __ballot(two);
+      if (m) put_entries(at + lanes_before(nz) + lanes_before(n2), j, m, two);
       at += __popcll(nz) + __popcll(n2);
+      some = some || (m != 0u && m != all);
     }
+    if (some) ctrl[19] = 1;
     if (wave == WAVES - 1 && lane == 0) count[0] = at;
   }
   __syncthreads();
   const int nU = __builtin_amdgcn_readfirstlane(count[0]);
   const int n_own = __builtin_amdgcn_readfirstlane(count[1]);
+  const bool mixed = __builtin_amdgcn_readfirstlane(ctrl[19]) != 0;   // not every block of the workgroup keeps every entry
 
-  // ---- order of the walk.  In ascending order the four blocks' shares of the work come in
-  // runs (the earliest frames of the union only matter to the first block, the latest only to
-  // the last), and since nobody can run more than RING entries ahead, waves would take turns
-  // waiting.  Entries with the same membership form a class (15 classes); each class is spread
-  // evenly over the walk: the p-th of c entries of a class gets the key (2p+1)/(2c), and the
-  // walk goes by ascending key.  Every stretch of the walk then holds every block's fair share.
-  // The softmax does not care about the order of the keys.  (Skipped when the two extra
-  // arrays it needs do not fit in LDS; the walk is then in ascending order.)
-  if (balance && first_slot != last_slot) {
-    unsigned* rest = ulist + n_own;                   // the own blocks keep their place in front
-    const int nR = nU - n_own;
-    unsigned* upos = ulist + union_max;               // position of an entry inside its class
-    int* ccount = (int*)(smem + LDS_TOTAL - 256);     // [16] entries per class
-    {
-      // wave w numbers the entries of classes w + 1 and w + 9
-      const unsigned ma = (unsigned)wave + 1u, mb = (unsigned)wave + 9u;   // mb = 16 for the last wave: no such class
-      int ca = 0, cb = 0;
-      for (int base = 0; base < nR; base += 64) {
-        const int i = base + lane;
-        const unsigned m4 = i < nR ? rest[i] >> 28 : 0u;
-        const unsigned long long ba = __ballot(m4 == ma), bb = __ballot(m4 == mb);
-        if (m4 == ma) upos[i] = (unsigned)(ca + lanes_before(ba));
-        if (m4 == mb) upos[i] = (unsigned)(cb + lanes_before(bb));
-        ca += __popcll(ba);
-        cb += __popcll(bb);
-      }
-      if (lane == 0) {
-        ccount[ma] = ca;
-        if (mb < 16u) ccount[mb] = cb;
-        if (wave == 0) ccount[0] = 0;
-      }
-    }
-    __syncthreads();
-    unsigned* sorted = upos + union_max;
-    for (int i = threadIdx.x; i < nR; i += 512) {
-      const unsigned e = rest[i];
-      const int m = (int)(e >> 28);
-      const int c = ccount[m];
-      const int a2 = 2 * (int)upos[i] + 1;            // my key is a2 / (2c)
-      const float rc = 1.0f / (float)c;
-      int rank = 0;
-#pragma unroll
-      for (int m2 = 1; m2 < 16; ++m2) {
-        const int c2 = ccount[m2];
-        if (c2 == 0) continue;
-        // entries j of class m2 with (2j+1)/(2 c2) < a2/(2c), i.e. (2j+1) c < a2 c2
-        const int A = a2 * c2;                        // below 2^24 (the lists fit in LDS): exact in float
-        int fl = (int)((float)A * rc);                // floor(A / c) up to one unit, put right below
-        int rem = A - fl * c;
-        if (rem < 0) {
-          fl -= 1;
-          rem += c;
-        } else if (rem >= c) {
-          fl += 1;
-          rem -= c;
-        }
-        int cntl = (fl + (rem != 0)) >> 1;            // ceil(A / c) / 2
-        // an exact tie goes to the lower class number
-        if (m2 < m && rem == 0 && (fl & 1)) cntl += 1;
-        rank += min(cntl, c2);
-      }
-      sorted[rank] = e;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nR; i += 512) rest[i] = sorted[i];
-    __syncthreads();
-  }
+  // ---- order of the walk.  In ascending order the blocks' shares of the work come in runs (the earliest frames of the
+  // union only matter to the first block, the latest only to the last), and since nobody can run more than RING entries
+  // ahead, waves would take turns waiting.  Entries with the same membership form a class, and each class is spread evenly
+  // over the walk: number p of the c entries of class m gets the key (p + u)/c, u the fraction of m times the golden
+  // section (so that the classes of one or two entries spread as well), and the walk goes by ascending key.  Every stretch
+  // of it then holds every block's fair share.  The softmax does not care about the order of the keys.
+  if (mixed && nU - n_own > 2 * RING) spread_walk(smem, ulist + n_own, nU - n_own, wave, lane);
 
   // The first entry of a group's walk is the best start for its running maxima (its own block, as a rule).  One of the
   // group's waves takes it; the others look at its scores before they start, so that none has to carry out tiles that the
   // drop rule would spare it.  Not worth a product where a wave has few tiles.
   const bool few = k * SUB < kPeekTiles * parts;
-  const unsigned my_bit = live ? (1u << (28 + qblk)) : 0u;
-  int* first = wcount;                                // [4] that entry of each group, -1: nobody looks
+  const unsigned my_bit = live ? (1u << (kMemberBit + lblock)) : 0u;
+  int* first = wcount;                                // [groups] that entry of each group, -1: nobody looks
   {
     int f = -1;
-    if (live && !few)
+    if (live && !few && parts > 1)
       for (int base = 0; base < nU; base += 64) {
         const unsigned long long m = __ballot(base + lane < nU && (ulist[min(base + lane, nU - 1)] & my_bit) != 0u);
         if (m) {
@@ -717,7 +718,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
           break;
         }
       }
-    if (part == 0 && lane == 0) first[group] = f;
+    if (part == 0 && lane == 0) first[lgroup] = f;
   }
   __syncthreads();
 
@@ -727,21 +728,20 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const unsigned char* Kbh = Kp + bh * q.n_pad * (D * 2);
   const unsigned char* Vbh = Vt + bh * q.n_pad * (D * 2);
   const int live_groups = __builtin_amdgcn_readfirstlane(ctrl[28]);
-  int first_of[4];
+  int first_of[4];                                    // (where a group has one wave nobody looks)
 #pragma unroll
   for (int w = 0; w < 4; ++w) first_of[w] = __builtin_amdgcn_readfirstlane(first[w]);
   // one wave brings the K tile of union entry u into ring slot u % RING
   auto issue_tile = [&](int u) {
     const unsigned e = (unsigned)__builtin_amdgcn_readfirstlane((int)ulist[u]);
     // how many waves will read the tile: one of each live group that holds the entry, and the others where they look
-    int readers = 0;
+    const int m = (int)(e >> kMemberBit);
+    const int holds = live_groups & (SUB == 1 ? m : 3 * ((m & 1) | (m & 2) << 1 | (m & 4) << 2 | (m & 8) << 3));
+    int readers = __builtin_popcount(holds);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int holds = (live_groups >> w) & (int)(e >> (28 + (SUB == 1 ? w : w >> 1))) & 1;
-      readers += holds + (u == first_of[w] ? holds * (parts - 1) : 0);
-    }
+    for (int w = 0; w < 4; ++w) readers += u == first_of[w] ? ((holds >> w) & 1) * (parts - 1) : 0;
     if (lane == 0) __atomic_store_n(&left[u & (RING - 1)], readers, __ATOMIC_RELAXED);   // (before the transfer, hence before the slot is published)
-    const long long j = (long long)(e & 0x3fffffu);
+    const long long j = (long long)(e & ((1u << kValidBit) - 1u));
     unsigned koff[4];
     tile_lane_offsets<256>(opaque_lane(), koff);      // (made anew each time: four registers the tile loop can use)
     dma_tile(Kbh + j * K_TILE, ring_lds + (unsigned)(u & (RING - 1)) * SLOT, koff);
@@ -840,11 +840,11 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   auto walk = [&](auto queries) {
     constexpr int NQ = decltype(queries)::value;
     float lazy = few ? 0.f : kLazy;
-    if (live && part > 0 && first_of[group] >= 0) {
-      const int u = first_of[group];
+    const int u = parts > 1 ? __builtin_amdgcn_readfirstlane(first[lgroup]) : -1;
+    if (live && part > 0 && u >= 0) {
       gave_up = !arrived(u);
       if (!gave_up) {
-        const int nv = (int)((__builtin_amdgcn_readfirstlane((int)ulist[u]) >> 22) & 63) + 1;
+        const int nv = (int)((__builtin_amdgcn_readfirstlane((int)ulist[u]) >> kValidBit) & 63) + 1;
 #pragma unroll 1
         for (int half = 0; half < 2 && 32 * half < nv; ++half) {
           f32x16 s[NQ];
@@ -874,9 +874,9 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         }
         snap = look();                                // asked for now, used after the tile: its latency hides behind the tile
         const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)e_lane, i);
-        const int nv = (int)((e >> 22) & 63u) + 1;
+        const int nv = (int)((e >> kValidBit) & 63u) + 1;
         const unsigned kaddr = kbase + (unsigned)(u & (RING - 1)) * SLOT;
-        const unsigned char* v = Vbh + (long long)(e & 0x3fffffu) * V_TILE;
+        const unsigned char* v = Vbh + (long long)(e & ((1u << kValidBit) - 1u)) * V_TILE;
         int kept = 0;
 #pragma unroll 1
         for (int half = 0; half < 2 && 32 * half < nv; ++half) {
@@ -911,7 +911,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   }
   if (gave_up && lane == 0) {
     atomicAdd(&g_wait_failures, 1ull);
-    atomicOr(&ctrl[29], 1 << group);
+    atomicOr(&ctrl[29], 1 << lgroup);
   }
   __syncthreads();                                    // everyone is done with the ring: reuse it to put the halves together
 
@@ -971,36 +971,42 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         *(float4*)(given + ((dt * 4 + a) * 64 + lane) * 16) = make_float4(x[dt][4 * a], x[dt][4 * a + 1], x[dt][4 * a + 2], x[dt][4 * a + 3]);
     ml[(part * groups + lgroup) * 64] = make_float2(sx.m, sum_across_halves(sx.l));
   };
-  if (part == 0) give(o[1], st[1]);
-  else if (part == 1) give(o[0], st[0]);
-  __syncthreads();
-  if (part > 1) return;                               // (put together with another wave's)
-  const bool failed = (ctrl[29] >> group) & 1;        // a wait ran out: say so with NaN rather than with wrong numbers
-  if (32 * part >= q_valid) {
-    // 32 pad slots and nothing else: their rows of the reordered output are zeroed (in the original
-    // order they do not exist)
-    if (has_block && !direct) {
-      const long long row0 = qb * BLOCK + BS * qsub + 32 * part;
-#pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int row = it * 4 + (lane >> 4), ch = lane & 15;
-        *(uint4*)(Op + (row0 + row) * (D * 2) + ch * 16) = make_uint4(0u, 0u, 0u, 0u);
-      }
-      if (lse && lane < 32) lse[row0 + lane] = 0.f;
-    }
-    return;
+  if (parts > 1) {
+    if (part == 0) give(o[1], st[1]);
+    else if (part == 1) give(o[0], st[0]);
+    __syncthreads();
+    if (part > 1) return;                             // (put together with another wave's)
   }
-
-  // ---- normalise, convert, stage through LDS, write rows of 256 B
-  auto finish = [&](const f32x16 (&x)[4], const Soft& sx) {
-    const float2 other = ml[((part ^ 1) * groups + lgroup) * 64];
-    const float l_mine = sum_across_halves(sx.l), m_all = fmaxf(sx.m, other.x);
+  const bool failed = (ctrl[29] >> lgroup) & 1;        // a wait ran out: say so with NaN rather than with wrong numbers
+  unsigned char* const o0 = Op + row_base(q.out);
+  // ---- normalise, convert, stage through LDS, write rows of 256 B.  x, sx: 32 queries (number h) of mine, or, with
+  // `joined`, what I have of them, the rest being the partner's
+  auto finish = [&](int h, const f32x16 (&x)[4], const Soft& sx, auto joined) {
+    unsigned char* const turn = joined ? taken : given;
+    if (32 * h >= q_valid) {
+      // 32 pad slots and nothing else: their rows of the reordered output are zeroed (in the original
+      // order they do not exist)
+      if (has_block && !direct) {
+        const long long row0 = qb * BLOCK + BS * qsub + 32 * h;
+#pragma unroll
+        for (int it = 0; it < 8; ++it) {
+          const int row = it * 4 + (lane >> 4), ch = lane & 15;
+          *(uint4*)(Op + (row0 + row) * (D * 2) + ch * 16) = make_uint4(0u, 0u, 0u, 0u);
+        }
+        if (lse && lane < 32) lse[row0 + lane] = 0.f;
+      }
+      return;
+    }
+    const float l_mine = sum_across_halves(sx.l);
+    float2 other = make_float2(-FLT_MAX, 0.f);
+    if constexpr (joined) other = ml[((part ^ 1) * groups + lgroup) * 64];
+    const float m_all = fmaxf(sx.m, other.x);
     const float a_mine = l_mine > 0.f ? __builtin_amdgcn_exp2f((sx.m - m_all) * kC2) : 0.f;
     const float a_other = other.y > 0.f ? __builtin_amdgcn_exp2f((other.x - m_all) * kC2) : 0.f;
     const float lt = l_mine * a_mine + other.y * a_other;
     const float inv = lt > 0.f ? 1.0f / lt : 0.f;     // 0 only in pad query slots whose waves skipped every tile, for an empty list and
-    const bool none = lt == 0.f && before > 0 && 32 * part + r < q_valid;   // for keys that all score minus infinity: no softmax is defined, NaN
-    if (lse && hh == 0) lse[qb * BLOCK + BS * qsub + 32 * part + r] = m_all * kScale + __logf(lt);
+    const bool none = lt == 0.f && before > 0 && 32 * h + r < q_valid;   // for keys that all score minus infinity: no softmax is defined, NaN
+    if (lse && hh == 0) lse[qb * BLOCK + BS * qsub + 32 * h + r] = m_all * kScale + __logf(lt);
     const float f_mine = a_mine * inv, f_other = a_other * inv;
     uint2 w2[4][4];
 #pragma unroll
@@ -1008,7 +1014,8 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         // registers 4a..4a+3 are d = 32dt + 8a + 4hh + 0..3 of query r
-        const float4 y = *(const float4*)(taken + ((dt * 4 + a) * 64 + lane) * 16);
+        float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (joined) y = *(const float4*)(taken + ((dt * 4 + a) * 64 + lane) * 16);
         f32x2 v0 = {x[dt][4 * a] * f_mine + y.x * f_other, x[dt][4 * a + 1] * f_mine + y.y * f_other};
         f32x2 v1 = {x[dt][4 * a + 2] * f_mine + y.z * f_other, x[dt][4 * a + 3] * f_mine + y.w * f_other};
         bf16x2 b0 = __builtin_convertvector(v0, bf16x2);
@@ -1019,93 +1026,65 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) *(uint2*)(taken + r * O_STRIDE + (32 * dt + 8 * a + 4 * hh) * 2) = w2[dt][a];
-  };
-  if (part) finish(o[1], st[1]);
-  else finish(o[0], st[0]);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  unsigned char* const o0 = Op + row_base(q.out);
-  auto write_rows = [&](auto there) {
+      for (int a = 0; a < 4; ++a) *(uint2*)(turn + r * O_STRIDE + (32 * dt + 8 * a + 4 * hh) * 2) = w2[dt][a];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    auto write_rows = [&](auto there) {
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int row = it * 4 + (lane >> 4), ch = lane & 15, slot = BS * qsub + 32 * part + row;
-      if (!there || slot < rows_there)
-        *(uint4*)(o0 + row_after(q.out, slot, there) + ch * 16) = *(const uint4*)(taken + row * O_STRIDE + ch * 16);
-    }
+      for (int it = 0; it < 8; ++it) {
+        const int row = it * 4 + (lane >> 4), ch = lane & 15, slot = BS * qsub + 32 * h + row;
+        if (!there || slot < rows_there)
+          *(uint4*)(o0 + row_after(q.out, slot, there) + ch * 16) = *(const uint4*)(turn + row * O_STRIDE + ch * 16);
+      }
+    };
+    if (direct) write_rows(std::true_type());
+    else write_rows(std::false_type());
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
-  if (direct) write_rows(std::true_type());
-  else write_rows(std::false_type());
-}
-
-// Which workgroups of a launch are whole (the first `wide`) and into how many shares (2^split) the others go.
-//
-// A workgroup fills a CU, so a launch of few comes in rounds of kCUs, and the last round takes as long as a full one
-// however few are in it.  A share of half of the queries puts twice as many waves to each list.  It is done in about
-// 0.6 of the time (key tiles are shared by fewer, and a ring of eight tiles looks less far ahead of more waves), a
-// quarter in about 0.45, so:
-//   - halves where the last round is at most half full (two halves fit where one whole did): 120 workgroups of 60 tiles
-//     158 -> 121 us, 315 of 315 tiles 1197 -> 988 us, 360 of 15 tiles 156 -> 139 us (times of da_forward); at 168 and 240
-//     in the last round 105 -> 119 and 177 -> 201 us;
-//   - quarters where all of the launch is at most a quarter of a round: 60 of 240 tiles 415 -> 188 us (halves 257), 15
-//     of 15 tiles 77 -> 57 us (63);
-//   - nothing after more than kMaxRounds rounds: workgroups differ in length, and by then they no longer end together
-//     (1575 workgroups, 39 in the last round: 4790 us either way).
-// Only the last round is shared out.  Halves for all of a launch are better still on some launches of one to two rounds (294
-// dense workgroups 1920 -> 1682 us, 360 of 240 tiles 902 -> 821 us) and worse on others, and quarters for all of 441 dense ones
-// cost 1975 -> 2454 us; what tells them apart is not known.
-struct Share {
-  long long wide, grid;
-  int split;
-};
-constexpr int kCUs = 256;
-constexpr int kMaxRounds = 4;
-inline Share share_out(const Geo& q) {
-  const int per_frame = q.gh * q.gw;
-  const TailPlan plan = tail_plan(q, 4 * BS / q.block);
-  const long long per_head = 8LL * ((per_frame + 7) / 8) * plan.full_groups + plan.tail_wgs;
-  const long long bh = (long long)q.B * q.H, total = bh * per_head;
-  const long long live = bh * ((long long)per_frame * plan.full_groups + plan.tail_wgs);   // (the others leave at once)
-  const int last_round = (int)(live % kCUs);
-  Share s = {total, total, 0};
-  if (live > kMaxRounds * kCUs || last_round == 0 || 2 * last_round > kCUs) return s;
-  s.split = 4 * live <= kCUs ? 2 : 1;
-  // the last `last_round` live ones are shared out
-  for (int got = 0; got < last_round;) {
-    const long long n = --s.wide % per_head - plan.tail_wgs;
-    got += n < 0 || (n & 7) + 8 * ((n >> 3) / plan.full_groups) < per_frame;
+  if (parts == 1) {
+    finish(0, o[0], st[0], std::false_type());
+    finish(1, o[1], st[1], std::false_type());
+  } else if (part) {
+    finish(1, o[1], st[1], std::true_type());
+  } else {
+    finish(0, o[0], st[0], std::true_type());
   }
-  s.grid = s.wide + (((total - s.wide + 7) / 8 * 8) << s.split);
-  return s;
 }
 
 }  // namespace ring
 
-// LDS left beside the ring: four bitmaps of g bits, the union list (at most min(g, 4k) entries)
-// and, for the balanced walk, two more arrays of that length.
-// 0: the kernel cannot run this problem; 1: it can, walking in ascending order; 2: balanced walk.
+// LDS left beside the ring, where a workgroup takes 8 / 2^split groups of 64 queries: their blocks' bitmaps of g bits and the
+// union list.
+static long long aux_bytes(const Geo& q, bool any_length, int split) {
+  const int sub = q.block / ring::BS;
+  const long long blocks = 8 / sub >> split ? 8 / sub >> split : 1;
+  const long long union_max = sub * (any_length ? (long long)q.g : q.g < blocks * q.k ? q.g : blocks * q.k);
+  return blocks * 4 * ((q.g + 31) / 32) + 4 * union_max + 512;
+}
+
+// 0: the kernel cannot run this problem, else 1.
 int attn_bf16_ring_fits(const Geo& q, bool any_length) {
   if (q.block != ring::BS && q.block != 2 * ring::BS) return 0;
   const int sub = q.block / ring::BS, fg = 4 / sub;
-  if ((long long)q.g * sub >= (1 << 22)) return 0;
-  long long union_max = sub * ((long long)q.g < (long long)fg * q.k || any_length ? q.g : (long long)fg * q.k);
-  long long base = 4LL * 4 * ((q.g + 31) / 32) + 4 * union_max + 512;
-  if (base > ring::AUX_BYTES) return 0;
-  return base + 8 * union_max <= ring::AUX_BYTES ? 2 : 1;
+  if ((long long)q.g * sub >= (1 << ring::kValidBit)) return 0;
+  const long long union_max = sub * ((long long)q.g < (long long)fg * q.k || any_length ? q.g : (long long)fg * q.k);
+  return 4LL * 4 * ((q.g + 31) / 32) + 4 * union_max + 512 <= ring::AUX_BYTES;
 }
 
 hipError_t launch_attn_bf16_ring(const Geo& q, const void* Qp, const void* Kp, const void* Vt, const int32_t* idx,
                                  const int32_t* row_ptr, long long cap, void* Op, float* lse, bool direct,
                                  unsigned long long* tile_counts, hipStream_t s) {
   const int sub = q.block / ring::BS;
-  const ring::Share share = ring::share_out(q);
-  const unsigned grid = (unsigned)share.grid;
-  const int balance = attn_bf16_ring_fits(q, row_ptr != nullptr) == 2 ? 1 : 0;
+  int least = 0;
+  while (least < 1 && aux_bytes(q, row_ptr != nullptr, least) > ring::AUX_BYTES) ++least;
+  const int fg = 8 / sub, per_frame = q.gh * q.gw;
+  const ring::Share share = ring::share_out((long long)q.B * q.H * ring::units_per_head(q.T, fg, per_frame), (long long)q.k * sub, least);
   const float skip = log2f((float)q.k * (float)q.block) + ring::kDropLog2;
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), 0, s, q, (const unsigned char*)Qp, (const unsigned char*)Kp,
-                       (const unsigned char*)Vt, idx, row_ptr, cap, (unsigned char*)Op, lse, balance, skip, direct ? 1 : 0,
-                       (int)share.wide, share.split, tile_counts);
+    hipLaunchKernelGGL(kernel, dim3(share.grid), dim3(512), 0, s, q, (const unsigned char*)Qp, (const unsigned char*)Kp,
+                       (const unsigned char*)Vt, idx, row_ptr, cap, (unsigned char*)Op, lse, skip, direct ? 1 : 0,
+                       share, tile_counts);
   };
   if (sub == 1 && !row_ptr) go(ring::attn_bf16_ring_kernel<1, false>);
   else if (sub == 1) go(ring::attn_bf16_ring_kernel<1, true>);

@@ -1,0 +1,85 @@
+"""How the bf16 attention deals a launch out: every query block of a head belongs to one place of one unit, every share of
+every unit to one workgroup, the shares of a unit stay on one XCD (workgroups go to the XCDs in turn), and no more than a
+few workgroups have nothing to do.  The kernel's own functions, compiled for the CPU."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_14708_amd", "csrc")
+SOURCE = """#include "ring_turns.h"
+using namespace da::ring;
+extern "C" int units(int T, int fg, int per_frame) { return units_per_head(T, fg, per_frame); }
+extern "C" void place(int n, int T, int log_fg, int per_frame, int* out) {
+  const UnitPlace u = unit_place(n, T, log_fg, per_frame);
+  out[0] = u.pos0; out[1] = u.frame0; out[2] = u.lg;
+}
+extern "C" void share(long long total, long long tiles, int least, int* out) {
+  const Share s = share_out(total, tiles, least);
+  out[0] = s.first; out[1] = s.split[0]; out[2] = s.split[1]; out[3] = (int)s.grid;
+}
+extern "C" void shares(long long total, long long tiles, int least, int grid, int* out) {
+  const Share s = share_out(total, tiles, least);
+  for (int b = 0; b < grid; ++b) {
+    const ShareOf w = share_of(s, b);
+    out[3 * b] = w.unit; out[3 * b + 1] = w.lsub; out[3 * b + 2] = w.sub;
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("unit_places")
+    src, out = d / "unit_places.cpp", d / "libunit_places.so"
+    src.write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(out)], check=True)
+    f = ctypes.CDLL(str(out))
+    f.share.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_void_p]
+    f.shares.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    return f
+
+
+@pytest.mark.parametrize("log_fg", [2, 3])
+@pytest.mark.parametrize("per_frame", [1, 2, 7, 8, 28, 60])
+def test_every_block_has_one_place(lib, log_fg, per_frame):
+    fg, out = 1 << log_fg, (ctypes.c_int * 3)()
+    for T in list(range(1, 36)) + [65]:
+        seen = set()
+        units = lib.units(T, fg, per_frame)
+        for n in range(units):
+            lib.place(n, T, log_fg, per_frame, out)
+            pos0, frame0, lg = out
+            blocks = [(pos0 + (w >> lg), frame0 + (w & ((1 << lg) - 1))) for w in range(fg)]
+            live = [b for b in blocks if b[0] < per_frame]
+            assert blocks[:len(live)] == live and live          # empty places only at the end
+            assert all(f < T for _, f in live)
+            assert not seen & set(live)
+            seen |= set(live)
+        assert len(seen) == T * per_frame
+        assert units <= T * per_frame // fg + log_fg + 1        # at most one unit with empty places per power of two
+
+
+@pytest.mark.parametrize("least", [0, 1])
+@pytest.mark.parametrize("tiles", [3, 200])
+def test_every_share_has_one_workgroup(lib, tiles, least):
+    s = (ctypes.c_int * 4)()
+    for total in list(range(1, 540)) + [1023, 1024, 1025, 5952]:
+        lib.share(total, tiles, least, s)
+        first, split0, split1, grid = s
+        assert min(split0, split1) >= least and grid > 0
+        out = (ctypes.c_int * (3 * grid))()
+        lib.shares(total, tiles, least, grid, out)
+        seen, xcd, idle = set(), {}, 0
+        for b in range(grid):
+            unit, lsub, sub = out[3 * b:3 * b + 3]
+            if unit >= total:
+                idle += 1
+                continue
+            assert lsub == (split0 if unit < first else split1) and 0 <= sub < 1 << lsub
+            assert (unit, sub) not in seen
+            seen.add((unit, sub))
+            assert xcd.setdefault(unit, b % 8) == b % 8
+        assert len(seen) == sum(1 << (split0 if u < first else split1) for u in range(total))
+        assert idle <= 7 << max(split0, split1)
