@@ -42,10 +42,13 @@
 //   left[s]    how many waves have yet to read the tile in slot s (set when the tile is asked for: one
 //              wave of each group of queries that holds the entry; every reader takes one off when it
 //              is through): at zero the slot may be overwritten
-//   next_load  entries are requested strictly in order, entry L once its slot L % 8 is free, by the waves
-//              that are waiting for a tile: the one that notices first claims it with a compare-and-
-//              swap, waits for the load (it is idle anyway, or at the top of its next trip) and
+//   next_load  entries are requested strictly in order, entry L into any slot that is free, by the waves
+//              that are waiting for a tile: the one that notices first claims the slot with a compare-and-
+//              swap and the entry with an add, waits for the load (it is idle anyway, or at the top of its next trip) and
 //              publishes it.  Waves that have a tile to work on do not look for room.
+// (With entry L tied to slot L % 8, one slow reader of entry L - 8 kept the others waiting whatever else was free: 24 heads x
+// 1980 blocks 11.96 -> 11.77 ms, three heads of 65 frames 5.41 -> 5.31, 8 heads x 252 blocks stage by stage 319 -> 308 us; and
+// requests four loads to a value of m0 instead of one, with a vector address each: 12.14 -> 11.96 ms, 5.50 -> 5.41, 324 -> 319.)
 // A wave reads all of this with one LDS access per poll.  Every wait is bounded: if a tile does
 // not show up the wave gives up (its output rows are then NaN, but the kernel always ends).
 //
@@ -100,6 +103,7 @@ constexpr float kC2 = 0.08838834764831845f * 1.4426950408889634f;   // log2(e)/s
 constexpr float kLazy = 8.0f;                     // move the running max only past this many powers of two
 constexpr float kDropLog2 = 14.0f;                // all keys dropped from a row together weigh less than 2^-14 of its largest term
 constexpr int kSpinLimit = 1 << 20;
+constexpr int kClaimed = 1 << 20;                    // a slot's reader count while its entry is not known yet
 constexpr int kValidBit = 18, kMemberBit = 24;       // fields of a union entry (key sub-blocks are numbered below 2^18)
 constexpr int kPeekTiles = 8;                       // lists of at least so many tiles per wave: all waves of a group look at the first one
 
@@ -134,9 +138,21 @@ __device__ __forceinline__ void dma16(const unsigned char* g, unsigned lds_addr)
       : "v"(g), "s"(lds_addr)
       : "memory");
 }
+// The same for a tile, four loads to a value of m0 (the instruction's offset counts on both sides).
 __device__ __forceinline__ void dma_tile(const unsigned char* src, unsigned lds_addr, const unsigned (&loff)[4]) {
 #pragma unroll
-  for (int it = 0; it < 16; ++it) dma16(src + it * 1024 + loff[it & 3], lds_addr + it * 1024);
+  for (int b = 0; b < 4; ++b) {
+    unsigned keep;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %6\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %5\n\t"
+        "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+        "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
+        "global_load_lds_dwordx4 %4, %5 offset:3072\n\ts_mov_b32 m0, %0"
+        : "=&s"(keep)
+        : "v"(loff[0]), "v"(loff[1]), "v"(loff[2]), "v"(loff[3]), "s"(src + b * 4096), "s"(lds_addr + b * 4096)
+        : "memory");
+  }
 }
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
@@ -732,7 +748,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 #pragma unroll
   for (int w = 0; w < 4; ++w) first_of[w] = __builtin_amdgcn_readfirstlane(first[w]);
   // one wave brings the K tile of union entry u into ring slot u % RING
-  auto issue_tile = [&](int u) {
+  auto issue_tile = [&](int u, int slot) {
     const unsigned e = (unsigned)__builtin_amdgcn_readfirstlane((int)ulist[u]);
     // how many waves will read the tile: one of each live group that holds the entry, and the others where they look
     const int m = (int)(e >> kMemberBit);
@@ -740,19 +756,20 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     int readers = __builtin_popcount(holds);
 #pragma unroll
     for (int w = 0; w < 4; ++w) readers += u == first_of[w] ? ((holds >> w) & 1) * (parts - 1) : 0;
-    if (lane == 0) __atomic_store_n(&left[u & (RING - 1)], readers, __ATOMIC_RELAXED);   // (before the transfer, hence before the slot is published)
+    if (lane == 0) __atomic_store_n(&left[slot], readers, __ATOMIC_RELAXED);   // (before the transfer, hence before the slot is published)
     const long long j = (long long)(e & ((1u << kValidBit) - 1u));
     unsigned koff[4];
     tile_lane_offsets<256>(opaque_lane(), koff);      // (made anew each time: four registers the tile loop can use)
-    dma_tile(Kbh + j * K_TILE, ring_lds + (unsigned)(u & (RING - 1)) * SLOT, koff);
+    dma_tile(Kbh + j * K_TILE, ring_lds + (unsigned)slot * SLOT, koff);
   };
-  int pending = -1;
+  int pending = -1;                                   // entry I have asked for, and the slot it goes to
+  int pending_slot = 0;
   // a tile this wave has requested becomes visible to the others once it has landed
   auto publish = [&]() {
     const int pd = __builtin_amdgcn_readfirstlane(pending);   // (the same in every lane; says so to the compiler)
     if (pd >= 0) {
       wait_vm0();
-      if (lane == 0) __atomic_store_n(&ready[pd & (RING - 1)], pd, __ATOMIC_RELAXED);
+      if (lane == 0) __atomic_store_n(&ready[__builtin_amdgcn_readfirstlane(pending_slot)], pd, __ATOMIC_RELAXED);
       pending = -1;
     }
   };
@@ -785,47 +802,52 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(ctrl_lds));   // (as one constant it would be kept in a register)
     return __atomic_load_n((const lds_int*)(uintptr_t)at, __ATOMIC_RELAXED);
   };
-  // request the next tile if the ring has room, judging by a look c (which may be old: then the
+  // request the next tile if there is a free slot, judging by a look c (which may be old: then the
   // compare-and-swap fails or the room is underestimated, both harmless)
   auto service = [&](int c) {
     if (__builtin_amdgcn_readfirstlane(pending) >= 0) return;   // at most one request of mine in flight
-    const int L = __builtin_amdgcn_readlane(c, 16);
-    if (L >= nU) return;
-    // its slot is free once every reader of the entry it holds has left it (and that entry did arrive)
-    const int sl = L & (RING - 1);
-    if (__builtin_amdgcn_readlane(c, 8 + sl) != 0) return;
-    if (L >= RING && __builtin_amdgcn_readlane(c, sl) != L - RING) return;
-    int got = L + 1;
-    if (lane == 0) got = atomicCAS(next_load, L, L + 1);
+    if (__builtin_amdgcn_readlane(c, 16) >= nU) return;
+    const unsigned free = (unsigned)(__ballot(c == 0) >> 8) & ((1u << RING) - 1u);   // slots that nobody has yet to read
+    if (!free) return;
+    const int slot = __builtin_ctz(free);
+    int got = 0;
+    if (lane == 0) {
+      got = atomicCAS(&left[slot], 0, kClaimed) == 0 ? atomicAdd(next_load, 1) : -1;
+      if (got >= nU) __atomic_store_n(&left[slot], 0, __ATOMIC_RELAXED);
+    }
     got = __builtin_amdgcn_readfirstlane(got);
-    if (got != L) return;
-    issue_tile(L);
-    pending = L;
+    if (got < 0 || got >= nU) return;
+    issue_tile(got, slot);
+    pending = got;
+    pending_slot = slot;
   };
   bool gave_up = false;
   int snap = look();
-  // wait until entry u is in its slot (false: the bounded wait ran out)
-  auto arrived = [&](int u) -> bool {
-    const int slot_i = u & (RING - 1);
+  // which slot of a look holds entry u (bit mask)
+  auto slot_of = [&](int u) -> unsigned { return (unsigned)__ballot(snap == u) & ((1u << RING) - 1u); };
+  // wait until entry u is in a slot, and say in which (-1: the bounded wait ran out)
+  auto arrived = [&](int u) -> int {
     publish();                                        // my last request has had a whole tile's time to land
-    if (__builtin_amdgcn_readlane(snap, slot_i) == u) return true;
+    unsigned in = slot_of(u);
+    if (in) return __builtin_ctz(in);
     int spins = 0;
     for (;;) {
       snap = look();
       service(snap);
-      if (__builtin_amdgcn_readlane(snap, slot_i) == u) return true;
+      in = slot_of(u);
+      if (in) return __builtin_ctz(in);
       if (__builtin_amdgcn_readfirstlane(pending) >= 0) {
         publish();                                    // idle anyway: wait for my own request and hand it over
       } else {
         __builtin_amdgcn_s_sleep(1);
-        if (++spins > kSpinLimit) return false;
+        if (++spins > kSpinLimit) return -1;
       }
     }
   };
-  // my reads of the slot of entry u are complete: one reader less
-  auto leave = [&](int u) {
+  // my reads of a slot are complete: one reader less
+  auto leave = [&](int slot) {
     wait_lds();
-    if (lane == 0) atomicSub(&left[u & (RING - 1)], 1);
+    if (lane == 0) atomicSub(&left[slot], 1);
   };
   const bool two = q_valid > 32;                      // else the second 32 queries are all pad slots
   // Tiles of 32 queries and 64 keys gone through and, from bit 16 on, half tiles carried out, the only half of a tile with at
@@ -842,17 +864,18 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
     float lazy = few ? 0.f : kLazy;
     const int u = parts > 1 ? __builtin_amdgcn_readfirstlane(first[lgroup]) : -1;
     if (live && part > 0 && u >= 0) {
-      gave_up = !arrived(u);
+      const int slot = arrived(u);
+      gave_up = slot < 0;
       if (!gave_up) {
         const int nv = (int)((__builtin_amdgcn_readfirstlane((int)ulist[u]) >> kValidBit) & 63) + 1;
 #pragma unroll 1
         for (int half = 0; half < 2 && 32 * half < nv; ++half) {
           f32x16 s[NQ];
-          half_scores<NQ>(kbase + (unsigned)(u & (RING - 1)) * SLOT + half * (SLOT / 2), nv - 32 * half, qf, s);
+          half_scores<NQ>(kbase + (unsigned)slot * SLOT + half * (SLOT / 2), nv - 32 * half, qf, s);
 #pragma unroll
           for (int h = 0; h < NQ; ++h) st[h].top = fmaxf(st[h].top, max_across_halves(max16(s[h], -INFINITY)));
         }
-        leave(u);
+        leave(slot);
       }
     }
     // The walk, 64 entries at a time: lane i holds entry base + i, a ballot tells which of them are my group's, a second
@@ -868,14 +891,15 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         const int i = (int)__builtin_ctzll(mine);
         mine &= mine - 1;
         const int u = base + i;
-        if (!arrived(u)) {
+        const int slot = arrived(u);
+        if (slot < 0) {
           gave_up = true;
           break;
         }
         snap = look();                                // asked for now, used after the tile: its latency hides behind the tile
         const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)e_lane, i);
         const int nv = (int)((e >> kValidBit) & 63u) + 1;
-        const unsigned kaddr = kbase + (unsigned)(u & (RING - 1)) * SLOT;
+        const unsigned kaddr = kbase + (unsigned)slot * SLOT;
         const unsigned char* v = Vbh + (long long)(e & ((1u << kValidBit) - 1u)) * V_TILE;
         int kept = 0;
 #pragma unroll 1
@@ -884,7 +908,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         }
         lazy = kLazy;
         tally += NQ + ((unsigned)(nv > 32 ? NQ * kept : 2 * NQ * kept) << 16);
-        leave(u);
+        leave(slot);
         // (Only waves that are waiting for a tile ask for tiles: having every wave look for room after each of
         // its tiles cost the busy ones more than the earlier requests saved.)
       }
