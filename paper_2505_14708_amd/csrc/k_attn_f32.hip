@@ -1,7 +1,7 @@
 // SparseAttn for float32 storage, blocks of 64 slots, d = 64 or 128: float32 throughout, on the float32 matrix
 // instructions (v_mfma_f32_16x16x4_f32: exact products, one rounding per term, like a chain of fused multiply-adds).
 //
-// A workgroup is half a query block, 32 queries; its waves share out the keys, 16 (a quarter of a block) at a time, and
+// A workgroup is half a query block, 32 queries, or a quarter where that fills the chip better (f32_share.h); its waves share out the keys, 16 (a quarter of a block) at a time, and
 // keep a running maximum, a sum and an output of their own, which are put together at the end.  A key is then wanted by
 // one wave only, so K and V go straight from memory to that wave's registers: no tile in LDS, no barrier in the loop.
 // Wave: 16 keys x 32 queries per step, the query on the lane axis of both products:
@@ -22,6 +22,7 @@
 #include <float.h>
 #include <math.h>
 #include "da_internal.h"
+#include "f32_share.h"
 
 namespace da {
 namespace {
@@ -46,26 +47,25 @@ __device__ __forceinline__ float query_sum(float x) {
 // VT: V comes block-transposed (DA_REORDER_VT); otherwise K and V alike are rows that q.in says where to find.
 constexpr int W = 4;                         // waves of a workgroup
 
-template <int D, bool VT>
-__global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float* __restrict__ Q, const float* __restrict__ K,
-                                                             const float* __restrict__ V, const int32_t* __restrict__ idx,
-                                                             const int32_t* __restrict__ row_ptr, long long cap,
-                                                             float* __restrict__ O, float* __restrict__ lse) {
+// What a workgroup shares with itself: the waves' outputs, references and normalisers
+template <int D>
+struct Parts {
+  float4 out[W][2 * (D / 16)][64];
+  float2 ml[W][2][16];
+};
+
+// 16 NH queries, from slot `first_query` of query block qb on
+template <int D, bool VT, int NH>
+__device__ __forceinline__ void attend(const Geo& q, const float* __restrict__ Q, const float* __restrict__ K,
+                                       const float* __restrict__ V, const int32_t* __restrict__ idx,
+                                       const int32_t* __restrict__ row_ptr, long long cap, float* __restrict__ O,
+                                       float* __restrict__ lse, long long qb, int first_query, Parts<D>& parts) {
   constexpr int NU = D / 16;                 // 16-byte pieces of a K or Q row per lane
   constexpr int NDT = D / 16;                // accumulators of the second product per 16 queries
-  constexpr int NG = 2 * NDT;                // 16-byte groups of a lane's output
-  __shared__ float4 part[W][NG][64];
-  __shared__ float2 part_ml[W][2][16];
-  // workgroups are dealt round-robin to the 8 XCDs: each gets a stretch of consecutive query blocks, whose lists have
-  // much in common
-  const long long total = 2LL * q.B * q.H * q.g, chunk = (total + 7) >> 3;
-  const long long unit = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
-  if ((blockIdx.x >> 3) >= chunk || unit >= total) return;
+  constexpr int NG = NH * NDT;               // 16-byte groups of a lane's output
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, kk = lane >> 4;
-  const long long qb = unit >> 1;
-  const int half = (int)(unit & 1);
   const long long bh = qb / q.g;
   const int i_blk = (int)(qb - bh * q.g);
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
@@ -73,22 +73,22 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
   // query rows (slots past the valid ones exist only where the tensors are in block order)
   const BlockPos qp = block_pos(q, i_blk);
   const int q_valid = q.reordered ? 64 : qp.vh * qp.vw;      // slots with a row of their own
-  if (32 * half >= q_valid) return;                          // (the whole workgroup)
+  if (first_query >= q_valid) return;                         // (the whole workgroup)
   const long long q_first = block_first_row(q, i_blk, qp);
   const int q_pitch = block_row_pitch(q, qp);
   auto query_row = [&](int slot) -> long long { return q_first + (long long)(slot / qp.vw) * q_pitch + slot % qp.vw; };
-  float4 qv[2][NU];
+  float4 qv[NH][NU];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int slot = 32 * half + 16 * h + r16;
+  for (int h = 0; h < NH; ++h) {
+    const int slot = first_query + 16 * h + r16;
     const float* qrow = Q + row_offset(q.in, q.H, bh, query_row(slot < q_valid ? slot : 0)) + 4 * kk;
 #pragma unroll
     for (int u = 0; u < NU; ++u) qv[h][u] = *(const float4*)(qrow + 16 * u);
   }
-  f32x4 o[2][NDT];
-  float m[2], l[2];
+  f32x4 o[NH][NDT];
+  float m[NH], l[NH];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < NH; ++h) {
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) o[h][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     l[h] = 0.f;
@@ -174,21 +174,23 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
   // The reference of a wave that has keys starts at the lowest finite value, not at minus infinity: all scores of its first
   // steps may be minus infinity (finite operands whose product leaves the range), and those keys weigh exp2(-inf) = 0,
   // not exp2(-inf + inf).
-  m[0] = m[1] = more ? -FLT_MAX : -INFINITY;
+#pragma unroll
+  for (int h = 0; h < NH; ++h) m[h] = more ? -FLT_MAX : -INFINITY;
   if (more) fetch_k();
   while (more) {
     fetch_v();
     __builtin_amdgcn_sched_barrier(0);
     const int keys = nv - first_key;                         // valid keys of this step (16 or more: all of them)
-    f32x4 s[2];
-    s[0] = s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 s[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       const float a[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
 #pragma unroll
       for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < NH; ++h) {
           const float b = c == 0 ? qv[h][u].x : c == 1 ? qv[h][u].y : c == 2 ? qv[h][u].z : qv[h][u].w;
           s[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b, s[h], 0, 0, 0);
         }
@@ -196,18 +198,24 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
     if (keys < 16) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (4 * kk + r >= keys) s[0][r] = s[1][r] = -INFINITY;   // pad keys are never attended
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+          if (4 * kk + r >= keys) s[h][r] = -INFINITY;       // pad keys are never attended
     }
     more = advance();
     __builtin_amdgcn_sched_barrier(0);
     fetch_k();                                               // (after the last step its own once more: what is in flight is then the same on every path)
     __builtin_amdgcn_sched_barrier(0);
-    float mx[2];
+    float mx[NH];
+    bool moves = false;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) mx[h] = query_max(fmaxf(fmaxf(s[h][0], s[h][1]), fmaxf(s[h][2], s[h][3])));
-    if (__any(mx[0] > m[0] || mx[1] > m[1])) {
+    for (int h = 0; h < NH; ++h) {
+      mx[h] = query_max(fmaxf(fmaxf(s[h][0], s[h][1]), fmaxf(s[h][2], s[h][3])));
+      moves = moves || mx[h] > m[h];
+    }
+    if (__any(moves)) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < NH; ++h) {
         const float m_new = fmaxf(m[h], mx[h]);
         const float alpha = m[h] == m_new ? 1.f : exp2f((m[h] - m_new) * scale_log2);
         m[h] = m_new;
@@ -217,7 +225,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
       }
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < NH; ++h)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         s[h][r] = exp2f((s[h][r] - m[h]) * scale_log2);
@@ -237,15 +245,15 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
       for (int dt = 0; dt < NDT; ++dt) {
         const float a = VT ? vr[dt & 3][dt >> 2][r] : vr[r][dt >> 2][dt & 3];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) o[h][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, s[h][r], o[h][dt], 0, 0, 0);
+        for (int h = 0; h < NH; ++h) o[h][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, s[h][r], o[h][dt], 0, 0, 0);
       }
   }
 
   // every wave hands over what it has; wave w puts together its share of the output's groups
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < NH; ++h) {
     const float lt = query_sum(l[h]);
-    if (kk == 0) part_ml[wave][h][r16] = make_float2(m[h], lt);
+    if (kk == 0) parts.ml[wave][h][r16] = make_float2(m[h], lt);
     // register r of accumulator dt is channel (d/16)(4 kk + r) + dt: with f = (d/16) r + dt the lane holds channels
     // (d/4) kk + f of its query
 #pragma unroll
@@ -253,24 +261,24 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
       float x[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[i] = o[h][(4 * gi + i) % NDT][(4 * gi + i) / NDT];
-      part[wave][h * NDT + gi][lane] = make_float4(x[0], x[1], x[2], x[3]);
+      parts.out[wave][h * NDT + gi][lane] = make_float4(x[0], x[1], x[2], x[3]);
     }
   }
   __syncthreads();
   constexpr int SHARE = NG / W;
-  const int h = wave / (W / 2);                              // which 16 queries the wave's groups belong to
+  const int h = wave / (W / NH);                             // which 16 queries the wave's groups belong to
   float a[W], m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
-  for (int w = 0; w < W; ++w) m_all = fmaxf(m_all, part_ml[w][h][r16].x);
+  for (int w = 0; w < W; ++w) m_all = fmaxf(m_all, parts.ml[w][h][r16].x);
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    const float2 ml = part_ml[w][h][r16];
+    const float2 ml = parts.ml[w][h][r16];
     a[w] = ml.y > 0.f ? exp2f((ml.x - m_all) * scale_log2) : 0.f;
     l_all += ml.y * a[w];
   }
   // an empty list: zero rows; keys that all score minus infinity (or NaN): no softmax is defined, NaN
   const float inv = l_all > 0.f ? 1.0f / l_all : m_all == -INFINITY ? 0.f : NAN;
-  const int slot = 32 * half + 16 * h + r16;
+  const int slot = first_query + 16 * h + r16;
   if (slot >= q_valid) return;
   float* orow = O + row_offset(q.out, q.H, bh, query_row(slot)) + (D / 4) * kk;
 #pragma unroll
@@ -279,7 +287,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
     float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const float4 x = part[w][grp][lane];
+      const float4 x = parts.out[w][grp][lane];
       y.x += x.x * a[w];
       y.y += x.y * a[w];
       y.z += x.z * a[w];
@@ -287,8 +295,21 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
     }
     *(float4*)(orow + 4 * (grp - h * NDT)) = make_float4(y.x * inv, y.y * inv, y.z * inv, y.w * inv);
   }
-  if (lse && kk == 0 && wave % (W / 2) == 0)
+  if (lse && kk == 0 && wave % (W / NH) == 0)
     lse[qb * 64 + slot] = l_all > 0.f ? m_all * (float)(1.0 / sqrt((double)D)) + logf(l_all) : -INFINITY;
+}
+
+template <int D, bool VT>
+__global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float* __restrict__ Q, const float* __restrict__ K,
+                                                             const float* __restrict__ V, const int32_t* __restrict__ idx,
+                                                             const int32_t* __restrict__ row_ptr, long long cap,
+                                                             float* __restrict__ O, float* __restrict__ lse, F32Share share) {
+  __shared__ Parts<D> parts;
+  const F32Piece piece = f32_piece(share, blockIdx.x);
+  if (piece.half >= 2LL * q.B * q.H * q.g) return;           // (the last stretch may be shorter)
+  const int first_query = 32 * (int)(piece.half & 1) + 16 * piece.second;
+  if (piece.queries == 32) attend<D, VT, 2>(q, Q, K, V, idx, row_ptr, cap, O, lse, piece.half >> 1, first_query, parts);
+  else attend<D, VT, 1>(q, Q, K, V, idx, row_ptr, cap, O, lse, piece.half >> 1, first_query, parts);
 }
 
 }  // namespace
@@ -296,10 +317,9 @@ __global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(Geo q, const float*
 // q.in / q.out / q.reordered say where the rows of Q, K (and V, unless it is block-transposed) and O are.
 hipError_t launch_attn_f32(const Geo& q, const float* Q, const float* K, const float* V, bool v_transposed,
                            const int32_t* idx, const int32_t* row_ptr, long long cap, float* O, float* lse, hipStream_t s) {
-  const long long total = 2LL * q.B * q.H * q.g;
-  const dim3 grid((unsigned)(8 * ((total + 7) / 8)));
+  const F32Share share = f32_share_out(2LL * q.B * q.H * q.g, q.d);
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * W), 0, s, q, Q, K, V, idx, row_ptr, cap, O, lse);
+    hipLaunchKernelGGL(kernel, dim3(share.grid), dim3(64 * W), 0, s, q, Q, K, V, idx, row_ptr, cap, O, lse, share);
   };
   if (q.d == 64 && v_transposed) go(attn_f32_kernel<64, true>);
   else if (q.d == 64) go(attn_f32_kernel<64, false>);
