@@ -306,12 +306,16 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   } else {
     if ((e = launch_pool_reorder(q, Q, K, q_pool, k_pool, bf16 && !k_in_place ? kp : nullptr, s)) != hipSuccess)
       return DA_ERR_HIP;
-    if ((e = launch_draft_logits(q, q_pool, k_pool, logits, s)) != hipSuccess) return DA_ERR_HIP;
     // guided sparsity: k per row, or the threshold over the whole map (Section 3.2.2)
-    if (whole_map)
-      e = launch_select_global(q, budget, cap, logits, row_ptr, idx, nullptr, base + w.select, s);
-    else
-      e = launch_select(q, logits, idx, nullptr, true, s);
+    if (!whole_map && draft_select_fits(q)) {
+      e = launch_draft_select(q, q_pool, k_pool, idx, s);
+    } else {
+      if ((e = launch_draft_logits(q, q_pool, k_pool, logits, s)) != hipSuccess) return DA_ERR_HIP;
+      if (whole_map)
+        e = launch_select_global(q, budget, cap, logits, row_ptr, idx, nullptr, base + w.select, s);
+      else
+        e = launch_select(q, logits, idx, nullptr, true, s);
+    }
   }
   if (e != hipSuccess) return DA_ERR_HIP;
   if (!bf16)

@@ -90,6 +90,9 @@ hipError_t launch_row_softmax(const Geo& q, const float* logits, float* draft, h
 // inside the array
 constexpr size_t kSelectSlack = 64 * 64 * sizeof(float);
 hipError_t launch_select(const Geo& q, const float* scores, int32_t* idx, uint8_t* mask, bool slack, hipStream_t s);
+// both in one launch, with no map left behind, where draft_select_fits (rows of the map are short)
+bool draft_select_fits(const Geo& q);
+hipError_t launch_draft_select(const Geo& q, const float* q_pool, const float* k_pool, int32_t* idx, hipStream_t s);
 hipError_t launch_all_lists(const Geo& q, int32_t* idx, int32_t* row_ptr, long long head_stride, hipStream_t s);
 // idx: k columns per row; or, with row_ptr [B,H,g+1], lists of any length, the lists of head bh one after the
 // other from idx + bh * cap on

@@ -22,6 +22,7 @@
 // take 5; a stretch of consecutive tiles per XCD changes nothing (278 us).
 #include <math.h>
 #include "da_internal.h"
+#include "select_keys.h"
 
 // The compiler contracts nothing in this file (the pragma covers the code below, and the build also
 // passes -ffp-contract=off for it): the only fused multiply-adds are the ones written out.
@@ -132,6 +133,89 @@ __global__ __launch_bounds__(256) void draft_logits_kernel(Geo q, const float* _
   }
 }
 
+// Logits and lists in one launch where a row of the map is short (g <= kFusedColumns): a workgroup of eight waves owns 32
+// rows of one head's map, a wave 32 columns of them, and the map goes no further than LDS.  Such launches are too small to
+// fill the chip, and what they take is a chain of latencies: one launch less, no trip of the map through memory, and the
+// operands come straight from the pooled rows into registers, without stages and barriers (a lane asks for four channels at
+// a time and uses the two of its half-wave: the chain of products is draft_logits_kernel's, and so are the bits).
+// The lists follow select_reg_kernel: a wave takes four rows, side by side, so that a bit costs one latency and not four.
+// da_forward, us, two launches -> one: 2 x 8 x 8 (64 channels) 23.7 -> 21.7, 2 x 25 x 25 49.1 -> 46.4, 48 x 28 x 28 104.6 ->
+// 102.6.  Wider rows gain nothing (4 x 84 x 84 193 either way) or lose (6 x 180 x 180 145 -> 154, 4 x 240 x 240 431 -> 442; with the
+// operands by way of LDS 2 x 252 x 252 120 -> 126): fewer workgroups share the selection, which is then the longer part.
+constexpr int kFusedColumns = 64;
+constexpr int FR = 32;                                   // rows of a workgroup
+constexpr int FW = 8;                                    // waves
+constexpr int FS = FR / FW;                              // rows per wave of the selection
+
+__global__ __launch_bounds__(64 * FW) void draft_select_kernel(Geo q, const float* __restrict__ q_pool,
+                                                               const float* __restrict__ k_pool, int32_t* __restrict__ idx,
+                                                               float scale, int row_tiles) {
+  constexpr int LDM = kFusedColumns + 4;
+  __shared__ float map[FR * LDM];
+  const int lane = threadIdx.x & 63, r32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bh = (int)(blockIdx.x / (unsigned)row_tiles);
+  const int row0 = ((int)blockIdx.x - bh * row_tiles) * FR, col0 = wave * 32;
+  if (col0 < q.g) {
+    // (rows past the last one read that again and are not used)
+    const float* const qr = q_pool + ((long long)bh * q.g + min(row0 + r32, q.g - 1)) * q.d;
+    const float* const kr = k_pool + ((long long)bh * q.g + min(col0 + r32, q.g - 1)) * q.d;
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    constexpr int CH = 64;                               // channels asked for at a time
+    for (int c0 = 0; c0 < q.d; c0 += CH) {               // (d is 64 or 128 here)
+      f32x4 a[CH / 4], b[CH / 4];
+#pragma unroll
+      for (int u = 0; u < CH / 4; ++u) {
+        a[u] = *(const f32x4*)(qr + c0 + 4 * u);
+        b[u] = *(const f32x4*)(kr + c0 + 4 * u);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < CH / 4; ++u) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(hh ? a[u].y : a[u].x, hh ? b[u].y : b[u].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(hh ? a[u].w : a[u].z, hh ? b[u].w : b[u].z, acc, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) map[(8 * (r >> 2) + 4 * hh + (r & 3)) * LDM + col0 + r32] = acc[r] * scale;
+  }
+  __syncthreads();
+  const int g = q.g, k = q.k;
+  unsigned key[FS];                                      // of column `lane`
+#pragma unroll
+  for (int w = 0; w < FS; ++w) key[w] = lane < g ? order_key(map[(wave * FS + w) * LDM + lane]) : 0u;
+  // the value that k keys reach, bit by bit from the top; a row at whose value exactly k keys arrive is done
+  unsigned thr[FS];
+  bool cut[FS];
+#pragma unroll
+  for (int w = 0; w < FS; ++w) thr[w] = 0u, cut[w] = false;
+  for (int bit = 31; bit >= 0; --bit) {
+    bool all = true;
+#pragma unroll
+    for (int w = 0; w < FS; ++w) {
+      const unsigned cand = thr[w] | (1u << bit);
+      const int cnt = __popcll(__ballot(key[w] >= cand));
+      if (!cut[w] && cnt >= k) thr[w] = cand;
+      cut[w] = cut[w] || cnt == k;
+      all = all && cut[w];
+    }
+    if (all) break;                                      // (the same in every lane)
+  }
+#pragma unroll
+  for (int w = 0; w < FS; ++w) {
+    const int row = row0 + wave * FS + w;
+    if (row >= g) break;                                 // (the same in every lane)
+    // what beats the value, and of what equals it the first columns, as many as are still wanted (cut: k keys reach the value,
+    // so all that equal it are)
+    const unsigned long long gt_mask = __ballot(key[w] > thr[w]), eq_mask = __ballot(lane < g && key[w] == thr[w]);
+    const bool take = (gt_mask >> lane & 1) || ((eq_mask >> lane & 1) && lane_prefix(eq_mask) < k - __popcll(gt_mask));
+    const unsigned long long take_mask = __ballot(take);
+    if (take) idx[((long long)bh * g + row) * k + lane_prefix(take_mask)] = lane;
+  }
+}
+
 __device__ inline float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
@@ -172,6 +256,16 @@ hipError_t launch_draft_logits(const Geo& q, const float* q_pool, const float* k
 hipError_t launch_row_softmax(const Geo& q, const float* logits, float* draft, hipStream_t s) {
   long long rows = (long long)q.B * q.H * q.g;
   hipLaunchKernelGGL(row_softmax_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, logits, draft, q.g, rows);
+  return hipGetLastError();
+}
+
+bool draft_select_fits(const Geo& q) { return q.g <= kFusedColumns && q.d % 64 == 0; }
+
+hipError_t launch_draft_select(const Geo& q, const float* q_pool, const float* k_pool, int32_t* idx, hipStream_t s) {
+  const float scale = (float)(1.0 / sqrt((double)q.d));
+  const int row_tiles = (q.g + FR - 1) / FR;
+  hipLaunchKernelGGL(draft_select_kernel, dim3((unsigned)(row_tiles * (long long)q.B * q.H)), dim3(64 * FW), 0, s, q, q_pool, k_pool,
+                     idx, scale, row_tiles);
   return hipGetLastError();
 }
 

@@ -9,26 +9,15 @@
 // ...): a counting pass is then one compare per key, whose lane mask is counted on the scalar
 // unit.  Longer rows keep their keys in LDS, or recompute them from global memory.
 #include "da_internal.h"
+#include "select_keys.h"
 #include "select_rows.h"
 
 namespace da {
-
-__device__ inline unsigned order_key(float x) {
-  unsigned u = __float_as_uint(x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0u;       // NaN ranks below everything
-  if ((u & 0x7fffffffu) == 0u) u = 0u;                  // -0 == +0
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
 
 __device__ inline int wave_sum_int(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
-}
-
-// number of set bits of `m` strictly below this lane
-__device__ inline int lane_prefix(unsigned long long m) {
-  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
 }
 
 template <bool IN_LDS>
