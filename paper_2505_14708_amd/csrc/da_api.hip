@@ -289,7 +289,8 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   const bool bf16 = q.dtype == DA_BF16;
   // Definition 3.2: pooled Q~, K~ and the draft logits (the ranking of a row of the draft
   // map is the ranking of its logits, so the softmax itself is not needed here).
-  // With bf16 the pooling pass also writes the reordered K of Algorithm 1 (one read of K for both); Q is not copied at
+  // With bf16 the pooling pass also writes the reordered K of Algorithm 1 (one read of K for both), and the same launch the
+  // reordered V (block-transposed, as matrix operands); Q is not copied at
   // all: the attention kernel reads its query rows from their original places and writes O's rows back to theirs,
   // which is Algorithm 1 for Q and Algorithm 2 for O done by addressing (a row of 256 bytes is contiguous in either
   // order).  The float32 attention brings every tile in by way of registers and takes K and V by addressing as well.
@@ -302,10 +303,12 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   const bool all_kept = whole_map ? budget == (long long)q.g * q.g : q.k == q.g;
   if (all_kept) {
     if (bf16 && !k_in_place && (e = launch_permute(q, K, kp, DA_REORDER_ROWS, s)) != hipSuccess) return DA_ERR_HIP;
+    if (bf16 && (e = launch_permute(q, V, vt, DA_REORDER_VOP, s)) != hipSuccess) return DA_ERR_HIP;
     e = launch_all_lists(q, idx, row_ptr, whole_map ? cap : (long long)q.g * q.g, s);
   } else {
-    if ((e = launch_pool_reorder(q, Q, K, q_pool, k_pool, bf16 && !k_in_place ? kp : nullptr, s)) != hipSuccess)
-      return DA_ERR_HIP;
+    e = bf16 ? launch_prepare(q, Q, K, V, q_pool, k_pool, k_in_place ? nullptr : kp, vt, s)
+             : launch_pool(q, Q, K, q_pool, k_pool, s);
+    if (e != hipSuccess) return DA_ERR_HIP;
     // guided sparsity: k per row, or the threshold over the whole map (Section 3.2.2)
     if (!whole_map && draft_select_fits(q)) {
       e = launch_draft_select(q, q_pool, k_pool, idx, s);
@@ -321,8 +324,6 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   if (!bf16)
     return hip_status(launch_attn_f32(q, (const float*)Q, (const float*)K, (const float*)V, false, idx, row_ptr, cap,
                                       (float*)O, nullptr, s));
-  // Algorithm 1: reorder V (block-transposed, as matrix operands)
-  if ((e = launch_permute(q, V, vt, DA_REORDER_VOP, s)) != hipSuccess) return DA_ERR_HIP;
   // SparseAttn
   return hip_status(launch_attn_bf16_ring(q, Q, kp, vt, idx, row_ptr, cap, O, nullptr, true, nullptr, s));
 }

@@ -81,9 +81,10 @@ __host__ __device__ inline long long token_slot(const Geo& q, long long n) {
 hipError_t launch_build_perm(const Geo& q, int32_t* perm, int32_t* inv, int32_t* valid, hipStream_t s);
 hipError_t launch_permute(const Geo& q, const void* X, void* Y, int mode, hipStream_t s);
 hipError_t launch_pool(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, hipStream_t s);
-// pooling and, with Kp (DA_BF16 only), the reordering of K (DA_REORDER_ROWS layout) in one pass over Q and K
-hipError_t launch_pool_reorder(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, void* Kp,
-                               hipStream_t s);
+// DA_BF16: pooling, the reordering of K (Kp in the DA_REORDER_ROWS layout; NULL: K stays where it is) and that of V
+// (DA_REORDER_VOP), in one launch as a rule
+hipError_t launch_prepare(const Geo& q, const void* Q, const void* K, const void* V, float* q_pool, float* k_pool, void* Kp,
+                          void* Vt, hipStream_t s);
 hipError_t launch_draft_logits(const Geo& q, const float* q_pool, const float* k_pool, float* logits, hipStream_t s);
 hipError_t launch_row_softmax(const Geo& q, const float* logits, float* draft, hipStream_t s);
 // slack: kSelectSlack bytes behind `scores` may be read (their values are not used); without it the last few rows stay

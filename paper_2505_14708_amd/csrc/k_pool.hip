@@ -8,17 +8,11 @@
 // push anything else out of the L2 (measured on the headline shape: 5.4 -> 5.8 TB/s).
 #include <type_traits>
 #include "da_internal.h"
+#include "vt_block.h"
 
 #pragma clang fp contract(off)
 
 namespace da {
-
-// 16 bytes, read once
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-__device__ inline uint4 load_once(const uint4* p) {
-  const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
 
 template <int DT>
 struct Vec;
@@ -45,18 +39,13 @@ struct Vec<DA_F32> {
 
 constexpr int kPoolThreads = 64;
 
-// grid.x covers (bh, block, chunk) items; grid.y = 0 for Q, 1 for K.  With REORDER the tokens of K are
-// also written, as they go by, to their slots of the reordered tensor Kp (Algorithm 1), pad
-// slots zeroed: pooling and reordering then read K once between them.
-template <int DT, bool REORDER, bool MAXP>
-__global__ __launch_bounds__(kPoolThreads) void pool_kernel(Geo q, const uint4* __restrict__ Q, const uint4* __restrict__ K,
-                                                   float* __restrict__ q_pool, float* __restrict__ k_pool,
-                                                   uint4* __restrict__ Kp, int cpr, long long items) {
+// Item number `item` of the (bh, block, chunk) of X.  With Kp (X is then K) the tokens are also written, as they go by,
+// to their slots of the reordered tensor Kp (Algorithm 1), pad slots zeroed: pooling and reordering then
+// read K once between them.
+template <int DT, bool MAXP>
+__device__ __forceinline__ void pool_item(const Geo& q, const uint4* __restrict__ X, float* __restrict__ out,
+                                          uint4* __restrict__ Kp, int cpr, long long item) {
   constexpr int N = Vec<DT>::N;
-  long long item = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (item >= items) return;
-  const uint4* X = blockIdx.y ? K : Q;
-  float* out = blockIdx.y ? k_pool : q_pool;
   long long blk = item / cpr;  // over bh * g
   int c = (int)(item - blk * cpr);
   long long bh = blk / q.g;
@@ -66,7 +55,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(Geo q, const uint4* 
   const long long sn = q.in.sn / N;
   const long long pitch = block_row_pitch(q, b);
   const uint4* src = X + row_offset(q.in, q.H, bh, block_first_row(q, i, b)) / N + c;
-  const bool wr = REORDER && blockIdx.y;               // (Q is only pooled)
+  const bool wr = Kp != nullptr;
   uint4* dstp = wr ? Kp + (blk * q.block) * cpr + c : nullptr;   // slot 0 of the block
   float acc[N];
 #pragma unroll
@@ -133,16 +122,12 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(Geo q, const uint4* 
 // of the sums is the same, token by token.  da_forward, one 30x52 frame, 48 heads: 109 -> 91 us; three of them in
 // float32, 4 heads: 115 -> 107 us; where every patch is eight wide (48x80, 24 heads) 109 us either way and on the
 // smallest 21.4 -> 22.5 us, so those stay with pool_kernel.
-template <int DT, bool REORDER, bool MAXP>
-__global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, const uint2* __restrict__ Q, const uint2* __restrict__ K,
-                                                                     float* __restrict__ q_pool, float* __restrict__ k_pool,
-                                                                     uint2* __restrict__ Kp, int cpr, long long items) {
+template <int DT, bool MAXP>
+__device__ __forceinline__ void pool_small_item(const Geo& q, const uint2* __restrict__ X, float* __restrict__ out,
+                                                uint2* __restrict__ Kp, int cpr, unsigned item) {
   constexpr int N = Vec<DT>::N / 2;
   constexpr int AHEAD = 64;
-  const unsigned item = blockIdx.x * kPoolThreads + threadIdx.x;   // (few: 32 bits hold them, and 64-bit divisions are five times as long)
-  if (item >= items) return;
-  const uint2* X = blockIdx.y ? K : Q;
-  float* out = blockIdx.y ? k_pool : q_pool;
+  // (few: 32 bits hold their numbers, and 64-bit divisions are five times as long)
   const unsigned in_head = item / (unsigned)cpr;   // over bh * g
   const int c = (int)(item - in_head * (unsigned)cpr);
   const long long blk = in_head, bh = in_head / (unsigned)q.g;
@@ -153,7 +138,7 @@ __global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, cons
   const int skip = block_row_pitch(q, b) - b.vw;                          // rows between a patch row's last token and the next one's first
   const int recip = (65536 + b.vw - 1) / b.vw;                            // slot / vw by way of the reciprocal: exact below 256
   const uint2* src = X + row_offset(q.in, q.H, bh, block_first_row(q, i, b)) / N + c;
-  const bool wr = REORDER && blockIdx.y;               // (Q is only pooled)
+  const bool wr = Kp != nullptr;
   uint2* dstp = wr ? Kp + (blk * q.block) * cpr + c : nullptr;   // slot 0 of the block
   float acc[N];
 #pragma unroll
@@ -186,42 +171,111 @@ __global__ __launch_bounds__(kPoolThreads, 2) void pool_small_kernel(Geo q, cons
   for (int j = 0; j < N; ++j) dst[j] = MAXP ? acc[j] : acc[j] / cnt;
 }
 
-// Below this many waves of pool_kernel in all.  (1008 waves 243 -> 225 us, 2016 waves 391 -> 386 us, from 2940 on no
-// difference either way.)
-constexpr long long kSmallWaves = 2048;
-
-hipError_t launch_pool(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, hipStream_t s) {
-  return launch_pool_reorder(q, Q, K, q_pool, k_pool, nullptr, s);
+// grid.x covers the items; grid.y = 0 for Q, 1 for K
+template <int DT, bool SMALL, bool MAXP>
+__global__ __launch_bounds__(kPoolThreads, SMALL ? 2 : 1) void pool_kernel(Geo q, const void* __restrict__ Q,
+                                                                           const void* __restrict__ K, float* __restrict__ q_pool,
+                                                                           float* __restrict__ k_pool, int cpr, long long items) {
+  const long long item = (long long)blockIdx.x * kPoolThreads + threadIdx.x;
+  if (item >= items) return;
+  const void* const X = blockIdx.y ? K : Q;
+  float* const out = blockIdx.y ? k_pool : q_pool;
+  if constexpr (SMALL) pool_small_item<DT, MAXP>(q, (const uint2*)X, out, nullptr, cpr, (unsigned)item);
+  else pool_item<DT, MAXP>(q, (const uint4*)X, out, nullptr, cpr, item);
 }
 
-// Kp may be NULL (K is then only pooled); given, dtype is DA_BF16
-hipError_t launch_pool_reorder(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, void* Kp,
-                               hipStream_t s) {
-  size_t es = q.dtype == DA_BF16 ? 2 : 4;
-  int cpr = (int)(q.d * es / 16);
-  long long items = (long long)q.B * q.H * q.g * cpr;
+// What stands before the draft logits and the attention, in one launch: pooling of Q, pooling of K with its reordering,
+// and the reordering of V as operands.  They have nothing to do with each other, so where a launch of one does not fill the chip
+// the others do; where it does, a tail and a launch are saved.  `per` workgroups for Q, as many for K, then one per block of V (the
+// shorter ones last).
+// da_forward, us, two launches -> one: 2 x 28 blocks 42.6 -> 39.2, 48 x 28 102.6 -> 97.1, 24 x 60 (48x80) 117.7 -> 114.8, 24 x 252
+// 922 -> 906, 8 x 540 1320 -> 1302, 30 x 63 (one of 47x39) 764 -> 741.
+// With K in block order already (no Kp), short launches gain as much (2 x 28 blocks 38.6 -> 37.1, 8 x 60 63.2 -> 59.8), longer ones lose
+// (24 x 84 162 -> 165, 76 x 84 222 -> 228, 8 x 392 711 -> 717): the two streams of reads run better one after the other there.
+// The line, kInPlaceBlocks, lies where it makes no difference (36 x 28 71.0 and 71.6).
+constexpr int kPrepThreads = 256;
+template <bool SMALL, bool MAXP>
+__global__ __launch_bounds__(kPrepThreads, SMALL ? 2 : 1) void prepare_kernel(Geo q, const void* __restrict__ Q,
+                                                                              const void* __restrict__ K,
+                                                                              const uint16_t* __restrict__ V,
+                                                                              float* __restrict__ q_pool, float* __restrict__ k_pool,
+                                                                              void* __restrict__ Kp, uint16_t* __restrict__ Vt,
+                                                                              int cpr, long long items, unsigned per) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (blockIdx.x >= 2 * per) {
+    const unsigned b = blockIdx.x - 2 * per, bh = b / (unsigned)q.g;
+    vt_block<uint16_t, true>(q, V, Vt, (int)(b - bh * (unsigned)q.g), bh, smem);
+    return;
+  }
+  const bool is_k = blockIdx.x >= per;
+  const long long item = (long long)(is_k ? blockIdx.x - per : blockIdx.x) * kPrepThreads + threadIdx.x;
+  if (item >= items) return;
+  const void* const X = is_k ? K : Q;
+  float* const out = is_k ? k_pool : q_pool;
+  if constexpr (SMALL) pool_small_item<DA_BF16, MAXP>(q, (const uint2*)X, out, is_k ? (uint2*)Kp : nullptr, cpr, (unsigned)item);
+  else pool_item<DA_BF16, MAXP>(q, (const uint4*)X, out, is_k ? (uint4*)Kp : nullptr, cpr, item);
+}
+
+// Below this many waves of pool_item in all pool_small_item is taken.  (1008 waves 243 -> 225 us, 2016 waves 391 -> 386 us,
+// from 2940 on no difference either way.)
+constexpr long long kSmallWaves = 2048;
+
+namespace {
+struct Items {
+  bool small;
+  int cpr;            // items per block
+  long long count;
+};
+Items pool_items(const Geo& q) {
+  const int cpr = (int)(q.d * (q.dtype == DA_BF16 ? 2 : 4) / 16);
+  const long long items = (long long)q.B * q.H * q.g * cpr;
   const bool cut = q.fw % q.pw != 0 || q.pw % 8 != 0;   // some patch rows are not a multiple of eight tokens
   const bool small = cut && 2 * items < 64 * kSmallWaves && q.block >= 64 && q.block <= 128 && q.in.sn < (1LL << 31);
-  auto pick = [&](auto dt, auto reorder, auto max_pool) {
-    constexpr int DT = decltype(dt)::value;
-    constexpr bool RE = decltype(reorder)::value, MX = decltype(max_pool)::value;
-    if (small)
-      hipLaunchKernelGGL((pool_small_kernel<DT, RE, MX>), dim3((unsigned)((2 * items + kPoolThreads - 1) / kPoolThreads), 2),
-                         dim3(kPoolThreads), 0, s, q, (const uint2*)Q, (const uint2*)K, q_pool, k_pool, (uint2*)Kp, 2 * cpr,
-                         2 * items);
-    else
-      hipLaunchKernelGGL((pool_kernel<DT, RE, MX>), dim3((unsigned)((items + kPoolThreads - 1) / kPoolThreads), 2),
-                         dim3(kPoolThreads), 0, s, q, (const uint4*)Q, (const uint4*)K, q_pool, k_pool, (uint4*)Kp, cpr, items);
-  };
-  auto pick_max = [&](auto dt, auto reorder) {
-    if (q.pool == DA_POOL_MAX) pick(dt, reorder, std::true_type());
-    else pick(dt, reorder, std::false_type());
-  };
-  const std::integral_constant<int, DA_BF16> bf16;
-  const std::integral_constant<int, DA_F32> f32;
-  if (q.dtype != DA_BF16) pick_max(f32, std::false_type());
-  else if (Kp) pick_max(bf16, std::true_type());
-  else pick_max(bf16, std::false_type());
+  return {small, small ? 2 * cpr : cpr, small ? 2 * items : items};
+}
+// go(small, max) with the two as types
+template <typename F>
+void pick_pool(const Geo& q, bool small, F go) {
+  const std::true_type yes;
+  const std::false_type no;
+  const bool max_pool = q.pool == DA_POOL_MAX;
+  if (small && max_pool) go(yes, yes);
+  else if (small) go(yes, no);
+  else if (max_pool) go(no, yes);
+  else go(no, no);
+}
+}  // namespace
+
+hipError_t launch_pool(const Geo& q, const void* Q, const void* K, float* q_pool, float* k_pool, hipStream_t s) {
+  const Items it = pool_items(q);
+  pick_pool(q, it.small, [&](auto small, auto max_pool) {
+    constexpr bool SM = decltype(small)::value, MX = decltype(max_pool)::value;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((it.count + kPoolThreads - 1) / kPoolThreads), 2), dim3(kPoolThreads), 0, s, q, Q,
+                         K, q_pool, k_pool, it.cpr, it.count);
+    };
+    if (q.dtype == DA_BF16) go(pool_kernel<DA_BF16, SM, MX>);
+    else go(pool_kernel<DA_F32, SM, MX>);
+  });
+  return hipGetLastError();
+}
+
+constexpr long long kInPlaceBlocks = 1024;
+
+hipError_t launch_prepare(const Geo& q, const void* Q, const void* K, const void* V, float* q_pool, float* k_pool, void* Kp,
+                          void* Vt, hipStream_t s) {
+  if (!Kp && (long long)q.B * q.H * q.g >= kInPlaceBlocks) {
+    const hipError_t e = launch_pool(q, Q, K, q_pool, k_pool, s);
+    return e != hipSuccess ? e : launch_permute(q, V, Vt, DA_REORDER_VOP, s);
+  }
+  const Items it = pool_items(q);
+  const unsigned per = (unsigned)((it.count + kPrepThreads - 1) / kPrepThreads);
+  const dim3 grid((unsigned)(2 * per + (long long)q.B * q.H * q.g));
+  pick_pool(q, it.small, [&](auto small, auto max_pool) {
+    constexpr bool SM = decltype(small)::value, MX = decltype(max_pool)::value;
+    hipLaunchKernelGGL((prepare_kernel<SM, MX>), grid, dim3(kPrepThreads), vt_block_lds(q), s, q, Q, K, (const uint16_t*)V, q_pool,
+                       k_pool, Kp, (uint16_t*)Vt, it.cpr, it.count, per);
+  });
   return hipGetLastError();
 }
 
