@@ -302,9 +302,9 @@ static int forward_impl(const da_problem* p, bool whole_map, const da_layout* in
   // 0 .. g-1 whatever the draft map says, so pooling, logits and selection are left out and only Algorithm 1 runs.
   const bool all_kept = whole_map ? budget == (long long)q.g * q.g : q.k == q.g;
   if (all_kept) {
-    if (bf16 && !k_in_place && (e = launch_permute(q, K, kp, DA_REORDER_ROWS, s)) != hipSuccess) return DA_ERR_HIP;
-    if (bf16 && (e = launch_permute(q, V, vt, DA_REORDER_VOP, s)) != hipSuccess) return DA_ERR_HIP;
-    e = launch_all_lists(q, idx, row_ptr, whole_map ? cap : (long long)q.g * q.g, s);
+    const long long head_stride = whole_map ? cap : (long long)q.g * q.g;
+    e = bf16 ? launch_prepare_dense(q, K, V, k_in_place ? nullptr : kp, vt, idx, row_ptr, head_stride, s)
+             : launch_all_lists(q, idx, row_ptr, head_stride, s);
   } else {
     e = bf16 ? launch_prepare(q, Q, K, V, q_pool, k_pool, k_in_place ? nullptr : kp, vt, s)
              : launch_pool(q, Q, K, q_pool, k_pool, s);

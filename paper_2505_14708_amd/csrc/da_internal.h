@@ -85,6 +85,9 @@ hipError_t launch_pool(const Geo& q, const void* Q, const void* K, float* q_pool
 // (DA_REORDER_VOP), in one launch as a rule
 hipError_t launch_prepare(const Geo& q, const void* Q, const void* K, const void* V, float* q_pool, float* k_pool, void* Kp,
                           void* Vt, hipStream_t s);
+// DA_BF16, every block kept: the reordering of K (Kp may be NULL as above) and V, and the lists (as launch_all_lists), in one launch
+hipError_t launch_prepare_dense(const Geo& q, const void* K, const void* V, void* Kp, void* Vt, int32_t* idx, int32_t* row_ptr,
+                                long long head_stride, hipStream_t s);
 hipError_t launch_draft_logits(const Geo& q, const float* q_pool, const float* k_pool, float* logits, hipStream_t s);
 hipError_t launch_row_softmax(const Geo& q, const float* logits, float* draft, hipStream_t s);
 // slack: kSelectSlack bytes behind `scores` may be read (their values are not used); without it the last few rows stay

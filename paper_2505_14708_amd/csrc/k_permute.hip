@@ -24,15 +24,13 @@ __global__ void build_perm_kernel(Geo q, int32_t* perm, int32_t* inv, int32_t* v
   if (valid && s == 0) valid[i] = nv;
 }
 
-// One workgroup per (block, batch*head).  cpr = 16-byte chunks per row.
+// A workgroup of 256 threads takes one block.  cpr = 16-byte chunks per row.
 // FWD: Y[slot] = X[pi[slot]] or zeros;  !FWD: X-order output, Y[token] = Xp[slot].
 // The reordered side is contiguous [B,H,n_pad,d]; the other side is the caller's tensor (q.in for
 // the source of FWD, q.out for the destination of !FWD).
 template <bool FWD>
-__global__ __launch_bounds__(256) void permute_rows_kernel(Geo q, const chunk16* __restrict__ X, chunk16* __restrict__ Y,
-                                                            int cpr) {
-  int i = blockIdx.x;
-  long long bh = blockIdx.y;
+__device__ __forceinline__ void rows_block(const Geo& q, const chunk16* __restrict__ X, chunk16* __restrict__ Y, int cpr, int i,
+                                           long long bh) {
   BlockPos b = block_pos(q, i);
   int nv = b.vh * b.vw;
   const int per = q.d / cpr;                           // elements per chunk
@@ -57,10 +55,49 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(Geo q, const chunk16*
   }
 }
 
+template <bool FWD>
+__global__ __launch_bounds__(256) void permute_rows_kernel(Geo q, const chunk16* __restrict__ X, chunk16* __restrict__ Y,
+                                                            int cpr) {
+  rows_block<FWD>(q, X, Y, cpr, (int)blockIdx.x, blockIdx.y);
+}
+
 template <typename E, bool OPERAND>
 __global__ __launch_bounds__(256) void permute_vt_kernel(Geo q, const E* __restrict__ X, E* __restrict__ Y) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   vt_block<E, OPERAND>(q, X, Y, (int)blockIdx.x, blockIdx.y, smem);
+}
+
+// All that stands before the attention where every block is kept (bf16): the reordering of V, that of K (Kp NULL: it stays where
+// it is) and the lists 0 .. g-1, in one launch, a workgroup for each block and each list.
+// da_forward and da_forward_global, us, three launches (two with K in place) -> one: 2 heads of a 30x52 frame 39.3 -> 34.4, 24 of
+// them 73.1 -> 67.3, in block order 65.6 -> 63.5, 8 heads of two 45x80 frames 240 -> 234, 24 of nine 30x52 frames 2571 -> 2557.
+__global__ __launch_bounds__(256) void prepare_dense_kernel(Geo q, const chunk16* __restrict__ K, const uint16_t* __restrict__ V,
+                                                            chunk16* __restrict__ Kp, uint16_t* __restrict__ Vt,
+                                                            int32_t* __restrict__ idx, int32_t* __restrict__ row_ptr,
+                                                            long long head_stride, int cpr, unsigned blocks) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const unsigned what = blockIdx.x / blocks, b = blockIdx.x - what * blocks;
+  const unsigned bh = b / (unsigned)q.g;
+  const int i = (int)(b - bh * (unsigned)q.g);
+  if (what == 0) {
+    vt_block<uint16_t, true>(q, V, Vt, i, bh, smem);
+  } else if (what == 1 && Kp) {
+    rows_block<true>(q, K, Kp, cpr, i, bh);
+  } else {
+    for (int j = threadIdx.x; j < q.g; j += 256) idx[bh * head_stride + (long long)i * q.g + j] = j;
+    if (row_ptr && threadIdx.x == 0) {
+      row_ptr[bh * (long long)(q.g + 1) + i] = i * q.g;
+      if (i == q.g - 1) row_ptr[bh * (long long)(q.g + 1) + q.g] = q.g * q.g;
+    }
+  }
+}
+
+hipError_t launch_prepare_dense(const Geo& q, const void* K, const void* V, void* Kp, void* Vt, int32_t* idx, int32_t* row_ptr,
+                                long long head_stride, hipStream_t s) {
+  const unsigned blocks = (unsigned)((long long)q.B * q.H * q.g);
+  hipLaunchKernelGGL(prepare_dense_kernel, dim3(blocks * (Kp ? 3 : 2)), dim3(256), vt_block_lds(q), s, q, (const chunk16*)K,
+                     (const uint16_t*)V, (chunk16*)Kp, (uint16_t*)Vt, idx, row_ptr, head_stride, q.d / 8, blocks);
+  return hipGetLastError();
 }
 
 hipError_t launch_build_perm(const Geo& q, int32_t* perm, int32_t* inv, int32_t* valid, hipStream_t s) {

@@ -1,4 +1,4 @@
-"""Pooling, K's reordering and V's in one launch (da_forward, bf16): the bits of lists and output that the same steps one by one
+"""Pooling, K's reordering and V's in one launch, or where every block is kept both reorderings and the lists (da_forward, bf16): the bits of lists and output that the same steps one by one
 give.  Small and large launches, whole and cut patch rows, blocks of 64 and 128, mean and maximum, contiguous, strided and
 block-ordered tensors, the last on both sides of the line where the launches are separate."""
 import pytest
@@ -12,10 +12,11 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("layout", ["plain", "fused", "blocks"])
 @pytest.mark.parametrize("H,T,fh,fw,pw,pool", [(1, 1, 3, 5, 8, 0), (3, 2, 30, 52, 8, 0), (3, 2, 30, 52, 8, 1), (2, 2, 16, 24, 8, 0), (2, 2, 13, 41, 16, 1),
                                                (36, 1, 30, 52, 8, 0), (37, 1, 30, 52, 8, 0), (16, 10, 30, 52, 8, 0), (64, 1, 16, 64, 8, 1)])
-def test_same_bits_as_one_by_one(H, T, fh, fw, pw, pool, layout):
+@pytest.mark.parametrize("sparsity", [0.7, 0.0])
+def test_same_bits_as_one_by_one(H, T, fh, fw, pw, pool, sparsity, layout):
     import torch
-    say(f"prepare {H} x {T}x{fh}x{fw} window 8x{pw} pool {pool} {layout}")
-    p = da.problem(1, H, T, fh, fw, 128, 8, pw, sparsity=0.7, pool=pool)
+    say(f"prepare {H} x {T}x{fh}x{fw} window 8x{pw} pool {pool} sparsity {sparsity} {layout}")
+    p = da.problem(1, H, T, fh, fw, 128, 8, pw, sparsity=sparsity, pool=pool)
     dims = da.da_derive(p)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(H * T)
@@ -49,6 +50,14 @@ def test_same_bits_as_one_by_one(H, T, fh, fw, pw, pool, layout):
     else:
         O = torch.empty_like(want)
         da.da_forward(p, *x, O, ws, idx)
+        if sparsity == 0.0:                                # the whole-map route: the same lists, with offsets
+            sizes = da.da_global_sizes(p)
+            row_ptr = torch.full((1, H, dims.g + 1), -1, dtype=torch.int32, device="cuda")
+            cols = torch.full((1, H, int(sizes.cap)), -1, dtype=torch.int32, device="cuda")
+            da.da_forward_global(p, *x, torch.empty_like(want), torch.empty(int(sizes.forward_ws), dtype=torch.uint8, device="cuda"),
+                                 row_ptr, cols)
+            assert torch.equal(row_ptr[0, -1].cpu(), torch.arange(dims.g + 1, dtype=torch.int32) * dims.g)
+            assert torch.equal(cols[:, :, :dims.g * dims.g].reshape(want_idx.shape), want_idx)
     torch.cuda.synchronize()
     assert torch.equal(idx, want_idx)
     assert torch.equal(O.view(torch.int16), want.view(torch.int16))
