@@ -1,9 +1,10 @@
 // SparseAttn for float32 storage, blocks of 64 slots, d = 64 or 128: float32 throughout, on the float32 matrix
 // instructions (v_mfma_f32_16x16x4_f32: exact products, one rounding per term, like a chain of fused multiply-adds).
 //
-// A workgroup is half a query block, 32 queries, or a quarter where that fills the chip better (f32_share.h); its waves share out the keys, 16 (a quarter of a block) at a time, and
-// keep a running maximum, a sum and an output of their own, which are put together at the end.  A key is then wanted by
-// one wave only, so K and V go straight from memory to that wave's registers: no tile in LDS, no barrier in the loop.
+// A workgroup is half a query block, 32 queries, or a quarter where that fills the chip better (f32_share.h); its waves share
+// out the keys, 16 (a quarter of a block) at a time, and keep a running maximum, a sum and an output of their own, which are put
+// together at the end.  A key is then wanted by one wave only, so K and V go straight from memory to that wave's registers: no
+// tile in LDS, no barrier in the loop.
 // Wave: 16 keys x 32 queries per step, the query on the lane axis of both products:
 //     S^T = K Q^T      lane l: query l % 16 of each 16; accumulator register r: key 4(l/16) + r
 //     O^T += V^T P^T   register r of P is, as it stands, the operand of the step that adds the keys 4(l/16) + r: no
