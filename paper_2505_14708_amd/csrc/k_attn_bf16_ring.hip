@@ -373,19 +373,19 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
 
 // Puts the n union entries at `list` in the order of the walk (see there), by all eight waves.  The scratch is the ring's place,
 // which holds nothing yet; ends with a barrier.  Number within the class: a wave takes a stretch of the list, 64 entries at a
-// time; rank by key: kBuckets buckets of keys, and inside a bucket by comparison (whatever the order in which waves reach
-// the counters, the result is the same).
-constexpr int kBuckets = 2048;
+// time; rank by key: kWalkBuckets buckets of keys, and inside a bucket by comparison (whatever the order in which waves reach
+// the counters, the result is the same).  An entry's key is formed once and read back from then on: the passes have to agree on
+// its bucket, for one more entry in a bucket than were counted would take the place of another.
 __device__ __forceinline__ void spread_walk(unsigned char* scratch, unsigned* list, int n, int wave, int lane) {
   int* const of_class = (int*)scratch;                // [WAVES][256] entries of a class in each wave's stretch, then before it
   float* const inv_total = (float*)(scratch + 8192);  // [256]
-  int* const start = (int*)(scratch + 16384);         // [kBuckets + 1] entries per bucket, then where it starts
+  int* const next = (int*)(scratch + 16384);          // [kWalkBuckets] entries per bucket, then where its next one goes: in the end where the next bucket starts
   int* const wave_sum = (int*)(scratch + 28672);      // [WAVES]
-  int* const number = (int*)(scratch + 32768);        // [n]
+  int* const number = (int*)(scratch + 32768);        // [n] number within the stretch's part of the class, then the key
   uint2* const slots = (uint2*)(scratch + 65536);     // [n] key and entry
   const int t = threadIdx.x;
   for (int i = t; i < WAVES * 256; i += 512) of_class[i] = 0;
-  for (int i = t; i < kBuckets; i += 512) start[i] = 0;
+  for (int i = t; i < kWalkBuckets; i += 512) next[i] = 0;
   __syncthreads();
   const int stretch = ((n + 511) >> 9) << 6;
   for (int base = wave * stretch; base < min(n, (wave + 1) * stretch); base += 64) {
@@ -415,17 +415,11 @@ __device__ __forceinline__ void spread_walk(unsigned char* scratch, unsigned* li
     inv_total[t] = 1.0f / (float)max(sum, 1);
   }
   __syncthreads();
-  // key of entry e, number p of its class (below 1 but for rounding), and the bucket of a key
-  auto key_of = [&](unsigned e, int p) -> float {
-    const int m = (int)(e >> kMemberBit);
-    const float u = (float)m * 0.618034f;
-    return ((float)p + (u - floorf(u))) * inv_total[m];
-  };
-  auto bucket_of = [](float key) -> int { return min((int)(key * (float)kBuckets), kBuckets - 1); };
   for (int i = t; i < n; i += 512) {
-    const unsigned e = list[i];
-    const int p = number[i] + of_class[(i / stretch) * 256 + (int)(e >> kMemberBit)];
-    number[i] = p | atomicAdd(&start[bucket_of(key_of(e, p))], 1) << 16;
+    const int m = (int)(list[i] >> kMemberBit);
+    const float key = walk_key(m, number[i] + of_class[(i / stretch) * 256 + m], inv_total[m]);
+    number[i] = __float_as_int(key);
+    atomicAdd(&next[walk_bucket(key)], 1);
   }
   __syncthreads();
   {
@@ -433,7 +427,7 @@ __device__ __forceinline__ void spread_walk(unsigned char* scratch, unsigned* li
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       c[j] = sum;
-      sum += start[4 * t + j];
+      sum += next[4 * t + j];
     }
     int incl = sum;
 #pragma unroll
@@ -446,20 +440,18 @@ __device__ __forceinline__ void spread_walk(unsigned char* scratch, unsigned* li
     int at = incl - sum;
     for (int w = 0; w < wave; ++w) at += wave_sum[w];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) start[4 * t + j] = at + c[j];
-    if (t == 511) start[kBuckets] = n;
+    for (int j = 0; j < 4; ++j) next[4 * t + j] = at + c[j];
   }
   __syncthreads();
   for (int i = t; i < n; i += 512) {
-    const unsigned e = list[i];
-    const float key = key_of(e, number[i] & 0xffff);
-    slots[start[bucket_of(key)] + (number[i] >> 16)] = make_uint2(__float_as_uint(key), e);
+    const int key = number[i];
+    slots[atomicAdd(&next[walk_bucket(__int_as_float(key))], 1)] = make_uint2((unsigned)key, list[i]);
   }
   __syncthreads();
   for (int i = t; i < n; i += 512) {
     const uint2 mine = slots[i];
     const float key = __uint_as_float(mine.x);
-    const int bucket = bucket_of(key), lo = start[bucket], hi = start[bucket + 1];
+    const int bucket = walk_bucket(key), lo = bucket ? next[bucket - 1] : 0, hi = next[bucket];
     int rank = lo;
     for (int x = lo; x < hi; ++x) {
       const uint2 other = slots[x];

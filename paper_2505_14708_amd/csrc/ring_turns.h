@@ -1,5 +1,5 @@
 // How the bf16 attention deals its work out, apart from HIP so that a CPU test can compile it: units of eight groups of 64
-// queries, how many workgroups share a unit, and which of the waves that share a list takes which entry of it.
+// queries, how many workgroups share a unit, which of the waves that share a list takes which entry of it, and the key that orders a walk.
 #pragma once
 
 #ifdef __HIPCC__
@@ -103,6 +103,18 @@ inline Share share_out(long long total, long long tiles, int least) {
 // (24 heads x 990 blocks of 8x16, 99 kept, peaked, two waves to a list 13.26 -> 12.29 ms; 5 heads, 21 frames, a quarter kept
 // 2.96 -> 2.52 ms; nothing dropped the same.)
 DA_HOST_DEVICE constexpr int wave_of_turn(int turn, int sub, int parts) { return (sub == 1 ? turn : turn + (turn >> 1)) & (parts - 1); }
+
+// The order of a walk: entry number p of a class of 1 / inv_total entries goes by the key (p + u) / (number of entries), u the
+// fraction of the class's number times the golden section; the sort puts keys (below 1 but for rounding) into buckets first.
+constexpr int kWalkBuckets = 2048;
+DA_HOST_DEVICE inline float walk_key(int cls, int p, float inv_total) {
+  const float u = (float)cls * 0.618034f;
+  return ((float)p + (u - (float)(int)u)) * inv_total;
+}
+DA_HOST_DEVICE inline int walk_bucket(float key) {
+  const int b = (int)(key * (float)kWalkBuckets);
+  return b < kWalkBuckets - 1 ? b : kWalkBuckets - 1;
+}
 
 }  // namespace ring
 }  // namespace da
