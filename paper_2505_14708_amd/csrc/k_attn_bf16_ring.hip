@@ -66,8 +66,8 @@
 //
 // The running max only moves (and O is rescaled) when a row max exceeds it by more than 2^8 in
 // the exponent's units; until then probabilities are formed against the stale max, which is
-// exact after the final division because numerator and denominator share it.  (In the first tile of a wave that has few it
-// moves with every larger score.)
+// exact after the final division because numerator and denominator share it.  (Where a list is short, and in the first tiles of
+// others, it follows the scores more closely: see the walk.)
 #include <float.h>
 #include <math.h>
 #include <stdlib.h>
@@ -106,6 +106,9 @@ constexpr int kSpinLimit = 1 << 20;
 constexpr int kClaimed = 1 << 20;                    // a slot's reader count while its entry is not known yet
 constexpr int kValidBit = 18, kMemberBit = 24;       // fields of a union entry (key sub-blocks are numbered below 2^18)
 constexpr int kPeekTiles = 8;                       // lists of at least so many tiles per wave: all waves of a group look at the first one
+constexpr int kFollowTiles = 24;                    // lists of fewer tiles, one wave each: the reference follows every larger score
+constexpr int kNearTiles = 2;                       // and in so many tiles it is the largest of each 32 keys,
+constexpr float kBelowTop = 90.0f;                  // no further below the largest score so far than this (11 powers of two)
 
 // Waves whose bounded wait for a tile ran out since the library was loaded (their rows were written as NaN).
 // No valid input makes that happen; the host can ask (da_wait_failures).
@@ -238,13 +241,13 @@ __device__ __forceinline__ int valid_slots(const Geo& q, int per_frame, int j) {
 }
 
 struct Soft {
-  // Reference max (raw score units).  Before the first tile the lowest finite value and not minus infinity: all scores of a
+  // Reference (raw score units): a maximum of some of the scores.  Before the first tile the lowest finite value and not minus infinity: all scores of a
   // half tile may be minus infinity (finite operands whose product leaves the range), and those keys weigh exp2(-inf) = 0,
   // not exp2(-inf + inf).
   float m;
   // Largest score seen so far, in what was carried out and in a first tile that was only looked at; +inf for a pad query.  (The
-  // reference trails the scores the wave has carried out by at most kLazy powers of two; it may start up to the drop rule's
-  // cut below a score that was only looked at.)
+  // reference trails the scores the wave has carried out by at most kLazy powers of two, or by kBelowTop in the first tiles of
+  // a short list; it may start up to the drop rule's cut below a score that was only looked at.)
   float top;
   float l;     // this lane's partial sum of probabilities
 };
@@ -283,7 +286,8 @@ __device__ __forceinline__ void half_scores(unsigned kaddr, int nv, const bf16x8
   }
 }
 
-// 32 keys (half a tile) for one wave.  v: the half tile's V^T in global memory (operand order: the 64 lanes' operands of
+// 32 keys (half a tile) for one wave.  lazy: how many powers of two the reference may trail the scores by; minus infinity: it
+// becomes the largest of these 32, also where that is smaller.  v: the half tile's V^T in global memory (operand order: the 64 lanes' operands of
 // (k-step t, channel group dt) are the contiguous KB number 4t + dt, so every load of a wave is one contiguous KB).
 template <int NQ>
 __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v, int nv, float skip, float lazy,
@@ -327,7 +331,8 @@ __device__ __forceinline__ void half_tile(unsigned kaddr, const unsigned char* v
   if (__any(moves)) {
 #pragma unroll
     for (int h = 0; h < NQ; ++h) {
-      const float m_new = fmaxf(st[h].m, mx[h]);
+      const bool near = lazy < 0.f && st[h].top < INFINITY;              // (not for pad queries)
+      const float m_new = fmaxf(near ? fmaxf(st[h].top - kBelowTop, -FLT_MAX) : st[h].m, mx[h]);
       const float alpha = st[h].m == m_new ? 1.0f : __builtin_amdgcn_exp2f((st[h].m - m_new) * kC2);   // 0 the first time
       st[h].m = m_new;
       st[h].l *= alpha;
@@ -847,13 +852,23 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   // AUX_BYTES / 4 = 2^13 entries, and a wave counts 2 and 4 for each)
   unsigned tally = 0u;
   int before = 0;                                     // entries of my group in the chunks before
-  // Where a wave has few tiles, its reference follows every larger score in the first of them: the first half is little to go
-  // by, and the largest probabilities, which count most, round best when they are 1.  (Error against float64 over that of
-  // probabilities relative to the row's maximum: one 30x52 frame, 14 blocks kept, 1.010 -> 0.982; one of 13x63, 4 kept, 1.009 ->
-  // 0.981.  Longer lists are at 0.95 to 1.00 without.)
+  // How closely the reference follows the scores.  The probability of the key it is taken from is 1, which bf16 holds
+  // exactly, and those just below it round better than those just above, so every reference that a row's sums are made up of saves
+  // part of the error.  Two waves to a list have two, each with its own tiles; one wave to a list makes up for that:
+  //   - it follows every larger score while the unit's own blocks go by, where a row's largest terms mostly are;
+  //   - in lists of fewer than kFollowTiles it follows throughout, and in the first kNearTiles each 32 keys have their own.
+  // With several waves to a list the first tile of short ones is followed.
+  // Error against float64 over that of two waves to every list with short ones (of up to 15 tiles) followed in the first tile
+  // (q scaled by 1, 1/4, 1/32; before this rule -> now): 48 heads of a 30x52 frame, 3 kept 1.005 -> 0.995, 1.018 -> 0.993, 1.026 -> 0.992, 14 kept
+  // 1.010 -> 0.998, 1.027 -> 0.992, 1.013 -> 0.994, 21 kept 1.009 -> 0.996, 1.014 -> 0.979, 1.005 -> 0.994; nine such frames,
+  // 63 kept 1.048 -> 0.990, 1.013 -> 0.977, 1.001 -> 0.996; 8x16 windows, 24 kept 1.049 -> 0.981, 1.018 -> 0.970, 1.002 -> 0.994.
+  // Tried besides: short lists that only follow, up to 1.008; with one tile where each 32 keys have their own 1.003, with four
+  // 1 to 2 % slower still.  Long ones that follow in the wave's own block alone, or have each 32 keys' own there, up to 1.013 and
+  // 1.001, and no faster.  What it costs (da_forward, us): 14 kept 97.4 -> 99.9, 3 kept 65.4 -> 67.2; 24 heads x 1980 blocks, 198 kept, peaked
+  // 11516 -> 11624, flat 19437 -> 19519.
   auto walk = [&](auto queries) {
     constexpr int NQ = decltype(queries)::value;
-    float lazy = few ? 0.f : kLazy;
+    const bool follow = parts == 1 && k * SUB < kFollowTiles;
     const int u = parts > 1 ? __builtin_amdgcn_readfirstlane(first[lgroup]) : -1;
     if (live && part > 0 && u >= 0) {
       const int slot = arrived(u);
@@ -893,12 +908,15 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         const int nv = (int)((e >> kValidBit) & 63u) + 1;
         const unsigned kaddr = kbase + (unsigned)slot * SLOT;
         const unsigned char* v = Vbh + (long long)(e & ((1u << kValidBit) - 1u)) * V_TILE;
+        const unsigned done = tally & 0xffffu;        // (NQ for each tile)
+        const float lazy = parts > 1   ? few && done == 0 ? 0.f : kLazy
+                           : follow    ? done < NQ * kNearTiles ? -INFINITY : 0.f
+                           : u < n_own ? 0.f : kLazy;
         int kept = 0;
 #pragma unroll 1
         for (int half = 0; half < 2 && 32 * half < nv; ++half) {
           half_tile<NQ>(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, lazy, qf, o, st, kept);
         }
-        lazy = kLazy;
         tally += NQ + ((unsigned)(nv > 32 ? NQ * kept : 2 * NQ * kept) << 16);
         leave(slot);
         // (Only waves that are waiting for a tile ask for tiles: having every wave look for room after each of
