@@ -715,19 +715,28 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   // of it then holds every block's fair share.  The softmax does not care about the order of the keys.
   if (mixed && nU - n_own > 2 * RING) spread_walk(smem, ulist + n_own, nU - n_own, wave, lane);
 
-  // The first entry of a group's walk is the best start for its running maxima (its own block, as a rule).  One of the
-  // group's waves takes it; the others look at its scores before they start, so that none has to carry out tiles that the
-  // drop rule would spare it.  Not worth a product where a wave has few tiles.
+  // A group's own block is the best start for its running maxima.  One of the group's waves takes it in its turn; the others look
+  // at its scores before they start, so that none has to carry out tiles that the drop rule would spare it.  Not worth a product
+  // where a wave has few tiles.  A list without it: the group's first entry.  (The own blocks are the first entries of the walk, eight
+  // at most, so all of them are in the ring before anybody has to be through with one.  Looking at the group's first entry in any
+  // case leaves all but one wave without a good start where the unit's blocks are of several positions, as those of left-over
+  // frames are: dense, peaked, one head x 760 blocks of 19 frames 888 -> 592 us, 3 heads x 196 of 7 253 -> 190 us, 8 x 84 of 3 121 ->
+  // 102 us; 405 of 15 frames, half kept, 301 -> 250 us.  Where attention is not peaked it makes no difference.)
   const bool few = k * SUB < kPeekTiles * parts;
   const unsigned my_bit = live ? (1u << (kMemberBit + lblock)) : 0u;
-  int* first = wcount;                                // [groups] that entry of each group, -1: nobody looks
+  const unsigned my_entry = (unsigned)(my_block * SUB + qsub);        // (not met where the group has no block)
+  constexpr int kTaker = 20;                          // the field of `first` that says which wave takes it
+  int* first = wcount;                                // [groups] that entry of each group and who takes it, -1: nobody looks
   {
     int f = -1;
     if (live && !few && parts > 1)
       for (int base = 0; base < nU; base += 64) {
-        const unsigned long long m = __ballot(base + lane < nU && (ulist[min(base + lane, nU - 1)] & my_bit) != 0u);
-        if (m) {
-          f = base + (int)__builtin_ctzll(m);
+        const unsigned e = ulist[min(base + lane, nU - 1)];
+        const unsigned long long ours = __ballot(base + lane < nU && (e & my_bit) != 0u);
+        if (ours) {
+          const unsigned long long own = __ballot((e & ((1u << kValidBit) - 1u)) == my_entry) & (base ? 0ull : ours);
+          const int i = (int)__builtin_ctzll(own ? own : ours);
+          f = (base + i) | wave_of_turn(__popcll(ours & ((1ull << i) - 1ull)), SUB, parts) << kTaker;
           break;
         }
       }
@@ -743,7 +752,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const int live_groups = __builtin_amdgcn_readfirstlane(ctrl[28]);
   int first_of[4];                                    // (where a group has one wave nobody looks)
 #pragma unroll
-  for (int w = 0; w < 4; ++w) first_of[w] = __builtin_amdgcn_readfirstlane(first[w]);
+  for (int w = 0; w < 4; ++w) first_of[w] = __builtin_amdgcn_readfirstlane(first[w]) & ((1 << kTaker) - 1);
   // one wave brings the K tile of union entry u into ring slot u % RING
   auto issue_tile = [&](int u, int slot) {
     const unsigned e = (unsigned)__builtin_amdgcn_readfirstlane((int)ulist[u]);
@@ -869,8 +878,9 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   auto walk = [&](auto queries) {
     constexpr int NQ = decltype(queries)::value;
     const bool follow = parts == 1 && k * SUB < kFollowTiles;
-    const int u = parts > 1 ? __builtin_amdgcn_readfirstlane(first[lgroup]) : -1;
-    if (live && part > 0 && u >= 0) {
+    const int look_at = parts > 1 ? __builtin_amdgcn_readfirstlane(first[lgroup]) : -1;
+    if (live && look_at >= 0 && part != look_at >> kTaker) {
+      const int u = look_at & ((1 << kTaker) - 1);
       const int slot = arrived(u);
       gave_up = slot < 0;
       if (!gave_up) {
