@@ -484,10 +484,9 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_TOTAL];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
-  // Heads one after the other (the K/V of the heads in flight then fit the last-level cache);
-  // inside a head a unit is one patch position and FG consecutive frames, and the frame
-  // groups of one position follow each other on one XCD (workgroups are dealt round-robin to the
-  // 8 XCDs).
+  // Heads one after the other (the K/V of the heads in flight then fit the last-level cache); inside a head a unit is one
+  // patch position and FG consecutive frames (or left-over frames of a few positions: unit_place).  Units are dealt to the 8 XCDs in
+  // turn, as workgroups are; only the shares of one unit stay together on one.
   constexpr int LOG_FG = SUB == 1 ? 3 : 2;
   constexpr int FG = 1 << LOG_FG;                     // query blocks (frames) per unit
   constexpr int BLOCK = BS * SUB;                     // slots per block
@@ -511,7 +510,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const int lblock = group / SUB - first_slot;        // my query block's number among them
   // block number of query block w of this workgroup, -1 if the place is empty (then all after it are)
   auto slot_block = [&](int w) -> int {
-    const int p = place.pos0 + ((first_slot + w) >> place.lg), fr = place.frame0 + ((first_slot + w) & ((1 << place.lg) - 1));
+    const int p = unit_pos(place, first_slot + w), fr = unit_frame(place, first_slot + w);
     return w < blocks && p < per_frame ? fr * per_frame + p : -1;
   };
   if (slot_block(0) < 0) return;                      // past the last position

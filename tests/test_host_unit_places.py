@@ -13,7 +13,7 @@ using namespace da::ring;
 extern "C" int units(int T, int fg, int per_frame) { return units_per_head(T, fg, per_frame); }
 extern "C" void place(int n, int T, int log_fg, int per_frame, int* out) {
   const UnitPlace u = unit_place(n, T, log_fg, per_frame);
-  out[0] = u.pos0; out[1] = u.frame0; out[2] = u.lg;
+  for (int w = 0; w < 1 << log_fg; ++w) { out[2 * w] = unit_pos(u, w); out[2 * w + 1] = unit_frame(u, w); }
 }
 extern "C" void share(long long total, long long tiles, int least, int* out) {
   const Share s = share_out(total, tiles, least);
@@ -44,21 +44,25 @@ def lib(tmp_path_factory):
 @pytest.mark.parametrize("log_fg", [2, 3])
 @pytest.mark.parametrize("per_frame", [1, 2, 7, 8, 28, 60])
 def test_every_block_has_one_place(lib, log_fg, per_frame):
-    fg, out = 1 << log_fg, (ctypes.c_int * 3)()
+    fg, out = 1 << log_fg, (ctypes.c_int * 16)()
     for T in list(range(1, 36)) + [65]:
-        seen = set()
+        seen, positions = set(), []
         units = lib.units(T, fg, per_frame)
         for n in range(units):
             lib.place(n, T, log_fg, per_frame, out)
-            pos0, frame0, lg = out
-            blocks = [(pos0 + (w >> lg), frame0 + (w & ((1 << lg) - 1))) for w in range(fg)]
+            blocks = [(out[2 * w], out[2 * w + 1]) for w in range(fg)]
             live = [b for b in blocks if b[0] < per_frame]
             assert blocks[:len(live)] == live and live          # empty places only at the end
             assert all(f < T for _, f in live)
             assert not seen & set(live)
             seen |= set(live)
+            positions.append(len({p for p, _ in live}))
         assert len(seen) == T * per_frame
-        assert units <= T * per_frame // fg + log_fg + 1        # at most one unit with empty places per power of two
+        assert units == -(-T * per_frame // fg)                 # at most one unit with empty places
+        # left-over frames of a position are in one unit or in two: as few positions to a unit as that allows
+        left = T % fg
+        assert max(positions) <= (1 if not left else -(-fg // left) + 1)
+        assert sum(positions) <= units + per_frame * (left > 0)
 
 
 @pytest.mark.parametrize("least", [0, 1])
