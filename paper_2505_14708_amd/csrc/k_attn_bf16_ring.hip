@@ -1122,7 +1122,8 @@ hipError_t launch_attn_bf16_ring(const Geo& q, const void* Qp, const void* Kp, c
   int least = 0;
   while (least < 1 && aux_bytes(q, row_ptr != nullptr, least) > ring::AUX_BYTES) ++least;
   const int fg = 8 / sub, per_frame = q.gh * q.gw;
-  const ring::Share share = ring::share_out((long long)q.B * q.H * ring::units_per_head(q.T, fg, per_frame), (long long)q.k * sub, least);
+  const ring::Share share = ring::share_out((long long)q.B * q.H * ring::units_per_head(q.T, fg, per_frame), (long long)q.k * sub,
+                                            row_ptr != nullptr, least);
   const float skip = log2f((float)q.k * (float)q.block) + ring::kDropLog2;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(share.grid), dim3(512), 0, s, q, (const unsigned char*)Qp, (const unsigned char*)Kp,

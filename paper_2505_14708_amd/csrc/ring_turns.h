@@ -55,32 +55,36 @@ DA_HOST_DEVICE inline ShareOf share_of(const Share& s, int b) {
   return {(past < 0 ? 0 : s.first) + (nth >> (3 + lsub)) * 8 + (nth & 7), lsub, (nth >> 3) & ((1 << lsub) - 1)};
 }
 
-// A workgroup fills a CU, so a launch of few comes in rounds of kCUs and the last round takes as long as a full one however
-// few are in it.  With two, four or eight workgroups to a unit there are as many times the waves to each list, and a
+// A workgroup fills a CU, so a launch of few comes in rounds of kCUs and the last round takes as long as a full one
+// however few are in it.  With two, four or eight workgroups to a unit there are as many times the waves to each list, and a
 // workgroup is done in about 0.55, 0.35 and 0.25 of the time (tiles are shared by fewer, the fixed part stays).  Times of
-// da_forward in us, whole units / halves / quarters / eighths (bold what is taken):
+// da_forward in us, whole units / halves / quarters / eighths (bold what is taken; units of a list of k entries each):
 //   - at most half a round is shared out so that it fills one: 18 units of 24 tiles 64 / 46 / 41 / *38*, 26 of 52 174 / 120 /
 //     97 / *82*, 36 of 17 129 / 106 / *95* / 108, 45 of 7 75 / 59 / *56* / 71, 90 of 12 104 / *81* / 89, 120 of 96 360 / *234* / 267;
-//   - up to three quarters of a round, as halves but for 64 as quarters (whole / *so*): 144 of 28 111 / 112, 160 of 51 253 /
-//     *211*, 180 of 238 785 / *717*, 184 of 37 220 / *196*, but 144 of 14 *100* / 107, 176 of 15 *122* / 128: where lists are
-//     short, the fixed part is most of it.  216 of 28 *174* / 190;
-//   - up to four rounds, the last few: 288 of 58 410, 64 of them as quarters *327*; 790 of 315 4956, *4353*; 1024 lists of any length
-//     (102 on average) 2278, *2110*; 360 dense ones of 720 2268, 104 of them as halves *1808*;
+//   - up to three quarters of a round, as halves but for 64 as quarters, so that a CU has two at most (whole / *so*): 136 of 40 176 / 171, of 120 397 /
+//     370, 160 of 64 248 / 240, 176 of 64 254 / 246, 192 of 120 428 / 416.  Not where lists are short, for the fixed part is most of it
+//     (144 of 20 *121* / 123, 176 of 28 *148* / 151, 192 of 28 *152* / 158), nor where a CU would get three (189 of 42 *192* / 230, 190 of
+//     75 *312* / 364).  More units are whole: 208 of 64 *270* / 326, 240 of 28 *169* / 202;
+//   - up to four rounds, what a last round has of at most half: up to 64 units as quarters (288 of 64 499 / 371, 576 of 64 785 /
+//     674), more as halves (384 of 64 516 / 456, 896 of 64 1080 / 1033; 640 of 64 799 / 737).  A fuller or full one stays (512 of 64 *589* / 639 with 64 as quarters,
+//     768 *878* / 923, 1024 *1174* / 1223, 448 *541* / 548), but for lists of any length, whose units end at different times: 1024 of
+//     102 on average 2278 / *2110*;
 //   - and 64 as halves after that, for units differ in length: 5952 of 198 12080, *11918*, nothing dropped 20167, *20103*.
 constexpr int kCUs = 256;
-constexpr int kShortList = 24;
-// total: units of the launch; tiles: entries of a list; least: units are shared by at least 2^least (LDS)
-inline Share share_out(long long total, long long tiles, int least) {
+constexpr int kLongList = 36;
+// total: units of the launch; tiles: entries of a list (on average, where they are of any length); least: units are shared by at
+// least 2^least (LDS)
+inline Share share_out(long long total, long long tiles, bool any_length, int least) {
   int split[2] = {0, 0};
   long long rest = 0;
   if (total <= kCUs / 8) split[0] = 3;
   else if (total <= kCUs / 4) split[0] = 2;
   else if (total <= kCUs / 2) split[0] = 1;
-  else if (total <= kCUs / 4 * 3 && tiles >= kShortList) split[0] = 1, split[1] = 2, rest = kCUs / 4;
+  else if (total <= kCUs / 4 * 3 && (total % 8 == 0 || total < kCUs / 4 * 3 - 8) && tiles >= kLongList) split[0] = 1, split[1] = 2, rest = kCUs / 4;
   else if (total > kCUs && total <= 4 * kCUs) {
     const int last = (int)(total % kCUs);
     if (last > kCUs / 4 && last <= kCUs / 2) split[1] = 1, rest = last;
-    else split[1] = 2, rest = kCUs / 4;
+    else if (any_length || (last > 0 && last <= kCUs / 4)) split[1] = 2, rest = kCUs / 4;
   } else if (total > kCUs) split[1] = 1, rest = kCUs / 4;
   for (int& x : split) x = x < least ? least : x;
   if (rest && split[0]) rest += (total - rest) % 8;

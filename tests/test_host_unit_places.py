@@ -15,12 +15,12 @@ extern "C" void place(int n, int T, int log_fg, int per_frame, int* out) {
   const UnitPlace u = unit_place(n, T, log_fg, per_frame);
   for (int w = 0; w < 1 << log_fg; ++w) { out[2 * w] = unit_pos(u, w); out[2 * w + 1] = unit_frame(u, w); }
 }
-extern "C" void share(long long total, long long tiles, int least, int* out) {
-  const Share s = share_out(total, tiles, least);
+extern "C" void share(long long total, long long tiles, int any_length, int least, int* out) {
+  const Share s = share_out(total, tiles, any_length, least);
   out[0] = s.first; out[1] = s.split[0]; out[2] = s.split[1]; out[3] = (int)s.grid;
 }
-extern "C" void shares(long long total, long long tiles, int least, int grid, int* out) {
-  const Share s = share_out(total, tiles, least);
+extern "C" void shares(long long total, long long tiles, int any_length, int least, int grid, int* out) {
+  const Share s = share_out(total, tiles, any_length, least);
   for (int b = 0; b < grid; ++b) {
     const ShareOf w = share_of(s, b);
     out[3 * b] = w.unit; out[3 * b + 1] = w.lsub; out[3 * b + 2] = w.sub;
@@ -36,8 +36,8 @@ def lib(tmp_path_factory):
     src.write_text(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(out)], check=True)
     f = ctypes.CDLL(str(out))
-    f.share.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_void_p]
-    f.shares.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    f.share.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    f.shares.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
     return f
 
 
@@ -66,15 +66,16 @@ def test_every_block_has_one_place(lib, log_fg, per_frame):
 
 
 @pytest.mark.parametrize("least", [0, 1])
+@pytest.mark.parametrize("any_length", [0, 1])
 @pytest.mark.parametrize("tiles", [3, 200])
-def test_every_share_has_one_workgroup(lib, tiles, least):
+def test_every_share_has_one_workgroup(lib, tiles, any_length, least):
     s = (ctypes.c_int * 4)()
     for total in list(range(1, 540)) + [1023, 1024, 1025, 5952]:
-        lib.share(total, tiles, least, s)
+        lib.share(total, tiles, any_length, least, s)
         first, split0, split1, grid = s
         assert min(split0, split1) >= least and grid > 0
         out = (ctypes.c_int * (3 * grid))()
-        lib.shares(total, tiles, least, grid, out)
+        lib.shares(total, tiles, any_length, least, grid, out)
         seen, xcd, idle = set(), {}, 0
         for b in range(grid):
             unit, lsub, sub = out[3 * b:3 * b + 3]
@@ -87,3 +88,17 @@ def test_every_share_has_one_workgroup(lib, tiles, least):
             assert xcd.setdefault(unit, b % 8) == b % 8
         assert len(seen) == sum(1 << (split0 if u < first else split1) for u in range(total))
         assert idle <= 7 << max(split0, split1)
+
+
+def test_full_rounds_are_not_shared(lib):
+    """Lists of one length: where the last of up to four rounds is empty or more than half full every unit is one workgroup, and no
+    CU gets a third share of a launch of less than a round."""
+    s = (ctypes.c_int * 4)()
+    for tiles in (3, 26, 40, 200):
+        for total in range(1, 1025):
+            lib.share(total, tiles, 0, 0, s)
+            first, split0, split1, grid = s
+            if total > 256 and (total % 256 == 0 or total % 256 > 128) or 192 < total <= 256:
+                assert (first, split0, grid) == ((total + 7) // 8 * 8, 0, (total + 7) // 8 * 8)
+            if 128 < total <= 192:
+                assert grid <= 512 and (split0 == 0 or tiles >= 36)
