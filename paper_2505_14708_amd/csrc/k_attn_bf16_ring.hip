@@ -950,7 +950,8 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   publish();
   if (tile_counts != nullptr && lane == 0 && tally) {
     atomicAdd(&tile_counts[0], (unsigned long long)(tally & 0xffffu));
-    atomicAdd(&tile_counts[1], (unsigned long long)(((tally >> 16) + (part & 1)) >> 1));   // (odd: up in one wave, down in the other)
+    // (odd: up in every other wave, whether the waves of a workgroup share lists or not)
+    atomicAdd(&tile_counts[1], (unsigned long long)(((tally >> 16) + ((lgroup + part) & 1)) >> 1));
   }
   if (gave_up && lane == 0) {
     atomicAdd(&g_wait_failures, 1ull);

@@ -57,3 +57,36 @@ def test_half_dropped_tiles(T, fh, fw, best, pw):
         # what a wave meets first is carried out, whatever it is worth
         assert query_tiles * 0.5 * (tiles - short) - 8 * tiles <= kept <= query_tiles * (0.5 * (tiles - short) + 8)
         assert kept < seen or tiles <= 8
+
+
+def test_odd_counts_are_rounded_evenly():
+    """Seven frames of 8x12: blocks of 64 and of 32 valid slots, 200 units of one wave per list.  A wave with 32 queries carries out half
+    of each of seven whole tiles and seven short ones: its count is 10.5, and 700 such waves are to round up about as often as down (of the seven of a head one more)."""
+    import torch
+    say("tile counts, odd counts of one wave per list")
+    T, fh, fw, H = 7, 8, 12, 100
+    p = da.problem(1, H, T, fh, fw, 128, 8, 8)
+    dims = da.da_derive(p)
+    n = T * fh * fw
+    perm = torch.empty(dims.n_pad, dtype=torch.int32, device="cuda")
+    da.da_build_perm(p, perm, None, None)
+    tokens = perm.cpu().numpy()
+    slot = np.empty(n, np.int64)
+    slot[tokens[tokens >= 0]] = np.nonzero(tokens >= 0)[0] % 64
+    Q = np.zeros((1, H, n, 128))
+    K = np.zeros_like(Q)
+    Q[..., 0], K[..., 0] = 32.0, np.where(slot < 32, 16.0, -16.0)
+    q, k = (to_dev(W.to_storage(a, W.BF16), W.BF16) for a in (Q, K))
+    Kp = empty((1, H, dims.n_pad, 128), W.BF16)
+    Vt, O = torch.empty_like(Kp), empty((1, H, n, 128), W.BF16)
+    da.da_permute(p, k, Kp, da.DA_REORDER_ROWS)
+    da.da_permute(p, k, Vt, da.DA_REORDER_VOP)
+    idx = torch.arange(dims.g, dtype=torch.int32, device="cuda").repeat(H * dims.g, 1).contiguous()
+    counts = torch.zeros(2, dtype=torch.int64, device="cuda")
+    da.da_sparse_attn_ex(p, q, Kp, Vt, idx, O, None, 1, counts)
+    torch.cuda.synchronize()
+    seen, kept = (int(c) for c in counts.cpu())
+    assert seen == H * T * (2 + 1) * 2 * T
+    exact = H * T * 3 * (7 * 0.5 + 7)
+    say(f"  carried out {kept}, exactly {exact}")
+    assert abs(kept - exact) <= 0.1 * H * T
