@@ -74,9 +74,9 @@ __global__ __launch_bounds__(256) void permute_vt_kernel(Geo q, const E* __restr
 __global__ __launch_bounds__(256) void prepare_dense_kernel(Geo q, const chunk16* __restrict__ K, const uint16_t* __restrict__ V,
                                                             chunk16* __restrict__ Kp, uint16_t* __restrict__ Vt,
                                                             int32_t* __restrict__ idx, int32_t* __restrict__ row_ptr,
-                                                            long long head_stride, int cpr, unsigned blocks) {
+                                                            long long head_stride, int cpr) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const unsigned what = blockIdx.x / blocks, b = blockIdx.x - what * blocks;
+  const unsigned what = blockIdx.y, b = blockIdx.x;
   const unsigned bh = b / (unsigned)q.g;
   const int i = (int)(b - bh * (unsigned)q.g);
   if (what == 0) {
@@ -94,9 +94,10 @@ __global__ __launch_bounds__(256) void prepare_dense_kernel(Geo q, const chunk16
 
 hipError_t launch_prepare_dense(const Geo& q, const void* K, const void* V, void* Kp, void* Vt, int32_t* idx, int32_t* row_ptr,
                                 long long head_stride, hipStream_t s) {
+  // (a launch has fewer than 2^32 threads along an axis: along x alone six million blocks would be too many)
   const unsigned blocks = (unsigned)((long long)q.B * q.H * q.g);
-  hipLaunchKernelGGL(prepare_dense_kernel, dim3(blocks * (Kp ? 3 : 2)), dim3(256), vt_block_lds(q), s, q, (const chunk16*)K,
-                     (const uint16_t*)V, (chunk16*)Kp, (uint16_t*)Vt, idx, row_ptr, head_stride, q.d / 8, blocks);
+  hipLaunchKernelGGL(prepare_dense_kernel, dim3(blocks, Kp ? 3 : 2), dim3(256), vt_block_lds(q), s, q, (const chunk16*)K,
+                     (const uint16_t*)V, (chunk16*)Kp, (uint16_t*)Vt, idx, row_ptr, head_stride, q.d / 8);
   return hipGetLastError();
 }
 

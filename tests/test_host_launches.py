@@ -1,0 +1,27 @@
+"""Which kernels a call launches and with what grids, recorded on the CPU with a stand-in for the HIP runtime's launch functions."""
+import os
+
+import pytest
+
+from paper_2505_14708_amd import binding as da
+from launch_recorder import record
+
+pytestmark = pytest.mark.skipif(not os.path.exists(da.LIB_PATH), reason="library not built")
+
+
+def _problem(B, H, T, fh, fw, keep, *, d=128, pw=8, dtype=da.DA_BF16):
+    return dict(B=B, H=H, T=T, fh=fh, fw=fw, d=d, ph=8, pw=pw, dtype=dtype, keep_blocks=keep, sparsity=0.0, pool=0, reserved=0)
+
+
+def test_grids_stay_within_the_launch_limits(tmp_path):
+    """A launch has fewer than 2^32 threads along each axis and at most 65535 workgroups along y and z.  Frames that are
+    mostly padding make many blocks of few tokens: 7500 heads of 100 frames of 1x57 tokens are six million blocks, 200 GB of reordered K
+    and V beside 44 GB of Q, K, V and O, which a card with 288 GB holds."""
+    calls = [(e, _problem(1, 7500, 100, 1, 57, k)) for e in ("da_forward", "da_forward_global") for k in (1, 320, 800)]
+    calls += [(e, _problem(1, 60000, 100, 1, 1, k)) for e in ("da_forward", "da_forward_blocks", "da_forward_global") for k in (1, 40, 100)]
+    calls += [(e, _problem(1, 3, 1700, 9, 9, k)) for e in ("da_forward", "da_forward_global") for k in (1, 600, 6800)]
+    for (entry, p), (status, launches) in zip(calls, record(str(tmp_path), calls)):
+        assert status == da.DA_OK and launches, (entry, p)
+        for name, grid, group, lds in launches:
+            assert all(0 < n * g < 1 << 32 for n, g in zip(grid, group)), (name, grid, group, p)
+            assert max(grid[1:]) <= 65535, (name, grid)
