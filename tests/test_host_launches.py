@@ -25,3 +25,16 @@ def test_grids_stay_within_the_launch_limits(tmp_path):
         for name, grid, group, lds in launches:
             assert all(0 < n * g < 1 << 32 for n, g in zip(grid, group)), (name, grid, group, p)
             assert max(grid[1:]) <= 65535, (name, grid)
+
+
+@pytest.mark.parametrize("dtype,d", [(da.DA_BF16, 128), (da.DA_F32, 64)])
+def test_logits_and_lists_in_one_launch(tmp_path, dtype, d):
+    """Where a map's rows have at most 64 columns and there are at most two workgroups (of 32 rows) for every CU, or a workgroup has
+    at least 16 of its rows and the map no more."""
+    cases = [(B * 24, g) for B in (1, 5, 11, 21, 22, 64) for g in (2, 15, 16, 28, 32, 33, 64, 65)]
+    calls = [("da_forward", _problem(1, H, g, 8, 8, 1, d=d, dtype=dtype)) for H, g in cases]
+    for (H, g), (status, launches) in zip(cases, record(str(tmp_path), calls)):
+        assert status == da.DA_OK
+        names = " ".join(l[0] for l in launches)
+        one = g <= 64 and (H * -(-g // 32) <= 512 or 16 <= g <= 32)
+        assert ("draft_select_kernel" in names, "draft_logits_kernel" in names) == (one, not one), (H, g)
