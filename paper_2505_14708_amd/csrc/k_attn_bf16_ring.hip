@@ -494,7 +494,8 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const int per_head = units_per_head(q.T, FG, per_frame);
   // The eight groups of 64 queries of a unit are shared between 2^lsub workgroups, with 2^lsub waves to a group.
   const ShareOf mine_is = share_of(share, (int)blockIdx.x);
-  const int lsub = mine_is.lsub, sub = mine_is.sub;
+  // (a head of at most four groups: the other half of its unit is empty, and the waves share the lists of this one)
+  const int lsub = mine_is.lsub == 0 && q.g * SUB <= 4 ? 1 : mine_is.lsub, sub = mine_is.sub;
   const long long bh = mine_is.unit / per_head;
   if (bh >= (long long)q.B * q.H) return;             // (the last eight units need not be eight)
   const UnitPlace place = unit_place(mine_is.unit - (int)bh * per_head, q.T, LOG_FG, per_frame);
