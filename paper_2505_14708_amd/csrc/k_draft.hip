@@ -134,11 +134,7 @@ __global__ __launch_bounds__(256) void draft_logits_kernel(Geo q, const float* _
 }
 
 // Logits and lists in one launch where a row of the map is short (g <= kFusedColumns): a workgroup of eight waves owns 32
-<<<<<<< Updated upstream
 // rows of one head's map, a wave 32 columns of them, and the map goes no further than LDS.  Small launches do not
-=======
-// rows of one head's map, a wave 32 columns of them, and the map goes no further than LDS.  Launches of up to a workgroup per CU do not
->>>>>>> Stashed changes
 // fill the chip, and what they take is a chain of latencies: one launch less, no trip of the map through memory, and the
 // operands come straight from the pooled rows into registers, without stages and barriers (a lane asks for four channels at
 // a time and uses the two of its half-wave: the chain of products is draft_logits_kernel's, and so are the bits).
@@ -146,17 +142,10 @@ __global__ __launch_bounds__(256) void draft_logits_kernel(Geo q, const float* _
 // da_forward, us, two launches -> one: 2 x 8 x 8 (64 channels) 23.7 -> 21.7, 2 x 25 x 25 49.1 -> 46.4, 48 x 28 x 28 104.6 ->
 // 102.6.  Wider rows gain nothing (4 x 84 x 84 193 either way) or lose (6 x 180 x 180 145 -> 154, 4 x 240 x 240 431 -> 442; with the
 // operands by way of LDS 2 x 252 x 252 120 -> 126): fewer workgroups share the selection, which is then the longer part.
-<<<<<<< Updated upstream
 // More than two workgroups for every CU, and the waves without columns or rows cost more than the launch, unless most of a tile's 32
 // rows are there (maps x g x g, da_forward, two launches / one, what is taken in *): 384 x 3 73.6 / *72.9*, x 8 118.5 / *116.8*, x 12 197.3 /
 // *196.5*, 192 x 40 260.8 / *257.5*, 288 x 40 *382* / 384, 576 x 40 *763* / 768, x 64 *1605* / 1602, 768 x 4 *122.9* / 124.4, 1536 x 4 *242* / 257, x 9 *657* /
 // 668, but 384 x 16 254.7 / *251.8*, x 28 615.9 / *611.8*, 1536 x 28 2374 / *2360*, x 32 2756 / *2733*.
-=======
-// More workgroups than CUs, and the waves without columns or rows cost more than the launch, unless most of a tile's 32 rows are
-// there (maps x g x g, two launches / one, what is taken in *): 192 x 40 260.8 / *257.5*, 288 x 40 *385* / 388, x 64 *847* / 849,
-// 384 x 4 *78.1* / 78.8, 1536 x 4 *240* / 253, x 8 *443* / 453, but 384 x 16 254.7 / *251.8*, x 28 615.9 / *611.8*, 1536 x 28 2374 / *2360*, x 32
-// 2756 / *2733*.
->>>>>>> Stashed changes
 constexpr int kFusedColumns = 64;
 constexpr int FR = 32;                                   // rows of a workgroup
 constexpr int FW = 8;                                    // waves
@@ -276,11 +265,7 @@ hipError_t launch_row_softmax(const Geo& q, const float* logits, float* draft, h
 
 bool draft_select_fits(const Geo& q) {
   const long long groups = (q.g + FR - 1) / FR * (long long)q.B * q.H;
-<<<<<<< Updated upstream
   return q.g <= kFusedColumns && q.d % 64 == 0 && (groups <= 512 || (q.g >= FR / 2 && q.g <= FR));
-=======
-  return q.g <= kFusedColumns && q.d % 64 == 0 && (groups <= 256 || (q.g >= FR / 2 && q.g <= FR));
->>>>>>> Stashed changes
 }
 
 hipError_t launch_draft_select(const Geo& q, const float* q_pool, const float* k_pool, int32_t* idx, hipStream_t s) {

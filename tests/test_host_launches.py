@@ -29,22 +29,12 @@ def test_grids_stay_within_the_launch_limits(tmp_path):
 
 @pytest.mark.parametrize("dtype,d", [(da.DA_BF16, 128), (da.DA_F32, 64)])
 def test_logits_and_lists_in_one_launch(tmp_path, dtype, d):
-<<<<<<< Updated upstream
     """Where a map's rows have at most 64 columns and there are at most two workgroups (of 32 rows) for every CU, or a workgroup has
     at least 16 of its rows and the map no more."""
     cases = [(B * 24, g) for B in (1, 5, 11, 21, 22, 64) for g in (2, 15, 16, 28, 32, 33, 64, 65)]
-=======
-    """Where a map's rows have at most 64 columns and there is at most a workgroup (32 rows) for every CU, or a workgroup has
-    at least 16 of its rows and the map no more."""
-    cases = [(B * 24, g) for B in (1, 5, 10, 11, 64) for g in (2, 15, 16, 28, 32, 33, 64, 65)]
->>>>>>> Stashed changes
     calls = [("da_forward", _problem(1, H, g, 8, 8, 1, d=d, dtype=dtype)) for H, g in cases]
     for (H, g), (status, launches) in zip(cases, record(str(tmp_path), calls)):
         assert status == da.DA_OK
         names = " ".join(l[0] for l in launches)
-<<<<<<< Updated upstream
         one = g <= 64 and (H * -(-g // 32) <= 512 or 16 <= g <= 32)
-=======
-        one = g <= 64 and (H * -(-g // 32) <= 256 or 16 <= g <= 32)
->>>>>>> Stashed changes
         assert ("draft_select_kernel" in names, "draft_logits_kernel" in names) == (one, not one), (H, g)
