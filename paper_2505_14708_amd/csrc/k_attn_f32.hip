@@ -320,7 +320,7 @@ hipError_t launch_attn_f32(const Geo& q, const float* Q, const float* K, const f
                            const int32_t* idx, const int32_t* row_ptr, long long cap, float* O, float* lse, hipStream_t s) {
   // (in block order every slot is a query's; else the last patches of a row, a column or both may have too few)
   const int last_h = (q.fh - 1) % q.ph + 1, last_w = (q.fw - 1) % q.pw + 1;
-  const bool even = q.reordered || (last_h * last_w > 32 && last_h * q.pw > 32 && q.ph * last_w > 32);
+  const bool even = !row_ptr && (q.reordered || (last_h * last_w > 32 && last_h * q.pw > 32 && q.ph * last_w > 32));
   const F32Share share = f32_share_out(2LL * q.B * q.H * q.g, even, q.d);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(share.grid), dim3(64 * W), 0, s, q, Q, K, V, idx, row_ptr, cap, O, lse, share);

@@ -38,3 +38,12 @@ def test_logits_and_lists_in_one_launch(tmp_path, dtype, d):
         names = " ".join(l[0] for l in launches)
         one = g <= 64 and (H * -(-g // 32) <= 512 or 16 <= g <= 32)
         assert ("draft_select_kernel" in names, "draft_logits_kernel" in names) == (one, not one), (H, g)
+
+
+def test_float32_last_rounds_in_pieces(tmp_path):
+    """One head of 28 frames of 39x45 tokens: 210 half blocks to an XCD, all of which hold queries, 64 at a time.  The last 18 are cut in
+    two only where lists are of any length."""
+    p = _problem(1, 1, 28, 39, 45, 84, dtype=da.DA_F32)
+    grids = [[g for name, g, _, _ in launches if "attn_f32" in name][0][0] for _, launches in
+             record(str(tmp_path), [("da_forward", p), ("da_forward_global", p), ("da_forward", dict(p, keep_blocks=840))])]
+    assert grids == [8 * 210, 8 * (192 + 2 * 18), 8 * 210]
