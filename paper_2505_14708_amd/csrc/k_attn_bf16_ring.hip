@@ -493,12 +493,11 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   const int per_frame = q.gh * q.gw;
   const int per_head = units_per_head(q.T, FG, per_frame);
   // The eight groups of 64 queries of a unit are shared between 2^lsub workgroups, with 2^lsub waves to a group.
-  const ShareOf mine_is = share_of(share, (int)blockIdx.x);
-  // (a head of at most four groups: the other half of its unit is empty, and the waves share the lists of this one)
-  const int lsub = mine_is.lsub == 0 && q.g * SUB <= 4 ? 1 : mine_is.lsub, sub = mine_is.sub;
-  const long long bh = mine_is.unit / per_head;
+  const ShareOf mine_is = share_of(share, (int)blockIdx.x, per_head, left_units(q.T, FG, per_frame));
+  const int lsub = mine_is.lsub, sub = mine_is.sub;
+  const long long bh = mine_is.head;
   if (bh >= (long long)q.B * q.H) return;             // (the last eight units need not be eight)
-  const UnitPlace place = unit_place(mine_is.unit - (int)bh * per_head, q.T, LOG_FG, per_frame);
+  const UnitPlace place = unit_place(mine_is.unit, q.T, LOG_FG, per_frame);
   // waves w and w+4 share a SIMD: they have different groups where there are some.
   // The waves of a group take its list entries in turn (part = which of them).
   const int groups = 8 >> lsub, parts = 1 << lsub;
@@ -1123,9 +1122,7 @@ hipError_t launch_attn_bf16_ring(const Geo& q, const void* Qp, const void* Kp, c
   const int sub = q.block / ring::BS;
   int least = 0;
   while (least < 1 && aux_bytes(q, row_ptr != nullptr, least) > ring::AUX_BYTES) ++least;
-  const int fg = 8 / sub, per_frame = q.gh * q.gw;
-  const ring::Share share = ring::share_out((long long)q.B * q.H * ring::units_per_head(q.T, fg, per_frame), (long long)q.k * sub,
-                                            row_ptr != nullptr, least);
+  const ring::Share share = ring::share_out((long long)q.B * q.H, (long long)q.g * sub, (long long)q.k * sub, row_ptr != nullptr, least);
   const float skip = log2f((float)q.k * (float)q.block) + ring::kDropLog2;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(share.grid), dim3(512), 0, s, q, (const unsigned char*)Qp, (const unsigned char*)Kp,

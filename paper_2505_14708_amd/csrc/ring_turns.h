@@ -38,57 +38,87 @@ DA_HOST_DEVICE inline UnitPlace unit_place(int n, int T, int log_fg, int per_fra
 DA_HOST_DEVICE inline int unit_pos(const UnitPlace& u, int w) { return u.pos0 + (((u.first + w) * u.recip) >> 8); }
 DA_HOST_DEVICE inline int unit_frame(const UnitPlace& u, int w) { return u.frame0 + u.first + w - (((u.first + w) * u.recip) >> 8) * u.frames; }
 
-// The first `first` units of a launch are shared by 2^split[0] workgroups each, the others by 2^split[1].  (`first` is a
-// multiple of eight where there are others and split[0] is not 0.)
+// Either all units of a launch are shared by 2^split[0] workgroups each, and then shares without a group have none: `head_shares` to a
+// head.  (A workgroup that finds nothing to do still takes a CU for 6 us, as much as all of the LDS needs to change hands: 250 heads of
+// one block as eighths 21 -> 69 us if seven of eight are empty.)  Or (head_shares 0) the first `first` units are shared by 2^split[0]
+// workgroups each, the others by 2^split[1].  (`first` is a multiple of eight where there are others and split[0] is not 0.)
 struct Share {
   int first, split[2];
   unsigned grid;
+  int head_shares;
 };
 // what workgroup `b` of a launch is
 struct ShareOf {
-  int unit, lsub, sub;    // share number `sub` of the 2^lsub of that unit
+  int head, unit, lsub, sub;    // share number `sub` of the 2^lsub of that unit of that head
 };
-DA_HOST_DEVICE inline ShareOf share_of(const Share& s, int b) {
+// left: units of left-over frames among the per_head units of a head
+DA_HOST_DEVICE inline ShareOf share_of(const Share& s, int b, int per_head, int left) {
+  if (s.head_shares) {
+    // (the shares of a unit are eight apart: on one XCD, but for the last few.  Where a head has only one, heads go to the XCDs in turn,
+    // as in the launch that leaves K and V in their L2: 96 and 128 heads of one block 20.7 and 21.5 -> 19.8 and 20.0 us.)
+    const int lsub = s.split[0], mask = (1 << lsub) - 1, stretch = b & ~(8 * mask + 7);
+    const bool apart = s.head_shares > 1 && stretch + 8 * mask + 8 <= (int)s.grid;
+    const int nth = apart ? stretch + ((b & 7) << lsub) + ((b >> 3) & mask) : b;
+    const int head = nth / s.head_shares, r = nth - head * s.head_shares;
+    // (the last unit of left-over frames, the one with empty places, is a head's last one here)
+    const int unit = (r >> lsub) + left;
+    return {head, unit < per_head ? unit : unit - per_head, lsub, r & mask};
+  }
   const int past = b - (s.first << s.split[0]);
   const int lsub = past < 0 ? s.split[0] : s.split[1], nth = past < 0 ? b : past;
   // (the shares of a unit are eight apart: on one XCD)
-  return {(past < 0 ? 0 : s.first) + (nth >> (3 + lsub)) * 8 + (nth & 7), lsub, (nth >> 3) & ((1 << lsub) - 1)};
+  const int unit = (past < 0 ? 0 : s.first) + (nth >> (3 + lsub)) * 8 + (nth & 7), head = unit / per_head;
+  return {head, unit - head * per_head, lsub, (nth >> 3) & ((1 << lsub) - 1)};
 }
 
 // A workgroup fills a CU, so a launch of few comes in rounds of kCUs and the last round takes as long as a full one
 // however few are in it.  With two, four or eight workgroups to a unit there are as many times the waves to each list, and a
 // workgroup is done in about 0.55, 0.35 and 0.25 of the time (tiles are shared by fewer, the fixed part stays).  Times of
 // da_forward in us, whole units / halves / quarters / eighths (bold what is taken; units of a list of k entries each):
-//   - at most half a round is shared out so that it fills one: 18 units of 24 tiles 64 / 46 / 41 / *38*, 26 of 52 174 / 120 /
-//     97 / *82*, 36 of 17 129 / 106 / *95* / 108, 45 of 7 75 / 59 / *56* / 71, 90 of 12 104 / *81* / 89, 120 of 96 360 / *234* / 267;
-//   - up to three quarters of a round, as halves but for 64 as quarters, so that a CU has two at most (whole / *so*): 136 of 40 176 / 171, of 120 397 /
-//     370, 160 of 64 248 / 240, 176 of 64 254 / 246, 192 of 120 428 / 416.  Not where lists are short, for the fixed part is most of it
-//     (144 of 20 *121* / 123, 176 of 28 *148* / 151, 192 of 28 *152* / 158), nor where a CU would get three (189 of 42 *192* / 230, 190 of
-//     75 *312* / 364).  More units are whole: 208 of 64 *270* / 326, 240 of 28 *169* / 202;
-//   - up to four rounds, what a last round has of at most half: up to 64 units as quarters (288 of 64 499 / 371, 576 of 64 785 /
-//     674), more as halves (384 of 64 516 / 456, 896 of 64 1080 / 1033; 640 of 64 799 / 737).  A fuller or full one stays (512 of 64 *589* / 639 with 64 as quarters,
-//     768 *878* / 923, 1024 *1174* / 1223, 448 *541* / 548), but for lists of any length, whose units end at different times: 1024 of
-//     102 on average 2278 / *2110*;
+//   - as many shares as fit in one round: 18 units of 24 tiles 64 / 46 / 41 / *38*,
+//     26 of 52 174 / 120 / 97 / *82*, 36 of 17 129 / 106 / *95* / 108, 45 of 7 75 / 59 / *56* / 71, 90 of 12 104 / *81* / 89, 120 of 96 360 /
+//     *234* / 267.  With the empty shares launched as well these were too many for a round: 36 heads of 28 blocks, 252 halves, 14
+//     kept 94 -> 76, 12 heads of 84, 42 kept 149 -> 119, 6 heads 105 -> 80 (quarters), 9 heads of 28, 14 kept 54 -> 49 (eighths);
+//   - up to three quarters of a round, as halves but for 64 as quarters, so that a CU has two at most (whole / *so*): 136 of 40 176 / *171*, 152 of 30 130 / *118*, 160 of 64 248 / *240*, 192 of 120 428 / *416*; lists of any length, whatever their average: 132 of 26
+//     232 / *167*, 165 of 6 165 / *130*, 168 of 17 368 / *246*, 180 of 29 220 / *185*.  Not where all lists are short, for the fixed part is most of it
+//     (144 of 8 *84* / 86, 160 of 3 *63* / 69, 171 of 18 *115* / 119, 180 of 9 *94* / 97; 156 of 16 *104* / 102), nor where a CU would get three
+//     (189 of 42 *192* / 230, 190 of 75 *312* / 364).  More units are whole: 208 of 64 *270* / 326, 240 of 28 *169* / 202;
+//   - up to four rounds, what a last round has of at most half: up to 64 units as quarters (288 of 64 499 / *371*, 576 of 64 785 /
+//     *674*), more as halves (384 of 64 516 / *456*, 896 of 64 1080 / *1033*, 640 of 64 799 / *737*).  Up to three quarters of a round, 64 as
+//     quarters, for units seldom last as long as one another (396 of 14 235 / *207*, 648 of 65 573 / *528*, 656 of 81 605 / *557*, 960 of
+//     256 2154 / *1998*, 414 of 9 169 / *161*; on 32 others from 4 % worse to 5 % better, 0.4 % better on average).  A fuller or full one
+//     stays (504 of 570 *4069* / 4510, of 65 *614* / 661, 750 of 300 *2026* / 2093; units that do last as long: 512 of 64 *589* / 639, 768 *878* / 923, 1024
+//     *1174* / 1223, but 448 541 / *548*).  Lists of any length, whose units end at different times: 64 as quarters (1024 of 102 on average
+//     2278 / *2110*), and in the second half of the second round all others as halves (64 as quarters / *so*: 408 of 56 455 / *391*, 418 of 88
+//     694 / *623*, 450 of 240 1457 / *1312*, 500 of 200 1716 / *1466*, 504 of 52 413 / *421*; not short ones, 420 of 14 *247* / 254);
 //   - and 64 as halves after that, for units differ in length: 5952 of 198 12080, *11918*, nothing dropped 20167, *20103*.
 constexpr int kCUs = 256;
-constexpr int kLongList = 36;
-// total: units of the launch; tiles: entries of a list (on average, where they are of any length); least: units are shared by at
-// least 2^least (LDS)
-inline Share share_out(long long total, long long tiles, bool any_length, int least) {
-  int split[2] = {0, 0};
+constexpr int kShortList = 24;
+// head_groups: groups of 64 queries of a head; tiles: entries of a list (on average, where they are of any length); least: units are
+// shared by at least 2^least (LDS)
+inline Share share_out(long long heads, long long head_groups, long long tiles, bool any_length, int least) {
+  const long long total = heads * ((head_groups + 7) / 8);
+  if (least == 0 && head_groups <= 4) least = 1;      // (whole units would be half empty, with nothing for the waves of that half to do)
+  int all = 3;
+  while (all > least && heads * ((head_groups + (8 >> all) - 1) / (8 >> all)) > kCUs) --all;
+  if (all) {
+    const int head_shares = (int)((head_groups + (8 >> all) - 1) / (8 >> all));
+    return {0, {all, all}, (unsigned)(heads * head_shares), head_shares};
+  }
+  int split[2] = {0, 0};                              // (more than kCUs halves, hence more than kCUs / 2 units, from here on)
   long long rest = 0;
-  if (total <= kCUs / 8) split[0] = 3;
-  else if (total <= kCUs / 4) split[0] = 2;
-  else if (total <= kCUs / 2) split[0] = 1;
-  else if (total <= kCUs / 4 * 3 && (total % 8 == 0 || total < kCUs / 4 * 3 - 8) && tiles >= kLongList) split[0] = 1, split[1] = 2, rest = kCUs / 4;
-  else if (total > kCUs && total <= 4 * kCUs) {
+  if (total <= kCUs / 4 * 3) {
+    // (beyond 184 units rounding up to eights leaves a third share to some CU unless there is nothing to round)
+    if ((total % 8 == 0 || total < kCUs / 4 * 3 - 8) && (any_length || tiles >= kShortList)) split[0] = 1, split[1] = 2, rest = kCUs / 4;
+  } else if (total > kCUs && total <= 4 * kCUs) {
     const int last = (int)(total % kCUs);
-    if (last > kCUs / 4 && last <= kCUs / 2) split[1] = 1, rest = last;
-    else if (any_length || (last > 0 && last <= kCUs / 4)) split[1] = 2, rest = kCUs / 4;
+    if (any_length && total > kCUs / 2 * 3 && total <= 2 * kCUs && tiles >= kShortList) split[0] = 1, split[1] = 2, rest = kCUs / 4;
+    else if (last > kCUs / 4 && last <= kCUs / 2) split[1] = 1, rest = last;
+    else if (any_length || (last > 0 && last <= kCUs / 4 * 3)) split[1] = 2, rest = kCUs / 4;
   } else if (total > kCUs) split[1] = 1, rest = kCUs / 4;
-  for (int& x : split) x = x < least ? least : x;
+  if (rest >= total) rest = 0;
   if (rest && split[0]) rest += (total - rest) % 8;
-  Share s = {(int)(rest ? total - rest : (total + 7) / 8 * 8), {split[0], split[1]}, 0};
+  Share s = {(int)(rest ? total - rest : (total + 7) / 8 * 8), {split[0], split[1]}, 0, 0};
   s.grid = ((unsigned)s.first << split[0]) + ((unsigned)((rest + 7) / 8 * 8) << split[1]);
   return s;
 }

@@ -15,15 +15,17 @@ extern "C" void place(int n, int T, int log_fg, int per_frame, int* out) {
   const UnitPlace u = unit_place(n, T, log_fg, per_frame);
   for (int w = 0; w < 1 << log_fg; ++w) { out[2 * w] = unit_pos(u, w); out[2 * w + 1] = unit_frame(u, w); }
 }
-extern "C" void share(long long total, long long tiles, int any_length, int least, int* out) {
-  const Share s = share_out(total, tiles, any_length, least);
-  out[0] = s.first; out[1] = s.split[0]; out[2] = s.split[1]; out[3] = (int)s.grid;
+extern "C" int left(int T, int fg, int per_frame) { return left_units(T, fg, per_frame); }
+extern "C" void share(long long heads, long long head_groups, long long tiles, int any_length, int least, int* out) {
+  const Share s = share_out(heads, head_groups, tiles, any_length, least);
+  out[0] = s.first; out[1] = s.split[0]; out[2] = s.split[1]; out[3] = (int)s.grid; out[4] = s.head_shares;
 }
-extern "C" void shares(long long total, long long tiles, int any_length, int least, int grid, int* out) {
-  const Share s = share_out(total, tiles, any_length, least);
+extern "C" void shares(long long heads, long long head_groups, long long tiles, int any_length, int least, int per_head, int left,
+                       int grid, int* out) {
+  const Share s = share_out(heads, head_groups, tiles, any_length, least);
   for (int b = 0; b < grid; ++b) {
-    const ShareOf w = share_of(s, b);
-    out[3 * b] = w.unit; out[3 * b + 1] = w.lsub; out[3 * b + 2] = w.sub;
+    const ShareOf w = share_of(s, b, per_head, left);
+    out[4 * b] = w.head; out[4 * b + 1] = w.unit; out[4 * b + 2] = w.lsub; out[4 * b + 3] = w.sub;
   }
 }
 """
@@ -36,8 +38,8 @@ def lib(tmp_path_factory):
     src.write_text(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(out)], check=True)
     f = ctypes.CDLL(str(out))
-    f.share.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
-    f.shares.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    f.share.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 2 + [ctypes.c_void_p]
+    f.shares.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 5 + [ctypes.c_void_p]
     return f
 
 
@@ -67,38 +69,65 @@ def test_every_block_has_one_place(lib, log_fg, per_frame):
 
 @pytest.mark.parametrize("least", [0, 1])
 @pytest.mark.parametrize("any_length", [0, 1])
-@pytest.mark.parametrize("tiles", [3, 200])
+@pytest.mark.parametrize("tiles", [1, 3, 200])
 def test_every_share_has_one_workgroup(lib, tiles, any_length, least):
-    s = (ctypes.c_int * 4)()
-    for total in list(range(1, 540)) + [1023, 1024, 1025, 5952]:
-        lib.share(total, tiles, any_length, least, s)
-        first, split0, split1, grid = s
-        assert min(split0, split1) >= least and grid > 0
-        out = (ctypes.c_int * (3 * grid))()
-        lib.shares(total, tiles, any_length, least, grid, out)
+    s = (ctypes.c_int * 5)()
+    cases = [(total, 8, 1, 8) for total in list(range(1, 540)) + [1023, 1024, 1025, 5952]]               # (heads, T, positions, blocks to a unit)
+    cases += [(heads, T, pf, fg) for heads in (1, 3, 12, 36, 250, 300) for T in (1, 2, 3, 7, 9) for pf in (1, 2, 5, 28, 42) for fg in (8, 4)]
+    for heads, T, per_frame, fg in cases:
+        head_groups, per_head, left = T * per_frame * (8 // fg), lib.units(T, fg, per_frame), lib.left(T, fg, per_frame)
+        lib.share(heads, head_groups, tiles, any_length, least, s)
+        first, split0, split1, grid, head_shares = s
+        assert min(split0, split1) >= least and grid > 0 and first >= 0
+        out = (ctypes.c_int * (4 * grid))()
+        lib.shares(heads, head_groups, tiles, any_length, least, per_head, left, grid, out)
+
+        def groups_in(unit):                                    # (places fill up from the front, and only the last left-over unit is not full)
+            return 8 if not left or unit != left - 1 else (T % fg * per_frame * (8 // fg) - 1) % 8 + 1
+
         seen, xcd, idle = set(), {}, 0
         for b in range(grid):
-            unit, lsub, sub = out[3 * b:3 * b + 3]
-            if unit >= total:
+            head, unit, lsub, sub = out[4 * b:4 * b + 4]
+            assert head >= 0 and 0 <= unit < per_head and 0 <= sub < 1 << lsub
+            if head >= heads or sub * (8 >> lsub) >= groups_in(unit):
                 idle += 1
                 continue
-            assert lsub == (split0 if unit < first else split1) and 0 <= sub < 1 << lsub
-            assert (unit, sub) not in seen
-            seen.add((unit, sub))
-            assert xcd.setdefault(unit, b % 8) == b % 8
-        assert len(seen) == sum(1 << (split0 if u < first else split1) for u in range(total))
-        assert idle <= 7 << max(split0, split1)
+            assert lsub == (split0 if head_shares or head * per_head + unit < first else split1)
+            assert (head, unit, sub) not in seen
+            seen.add((head, unit, sub))
+            xcd.setdefault((head, unit), []).append(b % 8)
+        want = sum(-(-groups_in(u) // (8 >> (split0 if head_shares or h * per_head + u < first else split1)))
+                   for h in range(heads) for u in range(per_head))
+        assert len(seen) == want
+        if head_shares:
+            # shares of a unit stay together where a unit's are all there are: two heads meet where a head has an odd number
+            assert idle == 0
+            apart = sum(len(set(x)) > 1 for x in xcd.values())
+            assert apart <= (0 if head_shares % (1 << split0) == 0 else len(xcd)) + 8
+        else:
+            assert all(len(set(x)) == 1 for x in xcd.values())
+            assert idle <= (7 << max(split0, split1)) + (heads << max(split0, split1))
 
 
 def test_full_rounds_are_not_shared(lib):
-    """Lists of one length: where the last of up to four rounds is empty or more than half full every unit is one workgroup, and no
-    CU gets a third share of a launch of less than a round."""
-    s = (ctypes.c_int * 4)()
-    for tiles in (3, 26, 40, 200):
-        for total in range(1, 1025):
-            lib.share(total, tiles, 0, 0, s)
-            first, split0, split1, grid = s
-            if total > 256 and (total % 256 == 0 or total % 256 > 128) or 192 < total <= 256:
-                assert (first, split0, grid) == ((total + 7) // 8 * 8, 0, (total + 7) // 8 * 8)
-            if 128 < total <= 192:
-                assert grid <= 512 and (split0 == 0 or tiles >= 36)
+    """Lists of one length: where the last of up to four rounds is empty or more than three quarters full every unit is one workgroup.  A launch
+    of less than a round leaves no CU a third share, and lists of any length in it are shared however short on average."""
+    s = (ctypes.c_int * 5)()
+    for tiles in (3, 26, 200):
+        for any_length in (0, 1):
+            for total in range(1, 1025):
+                lib.share(total, 8, tiles, any_length, 0, s)
+                first, split0, split1, grid, head_shares = s
+                if not any_length and total > 256 and (total % 256 == 0 or total % 256 > 192) or 192 < total <= 256:
+                    assert (first, split0, grid) == ((total + 7) // 8 * 8, 0, (total + 7) // 8 * 8)
+                if 128 < total <= 192:
+                    assert grid <= 512 and (split0 == 1) == ((any_length or tiles >= 24) and (total < 184 or total % 8 == 0))
+
+
+def test_empty_shares_do_not_count(lib):
+    """Twelve heads of 84 groups are 132 units, but 252 halves with a group: one round.  Likewise quarters and eighths."""
+    s = (ctypes.c_int * 5)()
+    for heads, head_groups, split in [(12, 84, 1), (12, 88, 0), (13, 84, 0), (9, 28, 3), (10, 28, 2), (18, 28, 2), (19, 28, 1),
+                                      (128, 1, 3), (256, 1, 3), (257, 1, 1), (128, 2, 3), (256, 2, 2), (256, 4, 1), (128, 8, 1), (1000, 4, 1), (1000, 5, 0)]:
+        lib.share(heads, head_groups, 8, 0, 0, s)
+        assert s[1] == split and s[4] == (-(-head_groups // (8 >> split)) if split else 0), (heads, head_groups, list(s))
