@@ -158,9 +158,10 @@ int da_permute(const da_problem* p, const void* X, void* Y, int mode, void* stre
  * (nothing is dropped when all scores of a row are within that range of each other).
  * A score that leaves float32 at its lower end (finite inputs, for instance a mask put into one channel of K) weighs
  * nothing; a row whose scores all do is NaN.
- * The bf16 kernel keeps the block lists of four query blocks (two when block = 128) in LDS, which
- * bounds the problem: roughly g/2 + 4*min(g, 4k) bytes must fit in 32 KB (g up to about 7000 with
- * nothing dropped, far more when k << g), and g * block / 64 < 2^22; larger problems return DA_ERR_UNSUPPORTED.  Its waits for tiles are
+ * The bf16 kernel keeps the block lists of eight query blocks (four when block = 128) in LDS, or of four (two) where those of
+ * eight do not fit, which bounds the problem: roughly g/2 + 4*min(g, 4k) bytes (block = 128: g/2 + 8*min(g, 2k)) must fit in
+ * 32 KB (g up to about 7000 with nothing dropped, far more when k << g), and g * block / 64 < 2^18; larger
+ * problems return DA_ERR_UNSUPPORTED.  Its waits for tiles are
  * bounded; should one ever run out (no valid input makes it), the rows concerned are written as NaN.
  * Lists that are not what is asked for above (entries outside [0,g), repeats) give unspecified results but no access
  * outside the arrays: an entry that is no block number is left out.

@@ -95,7 +95,7 @@ constexpr int RING = 8;
 constexpr int SLOT = K_TILE;
 constexpr int RING_BYTES = RING * SLOT;           // 128 KB
 constexpr int LDS_TOTAL = 160 * 1024;
-constexpr int AUX_BYTES = LDS_TOTAL - RING_BYTES; // bitmaps + union list + ring state
+static_assert(AUX_BYTES == LDS_TOTAL - RING_BYTES, "bitmaps + union list + ring state");
 constexpr int WAVES = 8;
 constexpr int O_STRIDE = D * 2 + 16;              // padded row stride of the output staging area
 constexpr float kScale = 0.08838834764831845f;                      // 1/sqrt(128)
@@ -104,7 +104,7 @@ constexpr float kLazy = 8.0f;                     // move the running max only p
 constexpr float kDropLog2 = 14.0f;                // all keys dropped from a row together weigh less than 2^-14 of its largest term
 constexpr int kSpinLimit = 1 << 20;
 constexpr int kClaimed = 1 << 20;                    // a slot's reader count while its entry is not known yet
-constexpr int kValidBit = 18, kMemberBit = 24;       // fields of a union entry (key sub-blocks are numbered below 2^18)
+constexpr int kMemberBit = 24;                       // fields of a union entry: the key sub-block below kValidBit, its valid keys, who wants it
 constexpr int kPeekTiles = 8;                       // lists of at least so many tiles per wave: all waves of a group look at the first one
 constexpr int kFollowTiles = 24;                    // lists of fewer tiles, one wave each: the reference follows every larger score
 constexpr int kNearTiles = 2;                       // and in so many tiles it is the largest of each 32 keys,
@@ -233,7 +233,7 @@ __device__ __forceinline__ int lanes_before(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
 }
 
-// valid slots of block j (blocks are numbered below 2^22)
+// valid slots of block j (blocks are numbered below 2^18)
 __device__ __forceinline__ int valid_slots(const Geo& q, int per_frame, int j) {
   const int rr = j - small_div(j, per_frame) * per_frame;
   const int bi = small_div(rr, q.gw), bj = rr - bi * q.gw;
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   int first_of[4];                                    // (where a group has one wave nobody looks)
 #pragma unroll
   for (int w = 0; w < 4; ++w) first_of[w] = __builtin_amdgcn_readfirstlane(first[w]) & ((1 << kTaker) - 1);
-  // one wave brings the K tile of union entry u into ring slot u % RING
+  // one wave brings the K tile of union entry u into the given slot of the ring
   auto issue_tile = [&](int u, int slot) {
     const unsigned e = (unsigned)__builtin_amdgcn_readfirstlane((int)ulist[u]);
     // how many waves will read the tile: one of each live group that holds the entry, and the others where they look
@@ -1098,30 +1098,17 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
 
 }  // namespace ring
 
-// LDS left beside the ring, where a workgroup takes 8 / 2^split groups of 64 queries: their blocks' bitmaps of g bits and the
-// union list.
-static long long aux_bytes(const Geo& q, bool any_length, int split) {
-  const int sub = q.block / ring::BS;
-  const long long blocks = 8 / sub >> split ? 8 / sub >> split : 1;
-  const long long union_max = sub * (any_length ? (long long)q.g : q.g < blocks * q.k ? q.g : blocks * q.k);
-  return blocks * 4 * ((q.g + 31) / 32) + 4 * union_max + 512;
-}
-
 // 0: the kernel cannot run this problem, else 1.
 int attn_bf16_ring_fits(const Geo& q, bool any_length) {
   if (q.block != ring::BS && q.block != 2 * ring::BS) return 0;
-  const int sub = q.block / ring::BS, fg = 4 / sub;
-  if ((long long)q.g * sub >= (1 << ring::kValidBit)) return 0;
-  const long long union_max = sub * ((long long)q.g < (long long)fg * q.k || any_length ? q.g : (long long)fg * q.k);
-  return 4LL * 4 * ((q.g + 31) / 32) + 4 * union_max + 512 <= ring::AUX_BYTES;
+  return ring::lists_fit(q.g, q.k, q.block / ring::BS, any_length);
 }
 
 hipError_t launch_attn_bf16_ring(const Geo& q, const void* Qp, const void* Kp, const void* Vt, const int32_t* idx,
                                  const int32_t* row_ptr, long long cap, void* Op, float* lse, bool direct,
                                  unsigned long long* tile_counts, hipStream_t s) {
   const int sub = q.block / ring::BS;
-  int least = 0;
-  while (least < 1 && aux_bytes(q, row_ptr != nullptr, least) > ring::AUX_BYTES) ++least;
+  const int least = ring::least_split(q.g, q.k, sub, row_ptr != nullptr);
   const ring::Share share = ring::share_out((long long)q.B * q.H, (long long)q.g * sub, (long long)q.k * sub, row_ptr != nullptr, least);
   const float skip = log2f((float)q.k * (float)q.block) + ring::kDropLog2;
   auto go = [&](auto kernel) {

@@ -38,6 +38,23 @@ DA_HOST_DEVICE inline UnitPlace unit_place(int n, int T, int log_fg, int per_fra
 DA_HOST_DEVICE inline int unit_pos(const UnitPlace& u, int w) { return u.pos0 + (((u.first + w) * u.recip) >> 8); }
 DA_HOST_DEVICE inline int unit_frame(const UnitPlace& u, int w) { return u.frame0 + u.first + w - (((u.first + w) * u.recip) >> 8) * u.frames; }
 
+// LDS beside the ring that a workgroup of 8 / 2^split groups of 64 queries needs: the bitmaps of its query blocks (g bits each), the
+// union of their lists (an entry is four bytes; sub of them to a block) and 512 bytes of the ring's state.
+constexpr int AUX_BYTES = 32 * 1024;
+constexpr int kValidBit = 18;                         // (key sub-blocks are numbered below 2^18; the lists take more LDS than there is long before)
+inline long long aux_bytes(long long g, long long k, int sub, bool any_length, int split) {
+  const long long blocks = 8 / sub >> split ? 8 / sub >> split : 1;
+  const long long union_max = sub * (any_length || g < blocks * k ? g : blocks * k);
+  return blocks * 4 * ((g + 31) / 32) + 4 * union_max + 512;
+}
+// What the kernel runs is what it ran when four groups of 64 queries were a workgroup's most: four bitmaps, and the union of four
+// (sub = 2: two) lists.  Halves of a unit always fit then, whole ones up to 6451 blocks where nothing is dropped.
+inline bool lists_fit(long long g, long long k, int sub, bool any_length) {
+  const long long blocks = 4 / sub, union_max = sub * (any_length || g < blocks * k ? g : blocks * k);
+  return g * sub < (1 << kValidBit) && 4LL * 4 * ((g + 31) / 32) + 4 * union_max + 512 <= AUX_BYTES;
+}
+inline int least_split(long long g, long long k, int sub, bool any_length) { return aux_bytes(g, k, sub, any_length, 0) > AUX_BYTES; }
+
 // Either all units of a launch are shared by 2^split[0] workgroups each, and then shares without a group have none: `head_shares` to a
 // head.  (A workgroup that finds nothing to do still takes a CU for 6 us, as much as all of the LDS needs to change hands: 250 heads of
 // one block as eighths 21 -> 69 us if seven of eight are empty.)  Or (head_shares 0) the first `first` units are shared by 2^split[0]

@@ -218,28 +218,60 @@ def test_full_config_whole_map(name, heads, check):
     torch.cuda.empty_cache()
 
 
-def test_many_blocks_ascending_walk():
-    """A problem whose union lists are too long for the balanced walk's extra arrays (the kernel
-    then walks in ascending order): 3000 one-patch frames, 800 key blocks kept per query block."""
-    import torch
-    w = W.Workload("many_blocks", B=1, H=1, d=128, T=3000, fh=8, fw=8, sparsity=0.0, seed=11)
+@pytest.fixture(scope="module")
+def one_patch_frames():
+    """7000 frames of one patch; the leading ones serve as shorter problems."""
     say("many_blocks: generating")
-    Q, K, V = W.make_qkv(w)
-    p = da.problem(w.B, w.H, w.T, w.fh, w.fw, w.d, keep_blocks=800)
+    return W.make_qkv(MANY_BLOCKS)
+
+
+MANY_BLOCKS = W.Workload("many_blocks", B=1, H=1, d=128, T=7000, fh=8, fw=8, sparsity=0.0, seed=11)
+
+
+@pytest.mark.parametrize("T,keep,any_length", [(3000, 800, False), (6440, 6440, False), (7000, 1700, False), (7000, 7000, False),
+                                               (7000, 1700, True)])
+def test_many_blocks(one_patch_frames, T, keep, any_length):
+    """The longest lists and unions: near the limit of the LDS beside the ring for whole units (6440 blocks, nothing dropped) and for units
+    that have to be shared because eight lists do not fit (7000)."""
+    import torch
+    w = MANY_BLOCKS.with_(T=T)
+    Q, K, V = (x[:, :, :T * 64] for x in one_patch_frames)
+    p = da.problem(w.B, w.H, w.T, w.fh, w.fw, w.d, keep_blocks=keep)
     dims = da.da_derive(p)
-    assert dims.g == 3000 and dims.k == 800
-    ws = torch.empty(da.da_workspace_size(p), dtype=torch.uint8, device="cuda")
+    assert dims.g == T and dims.k == keep
+    say(f"many_blocks {T} blocks, {keep} kept, {'lists of any length' if any_length else 'k per row'}")
+    dev = [to_dev(x, w.dtype) for x in (Q, K, V)]
     O = empty((1, 1, dims.n, w.d), w.dtype)
-    idx = torch.empty((1, 1, dims.g, dims.k), dtype=torch.int32, device="cuda")
-    da.da_forward(p, *(to_dev(x, w.dtype) for x in (Q, K, V)), O, ws, idx)
-    torch.cuda.synchronize()
-    say("many_blocks: GPU done")
-    ref = HeadRef(w, Q[0, 0], K[0, 0], V[0, 0], keep_blocks=800)
-    assert np.array_equal(idx.cpu().numpy()[0, 0], ref.idx)
-    rows = [0, 1, 2, 3, 1499, 2996, 2997, 2998, 2999]
-    want = ref.attention(rows=rows)
+    O.fill_(float("nan"))
+    ref = HeadRef(w, Q[0, 0], K[0, 0], V[0, 0], keep_blocks=keep)
+    rows = sorted({0, 1, 2, 3, 7, 8, T // 2 - 1, T // 2, *range(T - 4, T)})
+    if any_length:
+        sz = da.da_global_sizes(p)
+        ws = torch.empty(sz.forward_ws, dtype=torch.uint8, device="cuda")
+        row_ptr = torch.empty((1, 1, T + 1), dtype=torch.int32, device="cuda")
+        cols = torch.empty((1, 1, sz.cap), dtype=torch.int32, device="cuda")
+        da.da_forward_global(p, *dev, O, ws, row_ptr, cols)
+        torch.cuda.synchronize()
+        say("many_blocks: GPU done")
+        rp, c = row_ptr[0, 0].cpu().numpy(), cols[0, 0].cpu().numpy()
+        want_rp, want_c, _ = oa.select_blocks_global(ref.logits, sz.budget)
+        assert np.array_equal(rp, want_rp) and np.array_equal(c[:rp[-1]], want_c)
+        rows = sorted({*rows, int(np.argmax(np.diff(rp))), int(np.argmin(np.diff(rp)))})
+        want = ref.attention(rows=rows, idx=oa.lists_of(want_rp, want_c))
+    else:
+        ws = torch.empty(da.da_workspace_size(p), dtype=torch.uint8, device="cuda")
+        idx = torch.empty((1, 1, dims.g, dims.k), dtype=torch.int32, device="cuda")
+        da.da_forward(p, *dev, O, ws, idx)
+        torch.cuda.synchronize()
+        say("many_blocks: GPU done")
+        assert np.array_equal(idx.cpu().numpy()[0, 0], ref.idx)
+        want = ref.attention(rows=rows)
+    assert bool(torch.isfinite(O).all())
     got = to_host_f64(O[0, 0], w.dtype)
     for r in rows:
         slots = np.arange(r * 64, (r + 1) * 64)
         emax, emean = output_error(got[ref.perm[slots]], want[slots])
         assert emax <= 2e-2 and emean <= 2e-3, (r, emax, emean)
+    assert da.da_wait_failures() == 0
+    del ws, O, dev
+    torch.cuda.empty_cache()

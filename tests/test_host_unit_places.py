@@ -15,6 +15,9 @@ extern "C" void place(int n, int T, int log_fg, int per_frame, int* out) {
   const UnitPlace u = unit_place(n, T, log_fg, per_frame);
   for (int w = 0; w < 1 << log_fg; ++w) { out[2 * w] = unit_pos(u, w); out[2 * w + 1] = unit_frame(u, w); }
 }
+extern "C" long long aux(long long g, long long k, int sub, int any_length, int split) { return aux_bytes(g, k, sub, any_length, split); }
+extern "C" int fits(long long g, long long k, int sub, int any_length) { return lists_fit(g, k, sub, any_length); }
+extern "C" int least(long long g, long long k, int sub, int any_length) { return least_split(g, k, sub, any_length); }
 extern "C" int left(int T, int fg, int per_frame) { return left_units(T, fg, per_frame); }
 extern "C" void share(long long heads, long long head_groups, long long tiles, int any_length, int least, int* out) {
   const Share s = share_out(heads, head_groups, tiles, any_length, least);
@@ -39,6 +42,8 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(out)], check=True)
     f = ctypes.CDLL(str(out))
     f.share.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 2 + [ctypes.c_void_p]
+    f.aux.argtypes = f.fits.argtypes = f.least.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int] * 3
+    f.fits.argtypes, f.least.argtypes, f.aux.restype = f.fits.argtypes[:4], f.least.argtypes[:4], ctypes.c_longlong
     f.shares.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 5 + [ctypes.c_void_p]
     return f
 
@@ -131,3 +136,44 @@ def test_empty_shares_do_not_count(lib):
                                       (128, 1, 3), (256, 1, 3), (257, 1, 1), (128, 2, 3), (256, 2, 2), (256, 4, 1), (128, 8, 1), (1000, 4, 1), (1000, 5, 0)]:
         lib.share(heads, head_groups, 8, 0, 0, s)
         assert s[1] == split and s[4] == (-(-head_groups // (8 >> split)) if split else 0), (heads, head_groups, list(s))
+
+
+@pytest.mark.parametrize("any_length", [0, 1])
+@pytest.mark.parametrize("sub", [1, 2])
+def test_what_fits_also_fits_as_it_is_shared(lib, sub, any_length):
+    """The lists of every problem that is accepted fit beside the ring at the least split and at any finer one, and an entry's key number has
+    its bits; whole units are kept as long as they fit."""
+    reached = set()
+    for g in sorted({*range(1, 9000, 61), *range(6400, 7200, 7), 30000, 65535, 65536, 131072}):
+        for k in sorted({1, 2, 7, 100, 800, 801, 1700, 2000, g // 10, g // 4, g // 2, g} & set(range(1, g + 1))):
+            if not lib.fits(g, k, sub, any_length):
+                continue
+            least = lib.least(g, k, sub, any_length)
+            reached.add(least)
+            assert all(lib.aux(g, k, sub, any_length, split) <= 32 * 1024 for split in range(least, 4))
+            assert least == 0 or lib.aux(g, k, sub, any_length, 0) > 32 * 1024
+            assert g * sub < 2 ** 18
+            if any_length or k == g:
+                assert 4 * sub * g <= 32 * 1024
+    assert reached == ({0} if sub == 2 and any_length else {0, 1})   # (two frames' lists of any length are as long as four's)
+    # the sizes of the GPU tests at the limit
+    if sub == 1:
+        assert [lib.least(g, g, 1, 0) for g in (6440, 7000)] == [0, 1] and lib.least(7000, 1700, 1, any_length) == 1
+        assert lib.fits(7000, 7000, 1, any_length) and not lib.fits(7200, 7200, 1, any_length)
+
+
+def test_the_gpu_tests_reach_every_share(lib):
+    """The launches of the GPU tests are shared out as those tests say, so a change of the rule cannot empty them unseen."""
+    import test_gpu_attention_pairs as pairs
+    import test_gpu_attention_shares as shares
+    import test_gpu_attention_units as units
+    launches = [(s[:5] + (keep,), s[5]) for s, keeps in pairs.SHARED.items() for keep in keeps]
+    launches += [*shares.SHARED.items(), *units.SHARED.items()]
+    s, reached = (ctypes.c_int * 5)(), set()
+    for (T, fh, fw, pw, heads, keep), want in launches:
+        g, sub = T * -(-fh // 8) * -(-fw // pw), pw // 8
+        lib.share(heads, g * sub, min(keep, g) * sub, 0, lib.least(g, min(keep, g), sub, 0), s)
+        alike = s[4] > 0 or s[0] >= heads * -(-g * sub // 8)
+        assert ((s[1],) if alike else (s[1], s[2])) == want, (T, fh, fw, pw, heads, keep, list(s))
+        reached.add((sub, want))
+    assert reached >= {(sub, x) for sub in (1, 2) for x in ((3,), (2,), (1,), (0,), (1, 2))} | {(1, (0, 2)), (2, (0, 2)), (1, (0, 1))}
