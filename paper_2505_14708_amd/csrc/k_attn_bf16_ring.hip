@@ -872,11 +872,14 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
   // 63 kept 1.048 -> 0.990, 1.013 -> 0.977, 1.001 -> 0.996; 8x16 windows, 24 kept 1.049 -> 0.981, 1.018 -> 0.970, 1.002 -> 0.994.
   // Tried besides: short lists that only follow, up to 1.008; with one tile where each 32 keys have their own 1.003, with four
   // 1 to 2 % slower still.  Long ones that follow in the wave's own block alone, or have each 32 keys' own there, up to 1.013 and
-  // 1.001, and no faster.  What it costs (da_forward, us): 14 kept 97.4 -> 99.9, 3 kept 65.4 -> 67.2; 24 heads x 1980 blocks, 198 kept, peaked
-  // 11516 -> 11624, flat 19437 -> 19519.
+  // 1.001, and no faster.  What it costs (da_forward, us): 14 kept 100.6 -> 102.6, 3 kept 65.4 -> 67.2; 24 heads x 1980 blocks, 198 kept, peaked
+  // 11629 -> 11715, flat 19557 -> 19613.  (Worked out for each tile from what the rule goes by, which is then kept through the loop, 11835
+  // and 19694, and 23 heads x 14 frames of 20x71, 8x16, half kept, 1734 against 1711.)
   auto walk = [&](auto queries) {
     constexpr int NQ = decltype(queries)::value;
+    // (one number and a count of tiles: what the rule goes by need not be kept through the loop)
     const bool follow = parts == 1 && k * SUB < kFollowTiles;
+    int lazy = __float_as_int(parts > 1 ? (few ? 0.f : kLazy) : follow ? -INFINITY : 0.f), until = parts > 1 ? 1 : kNearTiles;
     const int look_at = parts > 1 ? __builtin_amdgcn_readfirstlane(first[lgroup]) : -1;
     if (live && look_at >= 0 && part != look_at >> kTaker) {
       const int u = look_at & ((1 << kTaker) - 1);
@@ -903,6 +906,10 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
       const unsigned long long ours = __ballot(is_ours);
       unsigned long long mine = __ballot(is_ours && wave_of_turn(before + lanes_before(ours), SUB, parts) == part);
       before += __popcll(ours);
+      if (parts == 1 && !follow && base == 0) {       // (the own blocks, eight at most, are the first entries)
+        until = __popcll(mine & ((1ull << n_own) - 1ull));
+        if (until == 0) lazy = __float_as_int(kLazy);
+      }
       while (mine) {
         const int i = (int)__builtin_ctzll(mine);
         mine &= mine - 1;
@@ -917,15 +924,12 @@ __global__ __launch_bounds__(512, 2) void attn_bf16_ring_kernel(Geo q, const uns
         const int nv = (int)((e >> kValidBit) & 63u) + 1;
         const unsigned kaddr = kbase + (unsigned)slot * SLOT;
         const unsigned char* v = Vbh + (long long)(e & ((1u << kValidBit) - 1u)) * V_TILE;
-        const unsigned done = tally & 0xffffu;        // (NQ for each tile)
-        const float lazy = parts > 1   ? few && done == 0 ? 0.f : kLazy
-                           : follow    ? done < NQ * kNearTiles ? -INFINITY : 0.f
-                           : u < n_own ? 0.f : kLazy;
         int kept = 0;
 #pragma unroll 1
         for (int half = 0; half < 2 && 32 * half < nv; ++half) {
-          half_tile<NQ>(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, lazy, qf, o, st, kept);
+          half_tile<NQ>(kaddr + half * (SLOT / 2), v + half * (V_TILE / 2), nv - 32 * half, skip, __int_as_float(lazy), qf, o, st, kept);
         }
+        if (--until == 0) lazy = __float_as_int(lazy < 0 ? 0.f : kLazy);   // (bits: minus infinity is the one below zero)
         tally += NQ + ((unsigned)(nv > 32 ? NQ * kept : 2 * NQ * kept) << 16);
         leave(slot);
         // (Only waves that are waiting for a tile ask for tiles: having every wave look for room after each of
