@@ -193,8 +193,8 @@ __global__ __launch_bounds__(kPoolThreads, SMALL ? 2 : 1) void pool_kernel(Geo q
 // With K in block order already (no Kp), short launches gain as much (2 x 28 blocks 38.6 -> 37.1, 8 x 60 63.2 -> 59.8), longer ones lose
 // (24 x 84 162 -> 165, 76 x 84 222 -> 228, 8 x 392 711 -> 717): the two streams of reads run better one after the other there.
 // The line, kInPlaceBlocks, lies where it makes no difference (36 x 28 71.0 and 71.6).
-// The largest launches are the same either way: 24 x 1980 11.97 and 11.98 ms, 24 x 990 of 128 slots 19.07 and 19.12 ms (the launch
-// itself 655 us against 606 for the two, but nothing of it is left in the call's time).
+// Where each of the three fills the chip by itself there is little in it: 24 x 720 blocks 2.42 and 2.43 ms, 24 x 1260 6.42 and 6.41, 24 x 1980 15.41
+// and 15.37, 12 x 3900 29.97 and 29.90, 24 x 990 of 128 slots 11.58 and 11.58 (the launch itself 657 us against 650 for the two at 24 x 1980).
 constexpr int kPrepThreads = 256;
 template <bool SMALL, bool MAXP>
 __global__ __launch_bounds__(kPrepThreads, SMALL ? 2 : 1) void prepare_kernel(Geo q, const void* __restrict__ Q,

@@ -107,7 +107,9 @@ DA_HOST_DEVICE inline ShareOf share_of(const Share& s, int b, int per_head, int 
 //     stays (504 of 570 *4069* / 4510, of 65 *614* / 661, 750 of 300 *2026* / 2093; units that do last as long: 512 of 64 *589* / 639, 768 *878* / 923, 1024
 //     *1174* / 1223, but 448 541 / *548*).  Lists of any length, whose units end at different times: 64 as quarters (1024 of 102 on average
 //     2278 / *2110*), and in the second half of the second round all others as halves (64 as quarters / *so*: 408 of 56 455 / *391*, 418 of 88
-//     694 / *623*, 450 of 240 1457 / *1312*, 500 of 200 1716 / *1466*, 504 of 52 413 / *421*; not short ones, 420 of 14 *247* / 254);
+//     694 / *623*, 450 of 240 1457 / *1312*, 500 of 200 1716 / *1466*, 504 of 52 413 / *421*; not short ones, 420 of 14 *247* / 254.  Towards the end of
+//     that range it depends on how peaked they are: 456 of 96 peaked 504 / *518*, 480 of 101 586 / *613*, 504 of 144 696 / *726*, but with q
+//     scaled by 1/4 432 of 96 572 / *552*, 480 670 / *640*, 512 of 204 1886 / *1883*; up to 450, peaked or not, 2 to 8 % are gained);
 //   - and 64 as halves after that, for units differ in length: 5952 of 198 12080, *11918*, nothing dropped 20167, *20103*.
 constexpr int kCUs = 256;
 constexpr int kShortList = 24;
