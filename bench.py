@@ -20,7 +20,7 @@ heads of 128, 8x8 pooling, 90 % sparsity, bf16.  Prints ONE JSON line.
                                 synthetic inputs it takes away a lot.  (Tiles of at most 32 valid keys
                                 are half the work: the first product's are counted from the lists, the
                                 second product's taken to be dropped as often as the others.  The one
-                                look per list that further waves take at its first tile is left out);
+                                look that the other waves of a shared list take at its block's own tile is left out);
                  no_drop.frac   the same launch, same block lists, with Q scaled by 2^-5 so that the
                                 scores of a row lie close together and nothing is dropped: what the
                                 kernel does on inputs whose attention is not peaked.
@@ -52,7 +52,7 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E, published
 # rocprofv3) but copied from a counter run of this program: FETCH_SIZE and WRITE_SIZE, scaled by what the same
 # counters read for the row-copy kernel of known size in the same run.  The file named holds the figures and the
 # command; it is regenerated whenever the kernel changes.  Workloads without a counter run: null.
-ATTN_TRAFFIC = {"720p_hunyuan": {"read": 42.54e9, "written": 0.743e9, "no_drop_read": 80.21e9, "no_drop_written": 0.730e9,
+ATTN_TRAFFIC = {"720p_hunyuan": {"read": 42.56e9, "written": 0.743e9, "no_drop_read": 80.44e9, "no_drop_written": 0.730e9,
                                  "source": "profiles/pmc_attn_720p_hunyuan.txt"}}
 FLOP_PER_MFMA = 2.0 * 32 * 32 * 16     # v_mfma_f32_32x32x16_bf16
 

@@ -105,7 +105,7 @@ constexpr float kDropLog2 = 14.0f;                // all keys dropped from a row
 constexpr int kSpinLimit = 1 << 20;
 constexpr int kClaimed = 1 << 20;                    // a slot's reader count while its entry is not known yet
 constexpr int kMemberBit = 24;                       // fields of a union entry: the key sub-block below kValidBit, its valid keys, who wants it
-constexpr int kPeekTiles = 8;                       // lists of at least so many tiles per wave: all waves of a group look at the first one
+constexpr int kPeekTiles = 8;                       // lists of at least so many tiles per wave: all waves of a group look at their own block first
 constexpr int kFollowTiles = 24;                    // lists of fewer tiles, one wave each: the reference follows every larger score
 constexpr int kNearTiles = 2;                       // and in so many tiles it is the largest of each 32 keys,
 constexpr float kBelowTop = 90.0f;                  // no further below the largest score so far than this (11 powers of two)
@@ -245,7 +245,7 @@ struct Soft {
   // half tile may be minus infinity (finite operands whose product leaves the range), and those keys weigh exp2(-inf) = 0,
   // not exp2(-inf + inf).
   float m;
-  // Largest score seen so far, in what was carried out and in a first tile that was only looked at; +inf for a pad query.  (The
+  // Largest score seen so far, in what was carried out and in a tile that was only looked at; +inf for a pad query.  (The
   // reference trails the scores the wave has carried out by at most kLazy powers of two, or by kBelowTop in the first tiles of
   // a short list; it may start up to the drop rule's cut below a score that was only looked at.)
   float top;
